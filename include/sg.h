@@ -100,14 +100,18 @@ typedef struct sg_problem {
  *   tile              spatial tiles of the inner solver: 32 = banded tiles (up to
  *                     64 columns including the Chebyshev halo; 128 rows in FP64,
  *                     256 in FP32; degrees <= 16),
- *                     16 = 16 x 16 tiles, 0 = automatic (banded tiles, with
+ *                     16 = 16 x 16 tiles, 0 = automatic: on grids up to
+ *                     n_e = 1025 the same iteration in the sine basis, in
+ *                     which K_0 and the preconditioner are diagonal (equal
+ *                     iterates and counts up to rounding); on larger grids,
+ *                     or with inner_maxit below n_e / 96, banded tiles, with
  *                     64-row bands for launches of fewer tiles than compute
- *                     units; 16 x 16 tiles above degree 16).
+ *                     units.
  *   warm_start        0: every inner solve starts from zero. 1: the inner
  *                     solves of the up sweep of Algorithm 1 start from the
  *                     down-sweep solution of the same level, and those of the
  *                     backward sweep of block Gauss-Seidel from the forward
- *                     sweep's (banded tiles; 16 x 16 tiles start from zero).
+ *                     sweep's (16 x 16 tiles start from zero).
  *                     The stopping test stays relative to the right-hand side.
  *   inner_rtol        relative residual at which an inner solve stops
  *                     (recursive residual, Euclidean norm); <= 0 runs
@@ -118,8 +122,8 @@ typedef struct sg_problem {
  *                     applied and replays the graph in every later outer
  *                     iteration and solve (until the options or the schedule
  *                     change). Needs a stream other than the default one. The
- *                     inner launches of a captured action are ordinary (not
- *                     cooperative) launches of at most the resident grid.
+ *                     tiled inner launches of a captured action are ordinary
+ *                     (not cooperative) launches of at most the resident grid.
  *                     Results are the same bit for bit.
  *   reserved          must be 0. */
 typedef struct sg_opts {
@@ -150,9 +154,10 @@ typedef struct sg_stats {
   double ms_matvec;           /* time in SG matvecs */
   double ms_inner;            /* device time of the inner PCG launches (HIP events on the stream; with
                                  use_graph, of the replayed preconditioner actions as a whole) */
-  double inner_bytes;         /* algorithmic bytes of those launches: per column (9 its + 6) n w
-                                 with banded tiles, (10 its + 6) n w with 16 x 16 tiles (3 n w
-                                 when it stops at once; n w more from a warm start) */
+  double inner_bytes;         /* algorithmic bytes of those launches, per column: 10 n w in the sine
+                                 basis (15 n w from a warm start), whatever the iterations;
+                                 (9 its + 6) n w with banded tiles, (10 its + 6) n w with 16 x 16
+                                 tiles (3 n w when it stops at once; n w more from a warm start) */
   int64_t inner_launches;     /* number of inner PCG launches */
 } sg_stats;
 
@@ -268,7 +273,8 @@ int sg_adjoint_grad(sg_handle h, const double* U, const double* w_mean, const do
  *                y-marching kernel with 1, 2 or 4 grid segments per XCD or the
  *                automatic count; band kernels with 32..128 row chunks per
  *                band, where the grid shape allows them);
- *   flags bit 1: the inner PCG (tile kind 16 or 32 where the Chebyshev halo
+ *   flags bit 1: the inner PCG (with tile = 0 the sine basis where it serves
+ *                the grid; tile kind 16 or 32 where the Chebyshev halo
  *                allows 32; block count automatic, half the CUs, or whole
  *                columns per block), timed on
  *                the columns of the largest chaos level with a constant
@@ -283,7 +289,8 @@ typedef struct sg_tune_report {
   int32_t mv_param;        /* row chunks per band (variants 0, 1); segments per XCD (2; 0 = automatic);
                               100 * rows per piece + waves per CU (3; 0 waves = all resident);
                               node rows per piece (4) */
-  int32_t pcg_tile;        /* inner tile kind (32 banded, 16 square) */
+  int32_t pcg_tile;        /* inner tile kind (32 banded, or the sine basis where tile = 0 was the
+                              fastest; 16 square) */
   int32_t pcg_max_blocks;  /* cap on the blocks of an inner launch (0 = as many as fit; -1 = whole
                               columns per block for launches whose columns fill at least 3/4 of the
                               resident blocks, no cap for smaller ones) */

@@ -1,0 +1,709 @@
+// Inner PCG in the sine basis: transforms to and from the basis and the
+// iteration on the transformed columns.
+//
+// A solve is five launches: right-hand side -> [x pass] -> [y pass] -> spectral
+// right-hand side -> iteration -> spectral solution -> [y pass] -> [x pass].
+// A pass is a product with the sine matrix of each parity on folded data (FP64
+// or FP32 matrix instructions).
+//
+// Why: on the grid an iteration of degree d sweeps a column d times with halos
+// and meets two column-wide synchronisations; here it is a dozen operations per
+// pair of modes on values that never leave the registers. Measured at 256^2,
+// degree 16, FP64: the 220 columns of the top level to 1e-4 (about 30
+// iterations) 13.5 ms on banded tiles, 0.95 ms here; the benchmark's whole solve
+// 230 -> 25 ms; 28 columns of 100^2 unknowns at degree 8 730 -> 149 us.
+#include <algorithm>
+
+#include "sg_internal.h"
+#include "sg_device.h"
+
+namespace sgk {
+
+namespace {
+
+constexpr long kSpinLimit = 1L << 26;  // bounded waits: a stuck group aborts the launch
+constexpr int kSumWidth = 4;           // sums exchanged at once by the blocks of a group
+constexpr unsigned long long kEmpty = 0x7ff8dead7ff8deadull;  // an exchange place without a value (a NaN)
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// 16 x 16 x 4 matrix instruction. Lane l holds A[l % 16][l / 16] and
+// B[l / 16][l % 16]; register r of the result is D[row(l, r)][l % 16].
+template <typename T>
+struct Mac;
+template <>
+struct Mac<double> {
+  using V = d4;
+  __device__ static __forceinline__ V mac(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  __device__ static __forceinline__ int row(int lane, int r) { return (lane >> 4) + 4 * r; }
+};
+template <>
+struct Mac<float> {
+  using V = f4;
+  __device__ static __forceinline__ V mac(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  __device__ static __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
+};
+
+// ---------------------------------------------------------------------------
+// Tables
+// ---------------------------------------------------------------------------
+
+// Wave number of spectral index a.
+__device__ __forceinline__ int wave_number(int a, int ho) { return a < ho ? 2 * a + 1 : 2 * (a - ho) + 2; }
+
+template <typename T>
+__global__ void sine_pack_kernel(SineSizes z, int n_e, T* pack) {
+  // pack order: fwd[0], fwd[1], inv[0], inv[1]
+  const long total = 4 * z.pack;
+  const int steps = 4 * z.nt;
+  const double scale = sqrt(2.0 / n_e);
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
+    const int which = (int)(i / z.pack);
+    const long o = i % z.pack;
+    const int lane = (int)(o % 64);
+    const int step = (int)(o / 64 % steps), tile = (int)(o / 64 / steps);
+    const int p = which & 1;
+    int j = 4 * step + lane / 16, k = 16 * tile + lane % 16;  // space index, index within the parity
+    if (which >= 2) {
+      const int u = j;
+      j = k;
+      k = u;
+    }
+    const int len = p ? z.he : z.ho;
+    double v = 0.0;
+    if (j < len && k < len) {
+      const long kw = p ? 2 * k + 2 : 2 * k + 1;
+      const long m = (long)(j + 1) * kw % (2L * n_e);
+      v = scale * sinpi((double)m / n_e);
+    }
+    pack[i] = (T)v;
+  }
+}
+
+__global__ void sine_tile_kernel(SineSizes z, int4* tiles) {
+  const int nte = (z.he + 15) / 16;
+  const long tri0 = (long)z.nt * (z.nt + 1) / 2, tri1 = (long)nte * (nte + 1) / 2;
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < z.ntiles; i += (long)gridDim.x * blockDim.x) {
+    int4 d = {0, 0, 0, 0};
+    if (i < tri0 + tri1) {
+      const bool even = i >= tri0;
+      const int len = even ? nte : z.nt;
+      long q = even ? i - tri0 : i;
+      int I = 0;
+      while (q >= len - I) q -= len - I++;
+      const int J = I + (int)q, base = even ? z.ho : 0, end = even ? z.nx : z.ho;
+      d = {base + 16 * I, base + 16 * J, end, end};
+    } else if (i < tri0 + tri1 + (long)z.nt * nte) {
+      const long q = i - tri0 - tri1;
+      d = {16 * (int)(q / nte), z.ho + 16 * (int)(q % nte), z.ho, z.nx};
+    }
+    tiles[i] = d;
+  }
+}
+
+// Row and column of a slot of a tile, and whether it holds a mode pair.
+__device__ __forceinline__ bool slot_place(const int4& d, int in_tile, int& a, int& b) {
+  a = d.x + (in_tile >> 4);
+  b = d.y + (in_tile & 15);
+  return a < d.z && b < d.w && a <= b;
+}
+
+__global__ void sine_slot_kernel(SineSizes z, SineConsts c, const int4* tiles, double* t, double* ipi) {
+  for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < z.slots; i += (long)gridDim.x * blockDim.x) {
+    int a, b;
+    double tv = 0.0, iv = 0.0;
+    if (slot_place(tiles[i / 256], (int)(i % 256), a, b)) {
+      // eigenvalue of D^-1 K_0, (8 - 2 c_i - 2 c_j - 4 c_i c_j) / 8 with
+      // c = cos(k pi / n_e), written through 1 - c = 2 sin^2(k pi / 2 n_e)
+      const double si = sinpi(wave_number(a, z.ho) / (2.0 * c.n_e)), sj = sinpi(wave_number(b, z.ho) / (2.0 * c.n_e));
+      const double ui = 2.0 * si * si, uj = 2.0 * sj * sj;
+      const double mu = (6.0 * (ui + uj) - 4.0 * ui * uj) / 8.0;
+      double S = 1.0 / c.diag, W = S * c.inv_theta, Z = W;
+      for (int j = 1; j < c.degree; ++j) {
+        S -= mu * W;
+        W = c.chebA[j] * W + c.chebB[j] * S;
+        Z += W;
+      }
+      tv = mu * c.diag * Z;
+      iv = 1.0 / Z;
+    }
+    t[i] = tv;
+    ipi[i] = iv;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Transform passes
+// ---------------------------------------------------------------------------
+
+constexpr int kPassThreads = 512;
+
+// Bound by the matrix cores and the loads that feed them: 220 columns of 255^2
+// take 120 to 130 us a pass in FP64 (29 TFLOP/s of folded products, 1.8 TB/s), 60
+// to 80 us in FP32. Two blocks fit a compute unit up to 128 modes per parity, so
+// that one block's loads run under the other's products.
+//
+// Pass along x: `rows` rows of nx values. Forward: a block folds R = 16 RT rows
+// into the parity parts in LDS and multiplies them by the sine matrices from
+// the right; inverse: it multiplies the two halves of a spectral row and
+// unfolds the results. A wave takes one 16-column tile of both parities, so
+// that the unfolding stays within a lane.
+template <typename T, bool INV, int RT>
+__global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab, const T* in, T* out, long rows,
+                                                              unsigned long long* ex, unsigned* ticket, int* status,
+                                                              int nex) {
+  using M = Mac<T>;
+  using V = typename M::V;
+  extern __shared__ unsigned char smem[];
+  const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt, ld = hp + 4;
+  constexpr int R = 16 * RT;
+  T* Q = reinterpret_cast<T*>(smem);  // [2][R][ld]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  if (!INV && nex >= 0 && blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < nex; i += blockDim.x) ex[i] = kEmpty;
+    if (threadIdx.x == 0) {
+      *status = 0;
+      *ticket = 0u;
+    }
+  }
+  const long r0 = (long)blockIdx.x * R;
+  for (int r = wave; r < R; r += nw) {
+    const bool on = r0 + r < rows;
+    const T* src = in + (r0 + r) * nx;
+    for (int j = lane; j < hp; j += 64) {
+      T u = T(0), v = T(0);
+      if (INV) {
+        if (on && j < ho) u = src[j];
+        if (on && j < he) v = src[ho + j];
+      } else if (on && j < ho) {
+        u = src[j];
+        if (j < he) {
+          const T m = src[nx - 1 - j];
+          v = u - m;
+          u = u + m;
+        }
+      }
+      Q[r * ld + j] = u;
+      Q[(R + r) * ld + j] = v;
+    }
+  }
+  __syncthreads();
+  const int steps = 4 * nt;
+  const T* pk0 = INV ? tab.inv[0] : tab.fwd[0];
+  const T* pk1 = INV ? tab.inv[1] : tab.fwd[1];
+  for (int ct = wave; ct < nt; ct += nw) {
+    V acc[2][RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      acc[0][i] = V{0, 0, 0, 0};
+      acc[1][i] = V{0, 0, 0, 0};
+    }
+    const T* f0 = pk0 + (long)ct * steps * 64 + lane;
+    const T* f1 = pk1 + (long)ct * steps * 64 + lane;
+    const T* q = Q + (lane & 15) * ld + (lane >> 4);
+#pragma unroll 4
+    for (int k = 0; k < steps; ++k) {
+      const T b0 = f0[64 * k], b1 = f1[64 * k];
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        acc[0][i] = M::mac(q[16 * i * ld + 4 * k], b0, acc[0][i]);
+        acc[1][i] = M::mac(q[(R + 16 * i) * ld + 4 * k], b1, acc[1][i]);
+      }
+    }
+    const int c = 16 * ct + (lane & 15);
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const long row = r0 + 16 * i + M::row(lane, r);
+        if (row >= rows) continue;
+        T* dst = out + row * nx;
+        const T u = acc[0][i][r], v = acc[1][i][r];
+        if (INV) {
+          if (c < he) {
+            dst[c] = u + v;
+            dst[nx - 1 - c] = u - v;
+          } else if (c < ho) {
+            dst[c] = u;
+          }
+        } else {
+          if (c < ho) dst[c] = u;
+          if (c < he) dst[ho + c] = v;
+        }
+      }
+  }
+}
+
+// Pass along y of one column's nx x nx array: a block takes CW = 16 CT array
+// columns, folds (forward) or splits (inverse) their rows into the parity parts
+// in LDS and multiplies by the sine matrices from the left. With 32 columns
+// the two halves of every other row are exchanged, so that the four rows of a
+// matrix operand fall into different LDS banks.
+template <typename T, bool INV, int CT>
+__global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab, const T* in, T* out, long n,
+                                                              int strips) {
+  using M = Mac<T>;
+  using V = typename M::V;
+  extern __shared__ unsigned char smem[];
+  const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt;
+  constexpr int CW = 16 * CT;
+  T* Q = reinterpret_cast<T*>(smem);  // [2][hp][CW]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int col = blockIdx.x / strips;
+  const int c0 = (blockIdx.x - col * strips) * CW;
+  const T* src = in + (long)col * n;
+  T* dst = out + (long)col * n;
+  auto place = [&](int j, int c) { return j * CW + (CT == 2 ? c ^ ((j & 1) << 4) : c); };
+  {
+    const int c = threadIdx.x % CW;
+    const bool on = c0 + c < nx;
+    for (int j = threadIdx.x / CW; j < hp; j += blockDim.x / CW) {
+      T u = T(0), v = T(0);
+      if (INV) {
+        if (on && j < ho) u = src[(long)j * nx + c0 + c];
+        if (on && j < he) v = src[(long)(ho + j) * nx + c0 + c];
+      } else if (on && j < ho) {
+        u = src[(long)j * nx + c0 + c];
+        if (j < he) {
+          const T m = src[(long)(nx - 1 - j) * nx + c0 + c];
+          v = u - m;
+          u = u + m;
+        }
+      }
+      Q[place(j, c)] = u;
+      Q[hp * CW + place(j, c)] = v;
+    }
+  }
+  __syncthreads();
+  const int steps = 4 * nt;
+  const T* pk0 = INV ? tab.inv[0] : tab.fwd[0];
+  const T* pk1 = INV ? tab.inv[1] : tab.fwd[1];
+  for (int rt = wave; rt < nt; rt += nw) {
+    V acc[2][CT];
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      acc[0][i] = V{0, 0, 0, 0};
+      acc[1][i] = V{0, 0, 0, 0};
+    }
+    const T* f0 = pk0 + (long)rt * steps * 64 + lane;
+    const T* f1 = pk1 + (long)rt * steps * 64 + lane;
+#pragma unroll 4
+    for (int k = 0; k < steps; ++k) {
+      const T a0 = f0[64 * k], a1 = f1[64 * k];
+      const int j = 4 * k + (lane >> 4);
+#pragma unroll
+      for (int i = 0; i < CT; ++i) {
+        const int o = place(j, 16 * i + (lane & 15));
+        acc[0][i] = M::mac(a0, Q[o], acc[0][i]);
+        acc[1][i] = M::mac(a1, Q[hp * CW + o], acc[1][i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < CT; ++i) {
+      const int c = c0 + 16 * i + (lane & 15);
+      if (c >= nx) continue;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int j = 16 * rt + M::row(lane, r);
+        const T u = acc[0][i][r], v = acc[1][i][r];
+        if (INV) {
+          if (j < he) {
+            dst[(long)j * nx + c] = u + v;
+            dst[(long)(nx - 1 - j) * nx + c] = u - v;
+          } else if (j < ho) {
+            dst[(long)j * nx + c] = u;
+          }
+        } else {
+          if (j < ho) dst[(long)j * nx + c] = u;
+          if (j < he) dst[(long)(ho + j) * nx + c] = v;
+        }
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Iteration
+// ---------------------------------------------------------------------------
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+// Sum over the wave in a fixed order, the same in every lane.
+__device__ __forceinline__ double wave_sum(double v) {
+  v += dpp_f64<0xB1>(v);
+  v += dpp_f64<0x4E>(v);
+  v += dpp_f64<0x141>(v);
+  v += dpp_f64<0x140>(v);
+  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+}
+
+// Sums over a column: the block's threads, then the blocks of its group (in
+// a fixed order), the same bits in every thread of the group. A group
+// of one block needs its own barrier only. Otherwise the blocks exchange their
+// sums through memory that every compute unit sees coherently (agent-scope
+// atomics): a published value is its own flag, since the place it goes to holds
+// kEmpty before and no sum is stored with those bits. Three exchange buffers
+// take turns. Passing the wait of one exchange means that every block has read
+// the one before it, so a block clears its places of that one, waits until the
+// stores are done and only then publishes again: nobody finds an old value.
+// The wait is bounded and ends the launch with an error status.
+__device__ __forceinline__ void agent_store(unsigned long long* p, unsigned long long v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct ColumnSums {
+  double (*red)[kSineThreads / 64][kSumWidth];  // two buffers, used in turn
+  double (*all)[kSumWidth];                     // group sums, two buffers
+  unsigned long long* ex;                       // the group's exchange [3][groups][kSumWidth]
+  int* status;
+  int* sflag;
+  int groups, g;
+  unsigned epoch;
+  bool dead;
+
+  __device__ unsigned long long* slot(unsigned e, int k) const { return ex + ((long)(e % 3) * groups + k) * kSumWidth; }
+
+  __device__ void sum(double (&v)[kSumWidth]) {
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    double (*buf)[kSumWidth] = red[epoch & 1];
+#pragma unroll
+    for (int i = 0; i < kSumWidth; ++i) v[i] = wave_sum(v[i]);
+    // all four before the branch (sunk past it, they would keep every slot's terms alive)
+    asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+    if (lane == 0)
+#pragma unroll
+      for (int i = 0; i < kSumWidth; ++i) buf[wv][i] = v[i];
+    __syncthreads();
+    // lane 4 w + i (and lane 32 + 4 w + i) holds sum i of wave w
+    double t = buf[(lane >> 2) & 7][lane & 3];
+    t += dpp_f64<0x128>(t);  // row_ror:8
+    t += dpp_f64<0x124>(t);  // row_ror:4
+    if (groups == 1) {
+#pragma unroll
+      for (int i = 0; i < kSumWidth; ++i) v[i] = lane_f64(t, i) + lane_f64(t, 16 + i);
+      ++epoch;
+      return;
+    }
+    double (*out)[kSumWidth] = all + (epoch & 1);
+    if (wv == 0) {
+      // lane i < 4 publishes sum i; then lanes read the group's places, 64 at a time
+      t += __shfl_xor(t, 16);
+      if (lane < kSumWidth) {
+        unsigned long long bits = (unsigned long long)__double_as_longlong(t);
+        if (bits == kEmpty) bits = 0x7ff8000000000000ull;
+        __builtin_amdgcn_s_waitcnt(0);  // this lane's clearing store of the last exchange is done
+        agent_store(slot(epoch, g) + lane, bits);
+      }
+      double s = 0.0;
+      int ok = dead ? 0 : 1;
+      const unsigned long long* src = slot(epoch, 0);
+      for (int k0 = 0; k0 < groups * kSumWidth; k0 += 64) {
+        const int k = k0 + lane;
+        unsigned long long bits = 0;
+        if (k < groups * kSumWidth) {
+          long spins = 0;
+          while ((bits = __hip_atomic_load(src + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kEmpty && ok) {
+            __builtin_amdgcn_s_sleep(1);
+            if (++spins > kSpinLimit) ok = 0;
+          }
+        }
+        // lane 4 k + i holds sum i of block k: add the four blocks of each row of lanes, then the rows
+        double val = __longlong_as_double((long long)bits);
+        val += dpp_f64<0x128>(val);  // row_ror:8
+        val += dpp_f64<0x124>(val);  // row_ror:4
+        if (groups > 4) {
+          val += __shfl_xor(val, 16);
+          val += __shfl_xor(val, 32);
+        }
+        s += val;
+      }
+      ok = __all(ok);
+      if (!ok && lane == 0) atomicExch(status, 1);
+      if (lane < kSumWidth) {
+        (*out)[lane] = s;
+        if (epoch > 0) agent_store(slot(epoch + 2, g) + lane, kEmpty);  // the place of exchange epoch - 1
+      }
+      if (lane == 0) *sflag = ok;
+    }
+    __syncthreads();
+    if (*sflag == 0) dead = true;
+#pragma unroll
+    for (int i = 0; i < kSumWidth; ++i) v[i] = lane_f64((*out)[i], 0);
+    ++epoch;
+  }
+};
+
+// One column at a time per group of blocks. Every slot keeps, for its pair of
+// modes, rho = the residual polynomial and phi = the direction polynomial at
+// the pair's eigenvalue (r = rho r_0, p = pi phi r_0 with pi the factor of the
+// preconditioner), and xi = sum alpha phi, the solution polynomial. With the
+// weight w = the sum of the pair's r_0^2
+//   r.z = sum v rho^2,  r.r = sum v rho^2 / pi,  p.q = sum v t phi^2,
+// v = pi w and t the eigenvalue of M K_0: one multiple of r_0 per pair stands
+// for all vectors of the iteration. p.q of the next direction p' = z + beta p is
+// z.K z + 2 beta z.K p + beta^2 p.q, so a single pass over the slots makes an
+// iteration (its rounding error is that of the three terms, at most cond(M K_0)
+// times p'.q'). All of a block's slots stay in registers (1 / pi and, beyond 11
+// slots a thread, t in LDS). Slots without a mode have v = 0 and t = 0.
+// Bound by the chain of an iteration: about 0.6 us of arithmetic on 18 slots a
+// thread and 1.8 us for the sums across the group (255^2: four blocks a column,
+// 2.4 us an iteration; the 220 columns of a large launch go through 64 groups in
+// four turns, 10.6 us per iteration of all). With one block a column, whose 68
+// slots a thread stream v, t and 1 / pi, an iteration took 15.8 us for one column
+// (cache bandwidth of one compute unit) and 23.4 us for 220.
+template <typename T, int NR>
+__global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A, int ngroups) {
+  constexpr bool TREG = NR <= 11;
+  extern __shared__ unsigned char smem[];
+  __shared__ double red[2][kSineThreads / 64][kSumWidth], all[2][kSumWidth];
+  __shared__ int sflag;
+  const int tid = threadIdx.x;
+  const int G = A.tab.groups;
+  // The blocks of a group wait for each other, so groups form in the order in
+  // which blocks start: whatever else holds compute units, at most one group of
+  // a launch is incomplete, and the complete ones run to their end.
+  int place_ = blockIdx.x;
+  if (G > 1) {
+    if (tid == 0) sflag = (int)atomicAdd(A.sc.arrivals, 1u);
+    __syncthreads();
+    place_ = __builtin_amdgcn_readfirstlane(sflag);
+    __syncthreads();
+  }
+  const int group = place_ / G, g = place_ - group * G;
+  const int nx = A.tab.nx;
+  const long sbase = (long)g * NR * kSineThreads;  // this block's first slot
+  const int4* tiles = A.tab.tiles + sbase / 256;
+  const int lane = tid & 63, w0 = __builtin_amdgcn_readfirstlane(tid >> 6) * NR;
+  const double* tt = A.tab.t + sbase + w0 * 64 + lane;  // element e at 64 e
+  const double* ip = A.tab.ipi + sbase + w0 * 64 + lane;
+  // row and column of element e (its 64 slots are a quarter of a tile)
+  auto place = [&](int e, int& a, int& b) { return slot_place(tiles[(w0 + e) >> 2], ((w0 + e) & 3) * 64 + lane, a, b); };
+  double* lds = reinterpret_cast<double*>(smem) + tid;
+  ColumnSums cs{red, all, reinterpret_cast<unsigned long long*>(A.sc.part) + (long)group * G * 3 * kSumWidth,
+                A.sc.status, &sflag, G, g, 0u, false};
+  for (int c = group; c < A.ncols; c += ngroups) {
+    T* s = A.s + (long)c * A.n;
+    const T* s0 = A.s0 + (long)c * A.n;
+    // ---- start: weights, b.b, r.r, r.z, z.K z (warm: r = b - K_0 x in place)
+    double sums[kSumWidth] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+    for (int e = 0; e < NR; ++e) {
+      int a, b;
+      const double iv = ip[64 * e];
+      double v = 0.0;
+      if (place(e, a, b)) {
+        const long i1 = (long)a * nx + b, i2 = (long)b * nx + a;
+        double b1 = s[i1], b2 = a == b ? 0.0 : (double)s[i2];
+        sums[0] += b1 * b1 + b2 * b2;
+        const double tv = tt[64 * e];
+        if (A.warm) {
+          const double kap = tv * iv;
+          b1 -= kap * s0[i1];
+          s[i1] = (T)b1;
+          if (a != b) {
+            b2 -= kap * s0[i2];
+            s[i2] = (T)b2;
+          }
+        }
+        const double w = b1 * b1 + b2 * b2;
+        v = w / iv;
+        sums[1] += w;
+        sums[2] += v;
+        sums[3] = fma(v, tv, sums[3]);
+      }
+      lds[e * kSineThreads] = v;
+    }
+    double rho[NR], phi[NR], xi[NR], rv[NR], rt[TREG ? NR : 1];
+#pragma unroll
+    for (int e = 0; e < NR; ++e) {
+      if (e % 4 == 0) __builtin_amdgcn_sched_barrier(0);
+      rv[e] = lds[e * kSineThreads];
+      rho[e] = 1.0;  // v = t = 0 where there is no mode
+      phi[e] = 0.0;
+      xi[e] = 0.0;
+      lds[e * kSineThreads] = ip[64 * e];
+      if constexpr (TREG) rt[e] = tt[64 * e];
+      else lds[(NR + e) * kSineThreads] = tt[64 * e];
+    }
+    cs.sum(sums);
+    const double bb = sums[0];
+    double rr = sums[1], rz = sums[2], pq = sums[3], beta = 0.0;
+    int it = 0;
+    for (;; ++it) {
+      if (cs.dead || it == A.maxit || bb == 0.0 || sqrt(rr) <= A.rtol * sqrt(bb)) break;
+      if (!(pq > 0.0) || !isfinite(pq)) break;  // breakdown: the iterate so far
+      const double alpha = rz / pq;
+      // p = z + beta p, r -= alpha q, and the sums r.r, r.z, z.K z, z.K p of the new residual
+      double q[kSumWidth] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int e = 0; e < NR; ++e) {
+        if (e % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // the LDS reads of four slots at a time
+        const double iv = lds[e * kSineThreads], tv = TREG ? rt[TREG ? e : 0] : lds[(NR + e) * kSineThreads];
+        phi[e] = fma(beta, phi[e], rho[e]);
+        xi[e] = fma(alpha, phi[e], xi[e]);
+        rho[e] = fma(-alpha * phi[e], tv, rho[e]);
+        const double vr = rv[e] * rho[e], z = vr * rho[e];
+        q[1] += z;
+        q[0] = fma(z, iv, q[0]);
+        q[2] = fma(z, tv, q[2]);
+        q[3] = fma(vr * tv, phi[e], q[3]);
+      }
+      cs.sum(q);
+      beta = q[1] / rz;
+      pq = fma(beta, fma(beta, pq, 2.0 * q[3]), q[2]);
+      rr = q[0];
+      rz = q[1];
+    }
+    if (tid == 0 && g == 0) A.sc.iters[c] = it;
+    // ---- solution: x = x_0 + pi xi r_0 (a zero right-hand side gives 0 also from a warm start)
+    const bool guess = A.warm && bb != 0.0;
+#pragma unroll
+    for (int e = 0; e < NR; ++e) lds[e * kSineThreads] = xi[e];
+#pragma unroll 2
+    for (int e = 0; e < NR; ++e) {
+      int a, b;
+      if (!place(e, a, b)) continue;
+      const double m = lds[e * kSineThreads] / ip[64 * e];
+      const long i1 = (long)a * nx + b, i2 = (long)b * nx + a;
+      double x1 = guess ? (double)s0[i1] : 0.0, x2 = guess ? (double)s0[i2] : 0.0;
+      if (it > 0) {
+        x1 = fma(m, (double)s[i1], x1);
+        x2 = fma(m, (double)s[i2], x2);
+      }
+      s[i1] = (T)x1;
+      if (a != b) s[i2] = (T)x2;
+    }
+  }
+}
+
+template <typename K>
+hipError_t allow_lds(K kfn, size_t bytes) {
+  if (bytes <= 64 * 1024) return hipSuccess;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(kfn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             (int)bytes);
+}
+
+template <typename T, bool INV>
+hipError_t x_pass(const SineArgs<T>& A, const T* in, T* out, int reset_groups, hipStream_t s) {
+  const int hp = 16 * A.tab.nt;
+  const long rows = (long)A.ncols * A.tab.nx;
+  const int threads = 64 * std::min(8, A.tab.nt);
+  // the first block clears the exchange and the ticket of the iteration that follows on the stream
+  unsigned long long* ex = reinterpret_cast<unsigned long long*>(A.sc.part);
+  const int nex = reset_groups == 0 ? -1 : A.tab.groups == 1 ? 0 : reset_groups * A.tab.groups * 3 * kSumWidth;
+  if (hp <= 256) {
+    const size_t sm = sizeof(T) * 2 * 32 * (hp + 4);
+    hipError_t e = allow_lds(sine_x_kernel<T, INV, 2>, sm);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sine_x_kernel<T, INV, 2>), dim3((unsigned)((rows + 31) / 32)), dim3(threads), sm, s, A.tab, in,
+                       out, rows, ex, A.sc.arrivals, A.sc.status, nex);
+  } else {
+    const size_t sm = sizeof(T) * 2 * 16 * (hp + 4);
+    hipError_t e = allow_lds(sine_x_kernel<T, INV, 1>, sm);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((sine_x_kernel<T, INV, 1>), dim3((unsigned)((rows + 15) / 16)), dim3(threads), sm, s, A.tab, in,
+                       out, rows, ex, A.sc.arrivals, A.sc.status, nex);
+  }
+  return hipGetLastError();
+}
+
+template <typename T, bool INV>
+hipError_t y_pass(const SineArgs<T>& A, const T* in, T* out, hipStream_t s) {
+  const int hp = 16 * A.tab.nt, nx = A.tab.nx;
+  const int threads = 64 * std::min(8, A.tab.nt);
+  if (hp <= 256) {
+    const size_t sm = sizeof(T) * 2 * hp * 32;
+    hipError_t e = allow_lds(sine_y_kernel<T, INV, 2>, sm);
+    if (e != hipSuccess) return e;
+    const int strips = (nx + 31) / 32;
+    hipLaunchKernelGGL((sine_y_kernel<T, INV, 2>), dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out,
+                       A.n, strips);
+  } else {
+    const size_t sm = sizeof(T) * 2 * hp * 16;
+    hipError_t e = allow_lds(sine_y_kernel<T, INV, 1>, sm);
+    if (e != hipSuccess) return e;
+    const int strips = (nx + 15) / 16;
+    hipLaunchKernelGGL((sine_y_kernel<T, INV, 1>), dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out,
+                       A.n, strips);
+  }
+  return hipGetLastError();
+}
+
+template <typename T, int NR>
+hipError_t pcg(const SineArgs<T>& A, int ngroups, hipStream_t s) {
+  auto kfn = sine_pcg_kernel<T, NR>;
+  const size_t sm = sizeof(double) * kSineThreads * (NR <= 11 ? NR : 2 * NR);
+  hipError_t e = allow_lds(kfn, sm);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(kfn, dim3((unsigned)(ngroups * A.tab.groups)), dim3(kSineThreads), sm, s, A, ngroups);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+template <typename T>
+void launch_sine_tables(const SineSizes& z, const SineConsts& k, T* pack, int4* tiles, double* t, double* ipi,
+                        bool packs, hipStream_t s) {
+  auto grid = [](long n) { return dim3((unsigned)std::min<long>((n + 255) / 256, 4096)); };
+  if (packs) {
+    hipLaunchKernelGGL(sine_pack_kernel<T>, grid(4 * z.pack), dim3(256), 0, s, z, k.n_e, pack);
+    hipLaunchKernelGGL(sine_tile_kernel, grid(z.ntiles), dim3(256), 0, s, z, tiles);
+  }
+  hipLaunchKernelGGL(sine_slot_kernel, grid(z.slots), dim3(256), 0, s, z, k, tiles, t, ipi);
+}
+
+template <typename T>
+hipError_t launch_sine(const SineArgs<T>& A, int num_cu, hipStream_t s) {
+  if (A.ncols <= 0) return hipSuccess;
+  const SineTables<T>& t = A.tab;
+  const SineSizes z = sine_sizes(t.nx);
+  if (t.nx < 1 || t.nx > kSineMaxNx || A.n != (long)t.nx * t.nx || t.ept != z.ept || t.groups != z.groups ||
+      t.nt != z.nt)
+    return hipErrorInvalidValue;
+  // one block per compute unit; a group then takes its columns in turn
+  const int ngroups = t.groups == 1 ? A.ncols : std::min(A.ncols, num_cu / t.groups);
+  if (ngroups < 1) return hipErrorInvalidValue;
+  hipError_t e = hipSuccess;
+  if (A.warm) {
+    e = x_pass<T, false>(A, A.x, A.w, 0, s);
+    if (e == hipSuccess) e = y_pass<T, false>(A, A.w, A.s0, s);
+    if (e != hipSuccess) return e;
+  }
+  e = x_pass<T, false>(A, A.b, A.w, ngroups, s);
+  if (e == hipSuccess) e = y_pass<T, false>(A, A.w, A.s, s);
+  if (e != hipSuccess) return e;
+  switch (t.ept) {
+    case 2: e = pcg<T, 2>(A, ngroups, s); break;
+    case 5: e = pcg<T, 5>(A, ngroups, s); break;
+    case 8: e = pcg<T, 8>(A, ngroups, s); break;
+    case 11: e = pcg<T, 11>(A, ngroups, s); break;
+    case 14: e = pcg<T, 14>(A, ngroups, s); break;
+    case 18: e = pcg<T, 18>(A, ngroups, s); break;
+    default: e = hipErrorInvalidValue;
+  }
+  if (e == hipSuccess) e = y_pass<T, true>(A, A.s, A.w, s);
+  if (e == hipSuccess) e = x_pass<T, true>(A, A.w, A.x, 0, s);
+  return e;
+}
+
+template void launch_sine_tables<double>(const SineSizes&, const SineConsts&, double*, int4*, double*, double*, bool,
+                                         hipStream_t);
+template void launch_sine_tables<float>(const SineSizes&, const SineConsts&, float*, int4*, double*, double*, bool,
+                                        hipStream_t);
+template hipError_t launch_sine<double>(const SineArgs<double>&, int, hipStream_t);
+template hipError_t launch_sine<float>(const SineArgs<float>&, int, hipStream_t);
+
+}  // namespace sgk

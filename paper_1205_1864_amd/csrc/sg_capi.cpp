@@ -90,6 +90,7 @@ struct Plan {
   size_t o_vec[7];
   size_t o_rw, o_zw;
   size_t o_pcg[6];
+  size_t o_sine_pack, o_sine_tiles, o_sine_t, o_sine_ipi;
   size_t o_part, o_arr, o_iters, o_status;
   size_t o_red_part, o_red_out;
   size_t total;
@@ -190,6 +191,12 @@ void make_plan(const sg_problem* pr, const sg_opts* op, Plan& pl) {
   pl.o_rw = L.take(isz * nP);
   pl.o_zw = L.take(op->inner_precision == 32 ? isz * nP : 0);
   for (int i = 0; i < 6; ++i) pl.o_pcg[i] = L.take(isz * pl.n * (long)pl.maxcols);
+  const sgk::SineSizes sz = sgk::sine_sizes(std::min(pl.nx, sgk::kSineMaxNx));
+  const bool sine = pl.nx <= sgk::kSineMaxNx;
+  pl.o_sine_pack = L.take(sine ? isz * 4 * sz.pack : 0);
+  pl.o_sine_tiles = L.take(sine ? sizeof(int4) * sz.ntiles : 0);
+  pl.o_sine_t = L.take(sine ? sizeof(double) * sz.slots : 0);
+  pl.o_sine_ipi = L.take(sine ? sizeof(double) * sz.slots : 0);
   pl.o_part = L.take(sizeof(double) * sgk::kPcgPartials * (long)pl.maxcols * pl.ntiles_max);
   pl.o_arr = L.take(sizeof(unsigned) * pl.maxcols);
   pl.o_iters = L.take(sizeof(int) * pl.maxcols);
@@ -518,6 +525,45 @@ int choose_tile(const sg_ctx* h, int degree) {
   return degree <= sgk::kBandMaxDegree ? 32 : 16;
 }
 
+// The sine basis costs four transform passes (n_e^3 operations a column) and next
+// to nothing per iteration, the tiles a full sweep of the column per iteration.
+// Measured where the two meet (FP64, degree 1, the worst for the transforms): 2
+// iterations at 256^2 (35 columns: 0.19 ms both), 5 at 512^2 (1.0 ms), 10 at
+// 1024^2 (20 columns: 4.3 ms), so an iteration cap below nx / 96 goes to the tiles.
+bool use_sine(const sg_ctx* h) {
+  return h->sine_ok && h->opts.tile == 0 && h->opts.inner_maxit * 96L >= h->nx;
+}
+
+template <typename T>
+sgk::SineTables<T> sine_tables(const sg_ctx* h) {
+  const sgk::SineSizes& z = h->sine;
+  const T* pk = (const T*)h->sine_pack;
+  return {z.nx, z.ho, z.he, z.nt, z.ept, z.groups, {pk, pk + z.pack}, {pk + 2 * z.pack, pk + 3 * z.pack},
+          h->sine_tiles, h->sine_t, h->sine_ipi};
+}
+template sgk::SineTables<double> sine_tables<double>(const sg_ctx*);
+template sgk::SineTables<float> sine_tables<float>(const sg_ctx*);
+
+// Builds the sine-basis tables on the handle's stream; without `packs` only the
+// slot tables, which depend on the preconditioner's degree.
+void build_sine_tables(sg_ctx* h, bool packs) {
+  sgk::PcgArgs<double> a{};
+  fill_pcg_consts<double>(h, a);
+  sgk::SineConsts k{};
+  k.n_e = h->n_e;
+  k.degree = effective_degree(h);
+  k.diag = a.c0;
+  k.inv_theta = a.inv_theta;
+  std::copy(a.chebA, a.chebA + sgk::kMaxCheb, k.chebA);
+  std::copy(a.chebB, a.chebB + sgk::kMaxCheb, k.chebB);
+  if (h->opts.inner_precision == 32)
+    sgk::launch_sine_tables<float>(h->sine, k, (float*)h->sine_pack, h->sine_tiles, h->sine_t, h->sine_ipi, packs,
+                                   h->stream);
+  else
+    sgk::launch_sine_tables<double>(h->sine, k, (double*)h->sine_pack, h->sine_tiles, h->sine_t, h->sine_ipi, packs,
+                                    h->stream);
+}
+
 int flush_inner(sg_ctx* h);
 
 // State vectors and scratch of the inner solver: by default the handle's part
@@ -542,7 +588,8 @@ int run_pcg(sg_ctx* h, const T* B, T* X, int ncols, int level_for_stats, std::ve
   if (ncols > buf.maxcols) return fail(SG_EINVAL, "too many columns for the inner solver");
   sgk::PcgArgs<T> a{};
   const int degree = effective_degree(h);
-  const int tile = choose_tile(h, degree);
+  const bool sine = use_sine(h);
+  const int tile = sine ? 0 : choose_tile(h, degree);
   a.nx = h->nx;
   a.n = h->n;
   a.ncols = ncols;
@@ -556,6 +603,21 @@ int run_pcg(sg_ctx* h, const T* B, T* X, int ncols, int level_for_stats, std::ve
   a.Z = (T*)buf.Z;
   a.sc = buf.sc;
   const int prec = sizeof(T) == 4 ? 32 : 64;
+  sgk::SineArgs<T> sa{};
+  if (sine) {
+    sa.tab = sine_tables<T>(h);
+    sa.n = h->n;
+    sa.ncols = ncols;
+    sa.b = B;
+    sa.x = X;
+    sa.s = (T*)buf.R0;
+    sa.s0 = (T*)buf.R1;
+    sa.w = (T*)buf.Z;
+    sa.maxit = h->opts.inner_maxit;
+    sa.rtol = h->opts.inner_rtol > 0.0 ? h->opts.inner_rtol : 0.0;
+    sa.warm = warm && h->opts.warm_start;
+    sa.sc = buf.sc;
+  }
   // automatic tiles: the band height by the rule for launches with few tiles
   a.rows = tile != 16 && h->opts.tile == 0 ? sgk::pcg_band_rows(h->nx, degree, prec, ncols, h->num_cu)
                                             : sgk::band_rows(prec, degree);
@@ -564,7 +626,7 @@ int run_pcg(sg_ctx* h, const T* B, T* X, int ncols, int level_for_stats, std::ve
   a.maxit = h->opts.inner_maxit;
   a.rtol = h->opts.inner_rtol > 0.0 ? h->opts.inner_rtol : 0.0;
   a.warm = warm && h->opts.warm_start && tile != 16;
-  fill_pcg_consts<T>(h, a);
+  if (!sine) fill_pcg_consts<T>(h, a);
   a.no_coop = h->capturing ? 1 : 0;
   // room for this launch's read-back, else settle the earlier ones first (not
   // possible inside a graph capture: the action is then too large to capture)
@@ -579,7 +641,8 @@ int run_pcg(sg_ctx* h, const T* B, T* X, int ncols, int level_for_stats, std::ve
   // events recorded by graph nodes cannot be timed: a captured action is timed as a whole
   const bool timed = !h->capturing;
   if (timed) SG_HIP(hipEventRecord(e0, h->stream));
-  SG_HIP(sgk::launch_pcg<T>(a, tile, h->pcg_max_blocks, h->stream));
+  if (sine) SG_HIP(sgk::launch_sine<T>(sa, h->num_cu, h->stream));
+  else SG_HIP(sgk::launch_pcg<T>(a, tile, h->pcg_max_blocks, h->stream));
   if (timed) SG_HIP(hipEventRecord(e1, h->stream));
   sg_ctx::PendingLaunch L{ncols, level_for_stats, tile, a.warm, (int)sizeof(T), h->iters_used, timed};
   SG_HIP(hipMemcpyAsync(h->iters_host + L.slot, buf.sc.iters, sizeof(int) * ncols, hipMemcpyDeviceToHost,
@@ -617,6 +680,13 @@ int flush_inner(sg_ctx* h) {
     for (int c = 0; c < L.ncols; ++c) {
       const int v = h->iters_host[L.slot + c];
       h->inner_it_acc += v;
+      if (L.tile == 0) {
+        // sine basis: four passes and the iteration each read and write a vector (warm: two more
+        // passes, and the iteration reads the guess)
+        h->inner_bytes_acc += (10.0 + (L.warm ? 5.0 : 0.0)) * (double)h->n * L.wsize;
+        mx = std::max(mx, v);
+        continue;
+      }
       // phase A reads z, p and x and writes p and x (and q with 16 x 16 tiles); phase B
       // reads r and p (q) and writes r and z; the start reads b and writes z and x (warm:
       // reads b and x, writes z and r); a column that stops after at least one iteration
@@ -1401,6 +1471,8 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
     const int band = h->opts.tile == 32 ? 32 : 0;
     std::vector<int> tiles = degree <= sgk::kBandMaxDegree ? std::vector<int>{band, 16}
                                                                                        : std::vector<int>{16};
+    // with the sine-basis solver the automatic choice is that solver, and banded tiles a candidate beside it
+    if (use_sine(h)) tiles = {0, 32, 16};
     // automatic grid, half the compute units, whole columns per block (large launches)
     std::vector<int> blocks = {0, std::max(1, h->num_cu / 2), -1};
     double best = 1e300;
@@ -1409,6 +1481,7 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
       for (int mb : blocks) {
         h->opts.tile = t;
         h->pcg_max_blocks = mb;
+        if (use_sine(h) && mb != 0) continue;  // its launches take no block cap
         int rc = h->opts.inner_precision == 32 ? run_pcg<float>(h, (const float*)h->rw, (float*)h->zw, ncols, -1)
                                                : run_pcg<double>(h, (const double*)h->rw, h->z, ncols, -1);
         if (rc) return rc;
@@ -1648,6 +1721,10 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   for (int i = 0; i < 7; ++i) *vecs[i] = (double*)(w + pl.o_vec[i]);
   h->rw = w + pl.o_rw;
   h->zw = op->inner_precision == 32 ? (void*)(w + pl.o_zw) : nullptr;
+  h->sine_pack = w + pl.o_sine_pack;
+  h->sine_tiles = (int4*)(w + pl.o_sine_tiles);
+  h->sine_t = (double*)(w + pl.o_sine_t);
+  h->sine_ipi = (double*)(w + pl.o_sine_ipi);
   void** pcgv[6] = {&h->pR0, &h->pR1, &h->pP0, &h->pP1, &h->pQ, &h->pZ};
   for (int i = 0; i < 6; ++i) *pcgv[i] = w + pl.o_pcg[i];
   h->pcg_maxcols = pl.maxcols;
@@ -1703,6 +1780,12 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   h->mj_lcol_d = (int*)(w + pl.o_mj_lcol);
   h->mj_lw_d = (double*)(w + pl.o_mj_lw);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess && h->nx <= sgk::kSineMaxNx) {
+    h->sine = sgk::sine_sizes(h->nx);
+    build_sine_tables(h, true);
+    e = hipGetLastError();
+    h->sine_ok = e == hipSuccess && h->sine.groups <= h->num_cu;
+  }
   if (e == hipSuccess && build_march_jobs(h, 0) != SG_OK) e = hipErrorUnknown;
   if (e == hipSuccess &&
       build_stage_tables(h, (sgk::StageTerm*)(w + pl.o_stg_terms), (sgk::StageSlot*)(w + pl.o_stg_slots),
@@ -1769,7 +1852,12 @@ int sg_set_opts(sg_handle h, const sg_opts* opts) {
   if (rc) return rc;
   if (opts->inner_precision != h->opts.inner_precision)
     return fail(SG_EINVAL, "inner precision is fixed at setup");
+  const bool degree_changed = opts->cheb_degree != h->opts.cheb_degree;
   h->opts = *opts;
+  if (degree_changed && h->sine_ok) {
+    build_sine_tables(h, false);
+    SG_HIP(hipGetLastError());
+  }
   drop_pc_graph(h);  // a captured action holds the old options
   return SG_OK;
 }

@@ -340,6 +340,91 @@ hipError_t launch_pcg_ragged(const PcgArgs<T>& args, const PcgCols<T>& cols, int
 template <typename T>
 size_t pcg_scratch_bytes(int ncols, int ntiles);
 
+// ---- The inner PCG in the sine basis (k_sine.hip).
+// K_0 = theta0 K_Lap on a uniform grid and its Jacobi-Chebyshev preconditioner
+// are both diagonal in the discrete sine basis sin(pi j k / n_e) of each
+// direction. PCG run there on the transformed right-hand side takes the same
+// steps as on the grid (the orthonormal transform keeps every scalar product):
+// K_0 is the eigenvalue of a mode, the preconditioner a factor per mode, and an
+// iteration needs no neighbours. A spectral vector is an nx x nx array
+// [ky'][kx'] whose index k' lists the odd wave numbers 1, 3, .. (ho of them)
+// before the even ones 2, 4, .. (he): a sine of odd k is even about the middle
+// of the interval and one of even k odd, so a transform of length nx splits
+// into two products of half the length on the folded data.
+// Modes (ky, kx) and (kx, ky) have the same eigenvalue and therefore the same
+// residual polynomial, so the iteration runs on slots, one per pair: 16 x 16
+// tiles of the array with a <= b (row index a, column index b), 256 slots a tile.
+constexpr int kSineMaxNx = 1024;    // longest transform (rows of both parities in LDS)
+constexpr int kSineThreads = 512;   // threads per block of the iteration kernel
+constexpr int kSineSlots = 18;      // most slots per thread (their state stays in registers)
+// Factors per transform length: packs of the sine matrices in the order the
+// matrix instructions read them (pack[p][tile][step][lane], parity p, 16 x 4
+// entries per step), and per slot t = eigenvalue of M K_0 and 1 / (factor of M).
+template <typename T>
+struct SineTables {
+  int nx, ho, he, nt;  // nt: tiles of 16 per parity (of ho)
+  int ept, groups;     // slots per thread, blocks that share a column
+  const T* fwd[2];     // S_p[4 s + l / 16][16 c + l % 16]
+  const T* inv[2];     // S_p[16 c + l % 16][4 s + l / 16]
+  const int4* tiles;   // [2 ept groups]: first row and column, row and column end
+  const double* t;     // [512 ept groups]
+  const double* ipi;   // 0 in slots that hold no mode
+};
+// Sizes of those tables.
+struct SineSizes {
+  int nx, ho, he, nt, ept, groups;
+  long pack, slots, ntiles;  // entries of one pack, slots, tiles
+};
+inline SineSizes sine_sizes(int nx) {
+  SineSizes z{};
+  z.nx = nx;
+  z.ho = (nx + 1) / 2;
+  z.he = nx / 2;
+  z.nt = (z.ho + 15) / 16;
+  const int nte = (z.he + 15) / 16;
+  const long tiles = (long)z.nt * (z.nt + 1) / 2 + (long)nte * (nte + 1) / 2 + (long)z.nt * nte;
+  const long per = (tiles * 256 + kSineThreads - 1) / kSineThreads;
+  z.groups = (int)((per + kSineSlots - 1) / kSineSlots);
+  z.ept = (int)((per + z.groups - 1) / z.groups);
+  for (int k : {2, 5, 8, 11, 14, kSineSlots})  // the counts of the compiled kernels (empty slots hold no mode)
+    if (z.ept <= k) {
+      z.ept = k;
+      break;
+    }
+  z.slots = (long)z.ept * z.groups * kSineThreads;
+  z.ntiles = z.slots / 256;
+  z.pack = 256L * z.nt * z.nt;
+  return z;
+}
+// The problem's constants behind the slot tables.
+struct SineConsts {
+  int n_e;
+  int degree;
+  double diag;       // theta0 * 8 / 3
+  double inv_theta;
+  double chebA[kMaxCheb], chebB[kMaxCheb];
+};
+template <typename T>
+struct SineArgs {
+  SineTables<T> tab;
+  long n;
+  int ncols;
+  const T* b;
+  T* x;
+  T* s;       // spectral right-hand side, then solution
+  T* s0;      // spectral initial guess (warm)
+  T* w;       // half-transformed vectors
+  int maxit;
+  double rtol;
+  int warm;
+  PcgScratch sc;
+};
+template <typename T>
+void launch_sine_tables(const SineSizes& z, const SineConsts& k, T* pack, int4* tiles, double* t, double* ipi,
+                        bool packs, hipStream_t s);
+template <typename T>
+hipError_t launch_sine(const SineArgs<T>& args, int num_cu, hipStream_t s);
+
 // FP64 BLAS-1 style kernels with deterministic two-stage reductions.
 void launch_dots(const double* const* a, const double* const* b, int ndots, long N, double* partials,
                  double* out, hipStream_t s);
@@ -482,6 +567,11 @@ struct sg_ctx {
   void* rw;  // inner-precision working residual, n x P
   void* zw;  // inner-precision output, n x P (FP32 only)
   void *pR0, *pR1, *pP0, *pP1, *pQ, *pZ;  // inner PCG state, n x maxcols
+  bool sine_ok = false;   // tables of the sine-basis solver built (k_sine.hip)
+  sgk::SineSizes sine{};
+  void* sine_pack = nullptr;  // inner precision
+  int4* sine_tiles = nullptr;
+  double *sine_t = nullptr, *sine_ipi = nullptr;
   int pcg_maxcols;
   sgk::PcgScratch pcgsc;
   double* red_part;  // reduction partials
