@@ -346,9 +346,10 @@ int sg_batch_solve(sg_batch b, const double* const* F, double* const* U, double 
 /* Schedule autotuner of a batch (the batch counterpart of sg_autotune):
  *   flags bit 0: every member's SG operator, as sg_autotune's bit 0 on the
  *                member's own sizes;
- *   flags bit 1: the ragged inner launches: banded tiles with the default or
- *                64-row bands, and 16 x 16 tiles when opts.tile is 0, each
- *                with all or half of the compute units, timed on one inner
+ *   flags bit 1: the ragged inner launches: the sine basis when opts.tile is
+ *                0 and every member's grid has it, banded tiles with the
+ *                default or 64-row bands, and 16 x 16 tiles when opts.tile is
+ *                0, tiles with all or half of the compute units, timed on one inner
  *                solve of every column set a preconditioner action uses, with
  *                a constant right-hand side in every problem.
  * Overwrites the members' vectors, drops a captured graph and synchronises

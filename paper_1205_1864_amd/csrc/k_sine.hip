@@ -143,6 +143,34 @@ __global__ void sine_slot_kernel(SineSizes z, SineConsts c, const int4* tiles, d
 
 constexpr int kPassThreads = 512;
 
+// What the first pass of a solve clears for the iteration that follows on the
+// stream: the exchange places and tickets of its groups, and the status word.
+struct SineReset {
+  unsigned long long* ex;
+  int nex;
+  unsigned* tickets;
+  int ntickets;
+  int* status;  // null: nothing to clear
+};
+
+// Columns of several problems: the arrays of a ragged launch (listed columns
+// only) and the tables of every problem.
+enum { COL_B = 0, COL_X = 1, COL_S = 2, COL_S0 = 3, COL_W = 4 };
+template <typename T>
+struct SineRagged {
+  PcgCols<T> cols;
+  const SineTables<T>* tabs;
+  __device__ T* column(int which, int o) const {
+    switch (which) {
+      case COL_B: return const_cast<T*>(ld_uniform(cols.b, o));
+      case COL_X: return ld_uniform(cols.x, o);
+      case COL_S: return ld_uniform(cols.r0, o);
+      case COL_S0: return ld_uniform(cols.r1, o);
+      default: return ld_uniform(cols.z, o);
+    }
+  }
+};
+
 // Bound by the matrix cores and the loads that feed them: 220 columns of 255^2
 // take 120 to 130 us a pass in FP64 (29 TFLOP/s of folded products, 1.8 TB/s), 60
 // to 80 us in FP32. Two blocks fit a compute unit up to 128 modes per parity, so
@@ -153,25 +181,37 @@ constexpr int kPassThreads = 512;
 // the right; inverse: it multiplies the two halves of a spectral row and
 // unfolds the results. A wave takes one 16-column tile of both parities, so
 // that the unfolding stays within a lane.
-template <typename T, bool INV, int RT>
+// RAGGED: the launch covers columns of several problems, `strips` blocks each
+// (as many as the largest grid needs; the blocks past a column's rows end).
+template <typename T, bool INV, int RT, bool RAGGED>
 __global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab, const T* in, T* out, long rows,
-                                                              unsigned long long* ex, unsigned* ticket, int* status,
-                                                              int nex) {
+                                                              SineReset reset, SineRagged<T> C, int from, int to,
+                                                              int strips) {
   using M = Mac<T>;
   using V = typename M::V;
   extern __shared__ unsigned char smem[];
+  if (!INV && blockIdx.x == 0 && reset.status) {
+    for (int i = threadIdx.x; i < reset.nex; i += blockDim.x) reset.ex[i] = kEmpty;
+    for (int i = threadIdx.x; i < reset.ntickets; i += blockDim.x) reset.tickets[i] = 0u;
+    if (threadIdx.x == 0) *reset.status = 0;
+  }
+  long strip = blockIdx.x;
+  if constexpr (RAGGED) {
+    const int i = blockIdx.x / strips;
+    if (i >= ld_uniform(C.cols.nact, 0)) return;
+    const int o = ld_uniform(C.cols.act, i);
+    strip = blockIdx.x - i * strips;
+    tab = C.tabs[ld_uniform(C.cols.prob, o)];
+    if (strip * 16 * RT >= tab.nx) return;
+    rows = tab.nx;
+    in = C.column(from, o);
+    out = C.column(to, o);
+  }
   const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt, ld = hp + 4;
   constexpr int R = 16 * RT;
   T* Q = reinterpret_cast<T*>(smem);  // [2][R][ld]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  if (!INV && nex >= 0 && blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < nex; i += blockDim.x) ex[i] = kEmpty;
-    if (threadIdx.x == 0) {
-      *status = 0;
-      *ticket = 0u;
-    }
-  }
-  const long r0 = (long)blockIdx.x * R;
+  const long r0 = strip * R;
   for (int r = wave; r < R; r += nw) {
     const bool on = r0 + r < rows;
     const T* src = in + (r0 + r) * nx;
@@ -244,20 +284,28 @@ __global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab,
 // in LDS and multiplies by the sine matrices from the left. With 32 columns
 // the two halves of every other row are exchanged, so that the four rows of a
 // matrix operand fall into different LDS banks.
-template <typename T, bool INV, int CT>
+template <typename T, bool INV, int CT, bool RAGGED>
 __global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab, const T* in, T* out, long n,
-                                                              int strips) {
+                                                              SineRagged<T> C, int from, int to, int strips) {
   using M = Mac<T>;
   using V = typename M::V;
   extern __shared__ unsigned char smem[];
+  const int col = blockIdx.x / strips;
+  const T* src = in + (long)col * n;
+  T* dst = out + (long)col * n;
+  if constexpr (RAGGED) {
+    if (col >= ld_uniform(C.cols.nact, 0)) return;
+    const int o = ld_uniform(C.cols.act, col);
+    tab = C.tabs[ld_uniform(C.cols.prob, o)];
+    if ((blockIdx.x - col * strips) * 16 * CT >= tab.nx) return;
+    src = C.column(from, o);
+    dst = C.column(to, o);
+  }
   const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt;
   constexpr int CW = 16 * CT;
   T* Q = reinterpret_cast<T*>(smem);  // [2][hp][CW]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int col = blockIdx.x / strips;
   const int c0 = (blockIdx.x - col * strips) * CW;
-  const T* src = in + (long)col * n;
-  T* dst = out + (long)col * n;
   auto place = [&](int j, int c) { return j * CW + (CT == 2 ? c ^ ((j & 1) << 4) : c); };
   {
     const int c = threadIdx.x % CW;
@@ -464,8 +512,10 @@ struct ColumnSums {
 // four turns, 10.6 us per iteration of all). With one block a column, whose 68
 // slots a thread stream v, t and 1 / pi, an iteration took 15.8 us for one column
 // (cache bandwidth of one compute unit) and 23.4 us for 220.
-template <typename T, int NR>
-__global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A, int ngroups) {
+// RAGGED: the listed columns of several problems; those whose tables have other
+// slot and block counts than this launch are left to the launches for theirs.
+template <typename T, int NR, bool RAGGED>
+__global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A, SineRagged<T> C, int ngroups) {
   constexpr bool TREG = NR <= 11;
   extern __shared__ unsigned char smem[];
   __shared__ double red[2][kSineThreads / 64][kSumWidth], all[2][kSumWidth];
@@ -483,10 +533,10 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
     __syncthreads();
   }
   const int group = place_ / G, g = place_ - group * G;
-  const int nx = A.tab.nx;
   const long sbase = (long)g * NR * kSineThreads;  // this block's first slot
-  const int4* tiles = A.tab.tiles + sbase / 256;
   const int lane = tid & 63, w0 = __builtin_amdgcn_readfirstlane(tid >> 6) * NR;
+  int nx = A.tab.nx;
+  const int4* tiles = A.tab.tiles + sbase / 256;
   const double* tt = A.tab.t + sbase + w0 * 64 + lane;  // element e at 64 e
   const double* ip = A.tab.ipi + sbase + w0 * 64 + lane;
   // row and column of element e (its 64 slots are a quarter of a tile)
@@ -494,9 +544,21 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
   double* lds = reinterpret_cast<double*>(smem) + tid;
   ColumnSums cs{red, all, reinterpret_cast<unsigned long long*>(A.sc.part) + (long)group * G * 3 * kSumWidth,
                 A.sc.status, &sflag, G, g, 0u, false};
-  for (int c = group; c < A.ncols; c += ngroups) {
+  const int ncols = RAGGED ? ld_uniform(C.cols.nact, 0) : A.ncols;
+  for (int c = group; c < ncols; c += ngroups) {
     T* s = A.s + (long)c * A.n;
     const T* s0 = A.s0 + (long)c * A.n;
+    if constexpr (RAGGED) {
+      const int o = ld_uniform(C.cols.act, c);
+      const SineTables<T>& tab = C.tabs[ld_uniform(C.cols.prob, o)];
+      if (tab.ept != NR || tab.groups != G) continue;
+      nx = tab.nx;
+      tiles = tab.tiles + sbase / 256;
+      tt = tab.t + sbase + w0 * 64 + lane;
+      ip = tab.ipi + sbase + w0 * 64 + lane;
+      s = C.column(COL_S, o);
+      s0 = C.column(COL_S0, o);
+    }
     // ---- start: weights, b.b, r.r, r.z, z.K z (warm: r = b - K_0 x in place)
     double sums[kSumWidth] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
@@ -596,60 +658,94 @@ hipError_t allow_lds(K kfn, size_t bytes) {
                              (int)bytes);
 }
 
-template <typename T, bool INV>
-hipError_t x_pass(const SineArgs<T>& A, const T* in, T* out, int reset_groups, hipStream_t s) {
-  const int hp = 16 * A.tab.nt;
-  const long rows = (long)A.ncols * A.tab.nx;
-  const int threads = 64 * std::min(8, A.tab.nt);
-  // the first block clears the exchange and the ticket of the iteration that follows on the stream
-  unsigned long long* ex = reinterpret_cast<unsigned long long*>(A.sc.part);
-  const int nex = reset_groups == 0 ? -1 : A.tab.groups == 1 ? 0 : reset_groups * A.tab.groups * 3 * kSumWidth;
-  if (hp <= 256) {
-    const size_t sm = sizeof(T) * 2 * 32 * (hp + 4);
-    hipError_t e = allow_lds(sine_x_kernel<T, INV, 2>, sm);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sine_x_kernel<T, INV, 2>), dim3((unsigned)((rows + 31) / 32)), dim3(threads), sm, s, A.tab, in,
-                       out, rows, ex, A.sc.arrivals, A.sc.status, nex);
-  } else {
-    const size_t sm = sizeof(T) * 2 * 16 * (hp + 4);
-    hipError_t e = allow_lds(sine_x_kernel<T, INV, 1>, sm);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sine_x_kernel<T, INV, 1>), dim3((unsigned)((rows + 15) / 16)), dim3(threads), sm, s, A.tab, in,
-                       out, rows, ex, A.sc.arrivals, A.sc.status, nex);
-  }
-  return hipGetLastError();
+template <typename T>
+const T* column_base(const SineArgs<T>& A, int which) {
+  return which == COL_B ? A.b : which == COL_X ? A.x : which == COL_S ? A.s : which == COL_S0 ? A.s0 : A.w;
 }
 
-template <typename T, bool INV>
-hipError_t y_pass(const SineArgs<T>& A, const T* in, T* out, hipStream_t s) {
-  const int hp = 16 * A.tab.nt, nx = A.tab.nx;
-  const int threads = 64 * std::min(8, A.tab.nt);
-  if (hp <= 256) {
-    const size_t sm = sizeof(T) * 2 * hp * 32;
-    hipError_t e = allow_lds(sine_y_kernel<T, INV, 2>, sm);
+// One pass over every column: `nx` the longest transform, C the columns of a ragged launch.
+template <typename T, bool INV, bool RAGGED>
+hipError_t x_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, const SineReset& reset,
+                  hipStream_t s) {
+  const int nt = ((nx + 1) / 2 + 15) / 16, hp = 16 * nt;
+  const long rows = (long)A.ncols * nx;
+  const int threads = 64 * std::min(8, nt);
+  const T* in = RAGGED ? nullptr : column_base(A, from);
+  T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
+  auto launch = [&](auto kfn, int R) {
+    const size_t sm = sizeof(T) * 2 * R * (hp + 4);
+    const hipError_t e = allow_lds(kfn, sm);
     if (e != hipSuccess) return e;
-    const int strips = (nx + 31) / 32;
-    hipLaunchKernelGGL((sine_y_kernel<T, INV, 2>), dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out,
-                       A.n, strips);
-  } else {
-    const size_t sm = sizeof(T) * 2 * hp * 16;
-    hipError_t e = allow_lds(sine_y_kernel<T, INV, 1>, sm);
-    if (e != hipSuccess) return e;
-    const int strips = (nx + 15) / 16;
-    hipLaunchKernelGGL((sine_y_kernel<T, INV, 1>), dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out,
-                       A.n, strips);
-  }
-  return hipGetLastError();
+    const int strips = (nx + R - 1) / R;
+    const long blocks = RAGGED ? (long)A.ncols * strips : (rows + R - 1) / R;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)blocks), dim3(threads), sm, s, A.tab, in, out, rows, reset, C, from, to,
+                       strips);
+    return hipGetLastError();
+  };
+  return hp <= 256 ? launch(sine_x_kernel<T, INV, 2, RAGGED>, 32) : launch(sine_x_kernel<T, INV, 1, RAGGED>, 16);
 }
 
-template <typename T, int NR>
-hipError_t pcg(const SineArgs<T>& A, int ngroups, hipStream_t s) {
-  auto kfn = sine_pcg_kernel<T, NR>;
-  const size_t sm = sizeof(double) * kSineThreads * (NR <= 11 ? NR : 2 * NR);
-  hipError_t e = allow_lds(kfn, sm);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kfn, dim3((unsigned)(ngroups * A.tab.groups)), dim3(kSineThreads), sm, s, A, ngroups);
-  return hipGetLastError();
+template <typename T, bool INV, bool RAGGED>
+hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, hipStream_t s) {
+  const int nt = ((nx + 1) / 2 + 15) / 16, hp = 16 * nt;
+  const int threads = 64 * std::min(8, nt);
+  const T* in = RAGGED ? nullptr : column_base(A, from);
+  T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
+  auto launch = [&](auto kfn, int W) {
+    const size_t sm = sizeof(T) * 2 * hp * W;
+    const hipError_t e = allow_lds(kfn, sm);
+    if (e != hipSuccess) return e;
+    const int strips = (nx + W - 1) / W;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out, A.n, C, from, to,
+                       strips);
+    return hipGetLastError();
+  };
+  return hp <= 256 ? launch(sine_y_kernel<T, INV, 2, RAGGED>, 32) : launch(sine_y_kernel<T, INV, 1, RAGGED>, 16);
+}
+
+template <typename T, bool RAGGED>
+hipError_t pcg(const SineArgs<T>& A, const SineRagged<T>& C, int ngroups, hipStream_t s) {
+  auto launch = [&](auto kfn, int nr) {
+    const size_t sm = sizeof(double) * kSineThreads * (nr <= 11 ? nr : 2 * nr);
+    const hipError_t e = allow_lds(kfn, sm);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kfn, dim3((unsigned)(ngroups * A.tab.groups)), dim3(kSineThreads), sm, s, A, C, ngroups);
+    return hipGetLastError();
+  };
+  switch (A.tab.ept) {
+    case 2: return launch(sine_pcg_kernel<T, 2, RAGGED>, 2);
+    case 5: return launch(sine_pcg_kernel<T, 5, RAGGED>, 5);
+    case 8: return launch(sine_pcg_kernel<T, 8, RAGGED>, 8);
+    case 11: return launch(sine_pcg_kernel<T, 11, RAGGED>, 11);
+    case 14: return launch(sine_pcg_kernel<T, 14, RAGGED>, 14);
+    case 18: return launch(sine_pcg_kernel<T, 18, RAGGED>, 18);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Groups of a launch: one block per compute unit; a group takes its columns in
+// turn. A column of one block is a group of its own.
+int group_count(int ncols, int groups, int num_cu) {
+  return groups == 1 ? ncols : std::min(ncols, num_cu / groups);
+}
+
+template <typename T, bool RAGGED>
+hipError_t transform_in(const SineArgs<T>& A, const SineRagged<T>& C, int nx, const SineReset& reset, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (A.warm) {
+    e = x_pass<T, false, RAGGED>(A, C, nx, COL_X, COL_W, SineReset{}, s);
+    if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S0, s);
+  }
+  if (e == hipSuccess) e = x_pass<T, false, RAGGED>(A, C, nx, COL_B, COL_W, reset, s);
+  if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S, s);
+  return e;
+}
+
+template <typename T, bool RAGGED>
+hipError_t transform_out(const SineArgs<T>& A, const SineRagged<T>& C, int nx, hipStream_t s) {
+  hipError_t e = y_pass<T, true, RAGGED>(A, C, nx, COL_S, COL_W, s);
+  if (e == hipSuccess) e = x_pass<T, true, RAGGED>(A, C, nx, COL_W, COL_X, SineReset{}, s);
+  return e;
 }
 
 }  // namespace
@@ -670,35 +766,51 @@ hipError_t launch_sine(const SineArgs<T>& A, int num_cu, hipStream_t s) {
   if (A.ncols <= 0) return hipSuccess;
   const SineTables<T>& t = A.tab;
   const SineSizes z = sine_sizes(t.nx);
+  const int ngroups = group_count(A.ncols, t.groups, num_cu);
   if (t.nx < 1 || t.nx > kSineMaxNx || A.n != (long)t.nx * t.nx || t.ept != z.ept || t.groups != z.groups ||
-      t.nt != z.nt)
+      t.nt != z.nt || ngroups < 1)
     return hipErrorInvalidValue;
-  // one block per compute unit; a group then takes its columns in turn
-  const int ngroups = t.groups == 1 ? A.ncols : std::min(A.ncols, num_cu / t.groups);
-  if (ngroups < 1) return hipErrorInvalidValue;
-  hipError_t e = hipSuccess;
-  if (A.warm) {
-    e = x_pass<T, false>(A, A.x, A.w, 0, s);
-    if (e == hipSuccess) e = y_pass<T, false>(A, A.w, A.s0, s);
-    if (e != hipSuccess) return e;
-  }
-  e = x_pass<T, false>(A, A.b, A.w, ngroups, s);
-  if (e == hipSuccess) e = y_pass<T, false>(A, A.w, A.s, s);
-  if (e != hipSuccess) return e;
-  switch (t.ept) {
-    case 2: e = pcg<T, 2>(A, ngroups, s); break;
-    case 5: e = pcg<T, 5>(A, ngroups, s); break;
-    case 8: e = pcg<T, 8>(A, ngroups, s); break;
-    case 11: e = pcg<T, 11>(A, ngroups, s); break;
-    case 14: e = pcg<T, 14>(A, ngroups, s); break;
-    case 18: e = pcg<T, 18>(A, ngroups, s); break;
-    default: e = hipErrorInvalidValue;
-  }
-  if (e == hipSuccess) e = y_pass<T, true>(A, A.s, A.w, s);
-  if (e == hipSuccess) e = x_pass<T, true>(A, A.w, A.x, 0, s);
+  const SineReset reset{reinterpret_cast<unsigned long long*>(A.sc.part),
+                        t.groups == 1 ? 0 : ngroups * t.groups * 3 * kSumWidth, A.sc.arrivals, t.groups == 1 ? 0 : 1,
+                        A.sc.status};
+  const SineRagged<T> none{};
+  hipError_t e = transform_in<T, false>(A, none, t.nx, reset, s);
+  if (e == hipSuccess) e = pcg<T, false>(A, none, ngroups, s);
+  if (e == hipSuccess) e = transform_out<T, false>(A, none, t.nx, s);
   return e;
 }
 
+// A class of a ragged launch takes a share of the exchange and a ticket of its own.
+size_t sine_exchange_bytes(int nclasses) { return sizeof(double) * (size_t)nclasses * kSineMaxBlocks * 3 * kSumWidth; }
+
+template <typename T>
+hipError_t launch_sine_ragged(const SineArgs<T>& args, const PcgCols<T>& cols, const SineTables<T>* tabs, int max_nx,
+                              const SineClass* classes, int nclasses, int num_cu, hipStream_t s) {
+  if (args.ncols <= 0) return hipSuccess;
+  if (!cols.act || max_nx < 1 || max_nx > kSineMaxNx || num_cu > kSineMaxBlocks) return hipErrorInvalidValue;
+  const SineRagged<T> C{cols, tabs};
+  constexpr int share = kSineMaxBlocks * 3 * kSumWidth;
+  const SineReset reset{reinterpret_cast<unsigned long long*>(args.sc.part), nclasses * share, args.sc.arrivals,
+                        nclasses, args.sc.status};
+  hipError_t e = transform_in<T, true>(args, C, max_nx, reset, s);
+  for (int k = 0; k < nclasses && e == hipSuccess; ++k) {
+    SineArgs<T> a = args;
+    a.tab.ept = classes[k].ept;
+    a.tab.groups = classes[k].groups;
+    a.sc.part = args.sc.part + (long)k * share;
+    a.sc.arrivals = args.sc.arrivals + k;
+    const int ngroups = group_count(args.ncols, classes[k].groups, num_cu);
+    if (ngroups < 1) return hipErrorInvalidValue;
+    e = pcg<T, true>(a, C, ngroups, s);
+  }
+  if (e == hipSuccess) e = transform_out<T, true>(args, C, max_nx, s);
+  return e;
+}
+
+template hipError_t launch_sine_ragged<double>(const SineArgs<double>&, const PcgCols<double>&,
+                                               const SineTables<double>*, int, const SineClass*, int, int, hipStream_t);
+template hipError_t launch_sine_ragged<float>(const SineArgs<float>&, const PcgCols<float>&, const SineTables<float>*,
+                                              int, const SineClass*, int, int, hipStream_t);
 template void launch_sine_tables<double>(const SineSizes&, const SineConsts&, double*, int4*, double*, double*, bool,
                                          hipStream_t);
 template void launch_sine_tables<float>(const SineSizes&, const SineConsts&, float*, int4*, double*, double*, bool,

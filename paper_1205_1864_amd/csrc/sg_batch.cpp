@@ -48,6 +48,11 @@ struct sg_batch_ctx {
   std::vector<size_t> set_off;      // byte offset of each set in the set region
   char* sets_base = nullptr;
   const void* sets_consts = nullptr;  // per-problem inner constants (device)
+  // inner solves in the sine basis (sine: in use; every member must have it)
+  bool sine_ok = false, sine = false;
+  const void* sine_tabs = nullptr;  // SineTables of every problem (device)
+  std::vector<sgk::SineClass> sine_classes;
+  int sine_max_nx = 0;
   sgk::PcgScratch sc{};
   int* sticky = nullptr;  // set if a bounded wait of an inner launch expired
   int* pdeg = nullptr;    // chaos degree of each problem (device)
@@ -109,7 +114,7 @@ std::vector<std::pair<int, int>> batch_tilings(const sg_opts& op) {
 // shared region. Returns false if a problem is rejected.
 struct BatchPlan {
   std::vector<size_t> ws_off, ws_size;
-  size_t o_N, o_tab, o_sc, o_active, o_pdeg, o_part, o_consts, o_sets, o_pcg_part, o_arr, o_iters, o_status, o_sticky;
+  size_t o_N, o_tab, o_sc, o_active, o_pdeg, o_part, o_consts, o_sine_tabs, o_sets, o_pcg_part, o_arr, o_iters, o_status, o_sticky;
   std::vector<int> set_ncols;
   std::vector<long> set_nwork;
   size_t set_bytes = 0;
@@ -121,6 +126,21 @@ size_t set_stride(long ncols) {
   // per column: nx, ntx, ntiles, prob, list entry (int), tbase, list base (long) and eight
   // pointers; plus the two list totals and the alignment of the 17 arrays
   return (size_t)ncols * (5 * sizeof(int) + 2 * sizeof(long) + 8 * sizeof(void*)) + 20 * 256;
+}
+
+// Classes of the members' inner iterations in the sine basis (distinct slot and block counts).
+std::vector<sgk::SineClass> sine_classes(int count, const sg_problem* probs) {
+  std::vector<sgk::SineClass> k;
+  for (int b = 0; b < count; ++b) {
+    const int nx = probs[b].n_e - 1;
+    if (nx > sgk::kSineMaxNx) continue;
+    const sgk::SineSizes z = sgk::sine_sizes(nx);
+    const bool seen = std::any_of(k.begin(), k.end(), [&](const sgk::SineClass& c) {
+      return c.ept == z.ept && c.groups == z.groups;
+    });
+    if (!seen) k.push_back({z.ept, z.groups});
+  }
+  return k;
 }
 
 int make_batch_plan(int count, const sg_problem* probs, const sg_opts* op, BatchPlan& bp) {
@@ -169,9 +189,12 @@ int make_batch_plan(int count, const sg_problem* probs, const sg_opts* op, Batch
   bp.o_pdeg = L.take(sizeof(int) * count);
   bp.o_part = L.take(sizeof(double) * 2 * sgk::kBatchBlocks * count);
   bp.o_consts = L.take(sizeof(sgk::PcgConsts<double>) * count);
+  bp.o_sine_tabs = L.take(sizeof(sgk::SineTables<double>) * count);
   bp.o_sets = L.take(bp.set_bytes);
-  bp.o_pcg_part = L.take(sizeof(double) * sgk::kPcgPartials * std::max<long>(1, bp.nwork_max));
-  bp.o_arr = L.take(sizeof(unsigned) * std::max<long>(1, bp.ncols_max));
+  const size_t nclasses = sine_classes(count, probs).size();
+  bp.o_pcg_part = L.take(std::max(sizeof(double) * sgk::kPcgPartials * (size_t)std::max<long>(1, bp.nwork_max),
+                                  sgk::sine_exchange_bytes((int)nclasses)));
+  bp.o_arr = L.take(sizeof(unsigned) * std::max<size_t>(nclasses, std::max<long>(1, bp.ncols_max)));
   bp.o_iters = L.take(sizeof(int) * std::max<long>(1, bp.ncols_max));
   bp.o_status = L.take(sizeof(int));
   bp.o_sticky = L.take(sizeof(int));
@@ -317,7 +340,19 @@ int run_set(sg_batch_ctx* B, int s, int pmin = 0, bool warm = false) {
   sgk::launch_batch_compact(cols.prob, cols.ntiles, ncols, B->V.active, B->pdeg, pmin, const_cast<int*>(cols.act),
                             const_cast<int*>(cols.nact), const_cast<long*>(cols.cbase),
                             const_cast<long*>(cols.nwork_act), B->stream);
-  SG_HIP(sgk::launch_pcg_ragged<T>(a, cols, B->tile, B->max_blocks, B->stream));
+  if (B->sine) {
+    sgk::SineArgs<T> sa{};
+    sa.ncols = ncols;
+    sa.maxit = a.maxit;
+    sa.rtol = a.rtol;
+    sa.warm = warm && B->opts.warm_start;
+    sa.sc = B->sc;
+    SG_HIP(sgk::launch_sine_ragged<T>(sa, cols, (const sgk::SineTables<T>*)B->sine_tabs, B->sine_max_nx,
+                                      B->sine_classes.data(), (int)B->sine_classes.size(), B->h[0]->num_cu,
+                                      B->stream));
+  } else {
+    SG_HIP(sgk::launch_pcg_ragged<T>(a, cols, B->tile, B->max_blocks, B->stream));
+  }
   sgk::launch_batch_count_iters(B->sc.iters, cols.act, cols.nact, cols.prob, ncols, B->V.sc, B->sc.status,
                                 B->sticky, B->stream);
   return SG_OK;
@@ -524,6 +559,22 @@ int sg_batch_setup(int32_t count, const sg_problem* probs, const sg_opts* opts, 
       std::memcpy(consts.data() + sizeof(k) * b, &k, sizeof(k));
     }
   }
+  // sine-basis tables per problem, where every member has them
+  B->sine_classes = sine_classes(count, probs);
+  B->sine_tabs = w + bp.o_sine_tabs;
+  B->sine_ok = std::all_of(B->h.begin(), B->h.end(), [](const sg_ctx* h) { return sgh::use_sine(h); }) &&
+               B->h[0]->num_cu <= sgk::kSineMaxBlocks;
+  B->sine = B->sine_ok;
+  std::vector<char> tabs(sizeof(sgk::SineTables<double>) * count);
+  for (int b = 0; b < count; ++b) {
+    sg_ctx* h = B->h[b];
+    B->sine_max_nx = std::max(B->sine_max_nx, h->nx);
+    if (!B->sine_ok) continue;
+    static_assert(sizeof(sgk::SineTables<float>) == sizeof(sgk::SineTables<double>), "tables of either precision");
+    const sgk::SineTables<double> t64 = sgh::sine_tables<double>(h);
+    const sgk::SineTables<float> t32 = sgh::sine_tables<float>(h);
+    std::memcpy(tabs.data() + sizeof(t64) * b, B->inner == 32 ? (const void*)&t32 : (const void*)&t64, sizeof(t64));
+  }
   // ragged column sets (built and uploaded after the shared tables)
   B->sets_base = w + bp.o_sets;
   B->sets_consts = w + bp.o_consts;
@@ -546,6 +597,8 @@ int sg_batch_setup(int32_t count, const sg_problem* probs, const sg_opts* opts, 
   hipError_t e = hipMemcpyAsync(w + bp.o_N, N.data(), sizeof(long) * count, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(tab_d, tab.data(), sizeof(void*) * tab.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(w + bp.o_consts, consts.data(), consts.size(), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(w + bp.o_sine_tabs, tabs.data(), tabs.size(), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(B->pdeg, pdeg.data(), sizeof(int) * count, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
@@ -683,12 +736,20 @@ int sg_batch_autotune(sg_batch B, int32_t flags, sg_tune_report* report) {
       return SG_OK;
     };
     int bt = B->tile, br = B->rows, bb = B->max_blocks;
+    bool bs = false;
     double best = 1e300;
     const int ncu = B->h[0]->num_cu;
-    for (const auto& tr : batch_tilings(B->opts))
+    // the sine basis first (it takes no tiling and no block cap), then the tilings
+    std::vector<std::pair<int, int>> cands = batch_tilings(B->opts);
+    if (B->sine_ok) cands.insert(cands.begin(), {0, 0});
+    for (const auto& tr : cands)
       for (int mb : {0, std::max(1, ncu / 2)}) {
-        B->tile = tr.first;
-        B->rows = tr.first == 16 ? B->rows : tr.second;
+        B->sine = tr.first == 0;
+        if (B->sine && mb != 0) continue;
+        if (!B->sine) {
+          B->tile = tr.first;
+          B->rows = tr.first == 16 ? B->rows : tr.second;
+        }
         B->max_blocks = mb;
         int rc = upload_sets(B);
         if (rc) return rc;
@@ -707,11 +768,13 @@ int sg_batch_autotune(sg_batch B, int32_t flags, sg_tune_report* report) {
         ++R.candidates;
         if (t[1] < best) {
           best = t[1];
+          bs = B->sine;
           bt = B->tile;
           br = B->rows;
           bb = mb;
         }
       }
+    B->sine = bs;
     B->tile = bt;
     B->rows = br;
     B->max_blocks = bb;

@@ -425,6 +425,20 @@ void launch_sine_tables(const SineSizes& z, const SineConsts& k, T* pack, int4* 
 template <typename T>
 hipError_t launch_sine(const SineArgs<T>& args, int num_cu, hipStream_t s);
 
+// Ragged launch over the listed columns of several problems (cols.act; state in
+// cols.r0, r1 and z), tables per problem in device memory. The iteration runs
+// once per class of columns with equal slot and block counts, each with a share
+// of the exchange (sine_exchange_bytes in args.sc.part) and a ticket
+// (args.sc.arrivals).
+constexpr int kSineMaxBlocks = 512;  // compute units a class's exchange serves
+struct SineClass {
+  int ept, groups;
+};
+size_t sine_exchange_bytes(int nclasses);
+template <typename T>
+hipError_t launch_sine_ragged(const SineArgs<T>& args, const PcgCols<T>& cols, const SineTables<T>* tabs, int max_nx,
+                              const SineClass* classes, int nclasses, int num_cu, hipStream_t s);
+
 // FP64 BLAS-1 style kernels with deterministic two-stage reductions.
 void launch_dots(const double* const* a, const double* const* b, int ndots, long N, double* partials,
                  double* out, hipStream_t s);

@@ -98,3 +98,25 @@ def test_more_columns_than_a_grid_dimension():
     K0 = sg.build_system(make_problem("k0", 3, 0, 0, 0.0, 0.5)).K[0].toarray()
     assert np.max(np.abs(X.cpu().numpy() @ K0 - B)) <= 1e-11 * np.max(np.abs(B))
     assert np.all(it > 0)
+
+
+@pytest.mark.parametrize("prec,pc,warm", [(64, "hsc", True), (32, "bgs", False)])
+def test_batch_classes_match_single_solves(prec, pc, warm):
+    """A batch whose members differ in slots per thread and blocks per column (one,
+    two and six): each member as its own solve, to the batch tests' tolerances."""
+    from paper_1205_1864_amd import binding as b
+    probs = [make_problem(f"c{i}", n_e, M, p, 0.2, 0.5)
+             for i, (n_e, M, p) in enumerate([(20, 3, 2), (70, 2, 2), (130, 2, 1), (300, 2, 2), (101, 1, 2)])]
+    opts = b.Options(inner_precision=prec, precond=pc, cheb_degree=8, inner_rtol=1e-4, warm_start=warm)
+    F = [b.to_device_block(pr.load_block()) for pr in probs]
+    print(f"sine batch classes FP{prec} {pc} warm={warm}", flush=True)
+    batch = b.SGBatch(probs, opts)
+    U, stats, info = batch.sg_batch_solve(F, rtol=1e-8, maxit=100)
+    assert info["rc"] == 0
+    for i, pr in enumerate(probs):
+        single = b.SGSolver(pr, opts)
+        Us, ss = single.sg_solve(F[i], rtol=1e-8, maxit=100)
+        single.close()
+        assert abs(stats[i]["outer_it"] - ss["outer_it"]) <= (0 if prec == 64 else 1)
+        assert float((U[i] - Us).norm() / Us.norm()) <= (1e-11 if prec == 64 else 1e-7)
+    batch.close()
