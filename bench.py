@@ -44,9 +44,8 @@ CHEB_DEGREE = 16  # updates of the Chebyshev preconditioner of the inner PCG (fa
 # pcg_kernel<double, BandTile<double, 128 | 64, 15, 16>, 1>, average over a solve's launches, by the
 # inner schedule's block cap (-1: whole columns per block where they fill the device; 0: automatic grid)
 PCG_TRAFFIC_BYTES = {-1: 14.30e9}
-# one SG matvec, by schedule (mv_variant, mv_param): the row-staged kernel with 10-row pieces,
-# and the y-marching kernel it replaced
-MATVEC_TRAFFIC_BYTES = {(4, 10): 354.2e6, (2, 2): 570.4e6, (2, 1): 543.0e6}
+# one SG matvec, by schedule (mv_variant, mv_param): the row-staged kernel with 10-row pieces
+MATVEC_TRAFFIC_BYTES = {(4, 10): 354.2e6}
 
 
 def log(msg):
@@ -479,9 +478,8 @@ def main():
     # the counter traffic belongs to the schedules it was measured with
     pcg_traffic = PCG_TRAFFIC_BYTES.get(schedule["pcg_max_blocks"]) if schedule["pcg_tile"] == 32 else None
     mv_traffic = MATVEC_TRAFFIC_BYTES.get((schedule["mv_variant"], schedule["mv_param"]))
-    mv_kernel = {4: "sgop_stage_kernel", 3: "sgop_piece_kernel<double>", 2: "sgop_march_kernel<double>",
-                 1: "sgop_strip_dyn_kernel<double>", 0: "sgop_strip_kernel<double>"}.get(
-                     schedule["mv_variant"], f"SG operator variant {schedule['mv_variant']}")
+    mv_kernel = {4: "sgop_stage_kernel", 3: "sgop_strip_kernel<double>"}.get(
+        schedule["mv_variant"], f"SG operator variant {schedule['mv_variant']}")
     roofline = {
         "kernel": "pcg_kernel (persistent batched inner PCG, all launches of the timed solves)",
         "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",

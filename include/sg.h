@@ -268,11 +268,9 @@ int sg_adjoint_grad(sg_handle h, const double* U, const double* w_mean, const do
 
 /* Schedule autotuner. Times candidate launch schedules on this handle's own
  * grid and chaos sizes and keeps the fastest for all later calls:
- *   flags bit 0: the SG operator (piece kernel with 8, 16 or 32 node rows
- *                per piece and all resident waves or 4 per CU, when M <= 12;
- *                y-marching kernel with 1, 2 or 4 grid segments per XCD or the
- *                automatic count; band kernels with 32..128 row chunks per
- *                band, where the grid shape allows them);
+ *   flags bit 0: the SG operator (strip kernel with 2, 4, 6 or 8 node rows per
+ *                wave, which the coupling products keep, and for the full
+ *                operator the row-staged kernel where it fits);
  *   flags bit 1: the inner PCG (with tile = 0 the sine basis where it serves
  *                the grid; tile kind 16 or 32 where the Chebyshev halo
  *                allows 32; block count automatic, half the CUs, or whole
@@ -284,11 +282,9 @@ int sg_adjoint_grad(sg_handle h, const double* U, const double* w_mean, const do
  * differ only in the order of floating-point sums. report (host, may be NULL)
  * receives the choice. */
 typedef struct sg_tune_report {
-  int32_t mv_variant;      /* 0, 1: band kernels; 2: y-marching kernel; 3: piece kernel;
-                              4: row-staged kernel (node rows of all chaos columns in LDS) */
-  int32_t mv_param;        /* row chunks per band (variants 0, 1); segments per XCD (2; 0 = automatic);
-                              100 * rows per piece + waves per CU (3; 0 waves = all resident);
-                              node rows per piece (4) */
+  int32_t mv_variant;      /* 3: strip kernel (one wave per 62 node columns by a few rows and chaos
+                              row); 4: row-staged kernel (node rows of all chaos columns in LDS) */
+  int32_t mv_param;        /* 100 * node rows per wave (3; 0 = automatic); node rows per piece (4) */
   int32_t pcg_tile;        /* inner tile kind (32 banded, or the sine basis where tile = 0 was the
                               fastest; 16 square) */
   int32_t pcg_max_blocks;  /* cap on the blocks of an inner launch (0 = as many as fit; -1 = whole

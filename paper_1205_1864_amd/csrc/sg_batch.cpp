@@ -786,7 +786,7 @@ int sg_batch_autotune(sg_batch B, int32_t flags, sg_tune_report* report) {
   sg_ctx* big = B->h[0];
   for (sg_ctx* h : B->h)
     if (h->n * (long)h->P > big->n * (long)big->P) big = h;
-  R.mv_variant = big->mv_variant;
+  R.mv_variant = big->mv_stage > 0 ? 4 : 3;
   R.mv_param = sgh::mv_param(big);
   R.pcg_tile = B->tile;
   R.pcg_max_blocks = B->max_blocks;

@@ -82,10 +82,7 @@ struct Plan {
   int maxcols, ntiles_max;
   size_t o_a64, o_a32, o_c64;
   size_t o_lo_ptr, o_lo_ent, o_lo_g64, o_lo_g32, o_up_ptr, o_up_ent, o_up_g64, o_up_g32;
-  size_t o_st_lo, o_st_up, o_st_glo64, o_st_gup64, o_st_glo32, o_st_gup32;
-  size_t o_en_ptr, o_en_k, o_en_lo, o_en_up, o_en_glo64, o_en_gup64, o_en_glo32, o_en_gup32;
   size_t o_pair_ptr, o_pair_a, o_pair_b, o_pair_g;
-  size_t o_mj_ptr, o_mj_rows, o_mj_kind, o_mj_lk, o_mj_lcol, o_mj_lw;
   size_t o_stg_terms, o_stg_slots, o_stg_wslot;
   size_t o_vec[7];
   size_t o_rw, o_zw;
@@ -154,34 +151,10 @@ void make_plan(const sg_problem* pr, const sg_opts* op, Plan& pl) {
   pl.o_up_ent = L.take(sizeof(int) * std::max(1, pl.nup));
   pl.o_up_g64 = L.take(sizeof(double) * std::max(1, pl.nup));
   pl.o_up_g32 = L.take(sizeof(float) * std::max(1, pl.nup));
-  const long PM = std::max<long>(1, (long)pl.P * M);
-  pl.o_st_lo = L.take(sizeof(int) * PM);
-  pl.o_st_up = L.take(sizeof(int) * PM);
-  pl.o_st_glo64 = L.take(sizeof(double) * PM);
-  pl.o_st_gup64 = L.take(sizeof(double) * PM);
-  pl.o_st_glo32 = L.take(sizeof(float) * PM);
-  pl.o_st_gup32 = L.take(sizeof(float) * PM);
-  pl.o_en_ptr = L.take(sizeof(int) * (pl.P + 1));
-  pl.o_en_k = L.take(sizeof(int) * PM);
-  pl.o_en_lo = L.take(sizeof(int) * PM);
-  pl.o_en_up = L.take(sizeof(int) * PM);
-  pl.o_en_glo64 = L.take(sizeof(double) * PM);
-  pl.o_en_gup64 = L.take(sizeof(double) * PM);
-  pl.o_en_glo32 = L.take(sizeof(float) * PM);
-  pl.o_en_gup32 = L.take(sizeof(float) * PM);
   pl.o_pair_ptr = L.take(sizeof(int) * (M + 1));
   pl.o_pair_a = L.take(sizeof(int) * std::max(1, pl.npairs));
   pl.o_pair_b = L.take(sizeof(int) * std::max(1, pl.npairs));
   pl.o_pair_g = L.take(sizeof(double) * std::max(1, pl.npairs));
-  // row groups of the y-marching operator: the matvec (P rows) and the 2p coupling
-  // products (two levels each), at most one group per row
-  const long mj_rows = 3L * pl.P;
-  pl.o_mj_ptr = L.take(sizeof(int) * (mj_rows + 2L * p + 2));
-  pl.o_mj_rows = L.take(sizeof(int) * mj_rows);
-  pl.o_mj_kind = L.take(sizeof(int) * mj_rows);
-  pl.o_mj_lk = L.take(sizeof(int) * mj_rows * sgk::kMarchNS);
-  pl.o_mj_lcol = L.take(sizeof(int) * mj_rows * sgk::kMarchRGL * sgk::kMarchNS);
-  pl.o_mj_lw = L.take(sizeof(double) * mj_rows * sgk::kMarchRGL * sgk::kMarchNS);
   // row-staged operator: output pairs and their (padded) term lists
   const long stg_slots = std::max(1, pl.P);
   pl.o_stg_terms = L.take(sizeof(sgk::StageTerm) * (pl.P + 1L) * (2L * M + 1));
@@ -207,85 +180,6 @@ void make_plan(const sg_problem* pr, const sg_opts* op, Plan& pl) {
   pl.total = L.total;
 }
 
-// Row groups of one use of the y-marching SG operator. Rows that use upper
-// neighbours go into groups of kMarchRGU rows that carry all KL terms; the
-// other rows are packed greedily, in order, into groups of at most kMarchRGL
-// rows whose lower neighbours use at most kMarchNS distinct KL terms. The
-// number of grid segments aims at one resident wave of blocks (cap_blocks).
-struct HostMarchJob {
-  std::vector<int> ptr, rows, kind, lk, lcol;
-  std::vector<double> lw;
-  int nseg = 8, seg_rows = 1;
-};
-
-void build_march_job(int M, int nx, const std::vector<int>& rows, bool lower, bool upper,
-                     const std::vector<int>& st_lo, const std::vector<int>& st_up,
-                     const std::vector<double>& st_glo, long cap_blocks, int seg_per_xcd, HostMarchJob& J) {
-  const int RGU = sgk::kMarchRGU, RGL = sgk::kMarchRGL, NS = sgk::kMarchNS;
-  std::vector<int> ru, rl;
-  for (int r : rows) {
-    bool has_up = false;
-    for (int k = 0; k < M && upper; ++k) has_up = has_up || st_up[(size_t)r * M + k] >= 0;
-    (has_up ? ru : rl).push_back(r);
-  }
-  J.ptr.assign(1, 0);
-  J.rows.clear();
-  J.kind.clear();
-  J.lk.clear();
-  J.lcol.clear();
-  J.lw.clear();
-  auto close = [&](int kind, const std::vector<int>& grp, const std::vector<int>& slots) {
-    J.rows.insert(J.rows.end(), grp.begin(), grp.end());
-    J.ptr.push_back((int)J.rows.size());
-    J.kind.push_back(kind);
-    for (int s = 0; s < NS; ++s) J.lk.push_back(s < (int)slots.size() ? slots[s] : -1);
-    for (int j = 0; j < RGL; ++j)
-      for (int s = 0; s < NS; ++s) {
-        int col = -1;
-        double w = 0.0;
-        if (kind == 1 && j < (int)grp.size() && s < (int)slots.size() && lower) {
-          const size_t e = (size_t)grp[j] * M + slots[s];
-          col = st_lo[e];
-          w = col >= 0 ? st_glo[e] : 0.0;
-        }
-        J.lcol.push_back(col);
-        J.lw.push_back(w);
-      }
-  };
-  for (size_t i = 0; i < ru.size(); i += RGU) {
-    std::vector<int> grp(ru.begin() + i, ru.begin() + std::min(ru.size(), i + RGU));
-    close(0, grp, {});
-  }
-  std::vector<int> grp, slots;
-  for (int r : rl) {
-    std::vector<int> need;
-    for (int k = 0; k < M && lower; ++k)
-      if (st_lo[(size_t)r * M + k] >= 0) need.push_back(k);
-    std::vector<int> merged = slots;
-    for (int k : need)
-      if (std::find(merged.begin(), merged.end(), k) == merged.end()) merged.push_back(k);
-    if (!grp.empty() && ((int)grp.size() == RGL || (int)merged.size() > NS)) {
-      close(1, grp, slots);
-      grp.clear();
-      slots.clear();
-      merged = need;
-    }
-    grp.push_back(r);
-    slots = merged;
-  }
-  if (!grp.empty()) close(1, grp, slots);
-  const long ng = std::max<long>(1, (long)J.kind.size());
-  // segments per XCD: as many as one resident wave of blocks allows (or the requested
-  // number), each at least 8 node rows tall
-  long spx = seg_per_xcd > 0 ? seg_per_xcd : std::min<long>(nx / 64, cap_blocks / (8 * ng));
-  spx = std::max<long>(1, std::min<long>(spx, nx / 64 > 0 ? nx / 64 : 1));
-  J.nseg = (int)(8 * spx);
-  J.seg_rows = (nx + J.nseg - 1) / J.nseg;
-}
-
-// Row groups of the y-marching SG operator for every use: job 0 is the matvec,
-// job 1 + 2 (l - 1) + dir the coupling product of level l in direction dir.
-// seg_per_xcd = 0 chooses the number of grid segments per XCD automatically.
 // Tables of the row-staged full operator. The slot of an output applies its
 // mean term (its own column, coefficient theta0); the term list holds the
 // Galerkin neighbours (b, k, g), b = a -+ e_k with the weight g of G_k (which
@@ -408,69 +302,31 @@ void set_stage_rows(sg_ctx* h, int rows) {
   h->stage.nyseg = (h->nx + rows - 1) / rows;
 }
 
-int build_march_jobs(sg_ctx* h, int seg_per_xcd) {
-  h->march_ok = false;
-  h->mjobs.clear();
-  const bool piece = h->mv_variant == 3 && h->M <= sgk::kPieceMaxM;
-  if (!piece && (!sgk::march_supported(h->n_e, h->M) || h->mv_variant != 2)) return SG_OK;
-  const int occ = piece ? 1 : sgk::march_blocks_per_cu(h->M, h->n_e);
-  if (occ <= 0) return SG_OK;
-  const long cap = (long)occ * h->num_cu;
-  const int M = h->M, P = h->P;
-  std::vector<HostMarchJob> jobs(1 + 2 * h->p);
-  std::vector<int> all(P);
-  for (int a = 0; a < P; ++a) all[a] = a;
-  build_march_job(M, h->nx, all, true, true, h->st_lo_h, h->st_up_h, h->st_glo_h, cap, seg_per_xcd, jobs[0]);
-  for (int l = 1; l <= h->p; ++l)
-    for (int dir = 0; dir < 2; ++dir) {
-      const int rl = dir == 0 ? l - 1 : l;
-      std::vector<int> rows;
-      for (int a = h->off[rl]; a < h->off[rl + 1]; ++a) rows.push_back(a);
-      build_march_job(M, h->nx, rows, dir == 1, dir == 0, h->st_lo_h, h->st_up_h, h->st_glo_h, cap, seg_per_xcd,
-                      jobs[1 + 2 * (l - 1) + dir]);
-    }
-  std::vector<int> ptr, rws, knd, lk, lcol;
-  std::vector<double> lw;
-  for (const HostMarchJob& J : jobs) {
-    sgk::MarchJob mj{};
-    mj.gptr = h->mj_ptr_d + ptr.size();
-    mj.grows = h->mj_rows_d;
-    mj.gkind = h->mj_kind_d + knd.size();
-    mj.lk = h->mj_lk_d + lk.size();
-    mj.lcol = h->mj_lcol_d + lcol.size();
-    mj.lw = h->mj_lw_d + lw.size();
-    mj.ngroups = (int)J.kind.size();
-    mj.nseg = J.nseg;
-    mj.seg_rows = J.seg_rows;
-    mj.piece = sgk::PieceGeom{0, 0, 0, 0, 0};
-    if (piece) {
-      // pieces of at most 62 output columns (one wavefront with its two halo
-      // columns), as many as the grid width needs and equally wide
-      const int nst = (h->nx + 61) / 62;
-      const int W = (h->nx + nst - 1) / nst;
-      const int TY = std::max(1, std::min(h->mv_piece_rows > 0 ? h->mv_piece_rows : 16, h->nx));
-      mj.piece = sgk::PieceGeom{W, (h->nx + W - 1) / W, TY, (h->nx + TY - 1) / TY, h->mv_piece_waves};
-    }
-    h->mjobs.push_back(mj);
-    const int base = (int)rws.size();
-    for (int v : J.ptr) ptr.push_back(base + v);
-    rws.insert(rws.end(), J.rows.begin(), J.rows.end());
-    knd.insert(knd.end(), J.kind.begin(), J.kind.end());
-    lk.insert(lk.end(), J.lk.begin(), J.lk.end());
-    lcol.insert(lcol.end(), J.lcol.begin(), J.lcol.end());
-    lw.insert(lw.end(), J.lw.begin(), J.lw.end());
-  }
-  hipStream_t s = h->stream;
-  SG_HIP(hipMemcpyAsync(h->mj_ptr_d, ptr.data(), sizeof(int) * ptr.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipMemcpyAsync(h->mj_rows_d, rws.data(), sizeof(int) * rws.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipMemcpyAsync(h->mj_kind_d, knd.data(), sizeof(int) * knd.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipMemcpyAsync(h->mj_lk_d, lk.data(), sizeof(int) * lk.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipMemcpyAsync(h->mj_lcol_d, lcol.data(), sizeof(int) * lcol.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipMemcpyAsync(h->mj_lw_d, lw.data(), sizeof(double) * lw.size(), hipMemcpyHostToDevice, s));
-  SG_HIP(hipStreamSynchronize(s));  // the host vectors go out of scope
-  h->march_ok = true;
-  h->mv_seg_per_xcd = piece ? 0 : seg_per_xcd;
-  return SG_OK;
+// Turns of the compute units (one block each) that the staged pieces of `rows`
+// node rows take, times the steps of a piece and 1.5 for its start.
+double stage_steps(const sg_ctx* h, int rows) {
+  const long pieces = (long)((h->nx + sgk::kStageOut - 1) / sgk::kStageOut) * ((h->nx + rows - 1) / rows);
+  return (double)((pieces + h->num_cu - 1) / h->num_cu) * (rows + 1.5);
+}
+
+// Kernel of the full operator without tuning: the staged kernel with the piece
+// height that fills the compute units' turns best (returned), or 0, the strip
+// kernel, by what the two were measured to take. A step of the staged kernel
+// takes 1.3 us + 7.7 ns per Galerkin entry (11.3 us at M = 10, p = 3; 1.4 at M = 4,
+// p = 2), the strip kernel 4 us + 2.0 ps per entry (the mean one included) and
+// node. Staged / strip kernel, us: 256^2, M = 10, p = 3, 10 rows 130 / 240; 512^2,
+// M = 8, p = 3, 37 rows 283 / 484 (10 rows: 322); 201^2, M = 6, p = 4, 6 rows 66 /
+// 111; 128^2, M = 8, p = 3, 3 rows 32 / 40; 100^2, M = 6, p = 4, 2 rows 32 / 29;
+// 512^2, M = 4, p = 2, 37 rows 54 / 32.
+int default_stage_rows(const sg_ctx* h) {
+  if (!h->stage_ok) return 0;
+  int best = 1;
+  for (int rows = 2; rows <= 64; ++rows)
+    if (stage_steps(h, rows) < stage_steps(h, best)) best = rows;
+  const double entries = (double)h->lo_ptr.back() + h->up_ptr.back();
+  const double staged = stage_steps(h, best) * (1.3 + 0.0077 * entries);
+  const double strip = 4.0 + 2.0e-6 * (entries + h->P) * (double)h->n;
+  return staged < strip ? best : 0;
 }
 
 // Spectrum of D^-1 K_0 for the Q1 stencil: (8 - 2 c_i - 2 c_j - 4 c_i c_j) / 8, c_i = cos(i pi / n_e).
@@ -722,19 +578,6 @@ sgk::ChaosLists<float> lists<float>(const sg_ctx* h) {
   return {h->lo_ptr_d, h->lo_ent_d, h->lo_g32, h->up_ptr_d, h->up_ent_d, h->up_g32};
 }
 template <typename T>
-sgk::StripTables<T> strip_tables(const sg_ctx* h);
-template <>
-sgk::StripTables<double> strip_tables<double>(const sg_ctx* h) {
-  return {h->st_lo_d, h->st_up_d, h->st_glo64, h->st_gup64, h->M, h->mv_blocks_per_band,
-          h->en_ptr_d, h->en_k_d, h->en_lo_d, h->en_up_d, h->en_glo64, h->en_gup64, h->mv_variant};
-}
-template <>
-sgk::StripTables<float> strip_tables<float>(const sg_ctx* h) {
-  return {h->st_lo_d, h->st_up_d, h->st_glo32, h->st_gup32, h->M, h->mv_blocks_per_band,
-          h->en_ptr_d, h->en_k_d, h->en_lo_d, h->en_up_d, h->en_glo32, h->en_gup32, h->mv_variant};
-}
-
-template <typename T>
 const T* coefs(const sg_ctx* h);
 template <>
 const double* coefs<double>(const sg_ctx* h) { return h->a64; }
@@ -762,7 +605,7 @@ void coupling(sg_ctx* h, int l, int dir, T* R, const T* V) {
   a.a = coefs<T>(h);
   a.lists = lists<T>(h);
   a.active = h->mask;
-  sgk::launch_sgop<T>(a, strip_tables<T>(h), h->march_ok ? &h->mjobs[1 + 2 * (l - 1) + dir] : nullptr, h->stream);
+  sgk::launch_sgop<T>(a, h->mv_rows, h->stream);
 }
 
 template void coupling<double>(sg_ctx*, int, int, double*, const double*);
@@ -1000,7 +843,7 @@ void matvec(sg_ctx* h, const double* U, double* Y) {
     sgk::launch_stage(a, h->stage, h->stream);
     return;
   }
-  sgk::launch_sgop<double>(a, strip_tables<double>(h), h->march_ok ? &h->mjobs[0] : nullptr, h->stream);
+  sgk::launch_sgop<double>(a, h->mv_rows, h->stream);
 }
 
 int read_out(sg_ctx* h, int count) {
@@ -1362,11 +1205,7 @@ int inner_solve_in(sg_ctx* h, const double* B, double* X, int ncols, int32_t* it
 }
 
 // Schedule parameter of the SG operator variant in use (as in sg_tune_report).
-int mv_param(const sg_ctx* h) {
-  if (h->mv_variant == 3) return (h->mv_piece_rows > 0 ? h->mv_piece_rows : 16) * 100 + h->mv_piece_waves;
-  if (h->mv_variant == 2) return h->mv_seg_per_xcd;
-  return h->mv_blocks_per_band;
-}
+int mv_param(const sg_ctx* h) { return h->mv_stage > 0 ? h->mv_stage : 100 * h->mv_rows; }
 
 // Schedule autotuner (sg_autotune).
 int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
@@ -1392,61 +1231,36 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
   if (flags & 1) {
     set_stage_rows(h, 0);  // the candidates below run the full operator through their own kernels
     sgk::launch_fill(h->pv, 1.0, N, s);
-    struct Cand {
-      int variant, param;
-    };
-    std::vector<Cand> cands;
-    const bool wide = h->n_e % 64 == 0 && h->n_e >= 64 && h->n_e <= 512;
-    // piece kernel: node rows per piece (param = rows * 100 + wave cap per CU)
-    if (h->M <= sgk::kPieceMaxM)
-      for (int ty : {8, 16, 32})
-        for (int waves : {0, 4})  // all resident waves, or 4 per CU (fewer pieces at once per XCD)
-          if (ty <= std::max(8, h->nx)) cands.push_back({3, ty * 100 + waves});
-    if (sgk::march_supported(h->n_e, h->M))
-      for (int spx : {0, 1, 2, 4}) cands.push_back({2, spx});
-    if (wide) {
-      for (int bpb : {32, 64, 128}) cands.push_back({1, bpb});
-      if (h->M <= 12)
-        for (int bpb : {64, 128}) cands.push_back({0, bpb});
-    }
-    auto apply = [&](const Cand& c) -> int {
-      h->mv_variant = c.variant;
-      h->mv_blocks_per_band = c.variant == 0 || c.variant == 1 ? c.param : 0;
-      if (c.variant == 3) {
-        h->mv_piece_rows = c.param / 100;
-        h->mv_piece_waves = c.param % 100;
-      }
-      return build_march_jobs(h, c.variant == 2 ? c.param : 0);
-    };
+    // strip kernel: rows per wave (the couplings keep the pick)
     double best = 1e300;
-    Cand pick{h->mv_variant, mv_param(h)};
-    for (const Cand& c : cands) {
-      int rc = apply(c);
-      if (rc) return rc;
+    int pick = 0;
+    for (int rows : {0, 2, 4, 6, 8}) {
+      h->mv_rows = rows;
       matvec(h, h->pv, h->q);
       matvec(h, h->pv, h->q);
       double med = 0.0;
-      rc = event_ms([&] { matvec(h, h->pv, h->q); }, 5, &med);
+      const int rc = event_ms([&] { matvec(h, h->pv, h->q); }, 5, &med);
       if (rc) return rc;
       ++R.candidates;
       if (med < best) {
         best = med;
-        pick = c;
+        pick = rows;
       }
     }
-    int rc = apply(pick);
-    if (rc) return rc;
-    R.mv_ms = cands.empty() ? 0.0 : best;
-    // the full operator may then take the row-staged kernel (the couplings keep the pick)
+    h->mv_rows = pick;
+    // the full operator may then take the row-staged kernel
     int best_rows = 0;
-    if (h->stage_ok)
-      for (int rows : {4, 6, 8, 10, 12, 16}) {
+    if (h->stage_ok) {
+      std::vector<int> heights = {4, 6, 8, 10, 12, 16};
+      const int fill = default_stage_rows(h);
+      if (fill > 0 && std::find(heights.begin(), heights.end(), fill) == heights.end()) heights.push_back(fill);
+      for (int rows : heights) {
         if (rows > std::max(4, h->nx)) continue;
         set_stage_rows(h, rows);
         matvec(h, h->pv, h->q);
         matvec(h, h->pv, h->q);
         double med = 0.0;
-        rc = event_ms([&] { matvec(h, h->pv, h->q); }, 5, &med);
+        const int rc = event_ms([&] { matvec(h, h->pv, h->q); }, 5, &med);
         if (rc) return rc;
         ++R.candidates;
         if (med < best) {
@@ -1454,11 +1268,12 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
           best_rows = rows;
         }
       }
+    }
     set_stage_rows(h, best_rows);
-    R.mv_ms = best < 1e300 ? best : 0.0;
+    R.mv_ms = best;
   }
-  R.mv_variant = h->mv_stage > 0 ? 4 : h->mv_variant;
-  R.mv_param = h->mv_stage > 0 ? h->mv_stage : mv_param(h);
+  R.mv_variant = h->mv_stage > 0 ? 4 : 3;
+  R.mv_param = mv_param(h);
   const int degree = effective_degree(h);
   if (flags & 2) {
     const int lev = h->p;
@@ -1566,11 +1381,7 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   h->ws_bytes = workspace_bytes;
   multi_indices(h->M, h->p, h->alpha, h->off);
   cheb_interval(h->n_e, h->lmin, h->lmax);
-  h->mv_blocks_per_band = 0;
-  if (const char* env = std::getenv("SGPC_MV_BLOCKS_PER_BAND")) h->mv_blocks_per_band = std::atoi(env);
-  h->mv_variant = pr->M <= sgk::kPieceMaxM ? 3 : 2;
-  if (const char* env = std::getenv("SGPC_MV_VARIANT")) h->mv_variant = std::atoi(env);
-  if (const char* env = std::getenv("SGPC_MV_PIECE_ROWS")) h->mv_piece_rows = std::atoi(env);
+  if (const char* env = std::getenv("SGPC_MV_ROWS")) h->mv_rows = std::atoi(env);
   h->pcg_max_blocks = 0;
   if (const char* env = std::getenv("SGPC_PCG_MAX_BLOCKS")) h->pcg_max_blocks = std::atoi(env);
   const int M = h->M, P = h->P;
@@ -1634,10 +1445,10 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
     up_ptr[a + 1] = (int)up_ent.size();
   }
   std::vector<float> lo_g32(lo_g.begin(), lo_g.end()), up_g32(up_g.begin(), up_g.end());
-  // dense [P][M] neighbour tables for the strip kernel
+  // dense [P][M] neighbour tables for the staged term lists
   const size_t PMd = std::max<size_t>(1, (size_t)P * M);
   std::vector<int> st_lo(PMd, -1), st_up(PMd, -1);
-  std::vector<double> st_glo(PMd, 0.0), st_gup(PMd, 0.0);
+  std::vector<double> st_glo(PMd, 0.0);
   for (int a = 0; a < P; ++a) {
     for (int e = lo_ptr[a]; e < lo_ptr[a + 1]; ++e) {
       const int k = (lo_ent[e] >> 20) - 1;
@@ -1647,26 +1458,8 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
     for (int e = up_ptr[a]; e < up_ptr[a + 1]; ++e) {
       const int k = (up_ent[e] >> 20) - 1;
       st_up[(size_t)a * M + k] = up_ent[e] & 0xFFFFF;
-      st_gup[(size_t)a * M + k] = up_g[e];
     }
   }
-  std::vector<float> st_glo32(st_glo.begin(), st_glo.end()), st_gup32(st_gup.begin(), st_gup.end());
-  // compact entry lists: one entry per KL term with at least one Galerkin neighbour
-  std::vector<int> en_ptr(P + 1, 0), en_k, en_lo, en_up;
-  std::vector<double> en_glo, en_gup;
-  for (int a = 0; a < P; ++a) {
-    for (int k = 0; k < M; ++k) {
-      const int lo = st_lo[(size_t)a * M + k], upi = st_up[(size_t)a * M + k];
-      if (lo < 0 && upi < 0) continue;
-      en_k.push_back(k);
-      en_lo.push_back(lo >= 0 ? lo : a);
-      en_up.push_back(upi >= 0 ? upi : a);
-      en_glo.push_back(lo >= 0 ? st_glo[(size_t)a * M + k] : 0.0);
-      en_gup.push_back(upi >= 0 ? st_gup[(size_t)a * M + k] : 0.0);
-    }
-    en_ptr[a + 1] = (int)en_k.size();
-  }
-  std::vector<float> en_glo32(en_glo.begin(), en_glo.end()), en_gup32(en_gup.begin(), en_gup.end());
   std::vector<int> pair_ptr(M + 1, 0), pair_a, pair_b;
   std::vector<double> pair_g;
   for (int k = 0; k < M; ++k) {
@@ -1699,20 +1492,6 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   h->up_ent_d = (int*)(w + pl.o_up_ent);
   h->up_g64 = (double*)(w + pl.o_up_g64);
   h->up_g32 = (float*)(w + pl.o_up_g32);
-  h->st_lo_d = (int*)(w + pl.o_st_lo);
-  h->st_up_d = (int*)(w + pl.o_st_up);
-  h->st_glo64 = (double*)(w + pl.o_st_glo64);
-  h->st_gup64 = (double*)(w + pl.o_st_gup64);
-  h->st_glo32 = (float*)(w + pl.o_st_glo32);
-  h->st_gup32 = (float*)(w + pl.o_st_gup32);
-  h->en_ptr_d = (int*)(w + pl.o_en_ptr);
-  h->en_k_d = (int*)(w + pl.o_en_k);
-  h->en_lo_d = (int*)(w + pl.o_en_lo);
-  h->en_up_d = (int*)(w + pl.o_en_up);
-  h->en_glo64 = (double*)(w + pl.o_en_glo64);
-  h->en_gup64 = (double*)(w + pl.o_en_gup64);
-  h->en_glo32 = (float*)(w + pl.o_en_glo32);
-  h->en_gup32 = (float*)(w + pl.o_en_gup32);
   h->pair_ptr_d = (int*)(w + pl.o_pair_ptr);
   h->pair_a_d = (int*)(w + pl.o_pair_a);
   h->pair_b_d = (int*)(w + pl.o_pair_b);
@@ -1752,20 +1531,6 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   if (e == hipSuccess) e = up(h->up_ent_d, up_ent.data(), sizeof(int) * up_ent.size());
   if (e == hipSuccess) e = up(h->up_g64, up_g.data(), sizeof(double) * up_g.size());
   if (e == hipSuccess) e = up(h->up_g32, up_g32.data(), sizeof(float) * up_g32.size());
-  if (e == hipSuccess) e = up(h->st_lo_d, st_lo.data(), sizeof(int) * st_lo.size());
-  if (e == hipSuccess) e = up(h->st_up_d, st_up.data(), sizeof(int) * st_up.size());
-  if (e == hipSuccess) e = up(h->st_glo64, st_glo.data(), sizeof(double) * st_glo.size());
-  if (e == hipSuccess) e = up(h->st_gup64, st_gup.data(), sizeof(double) * st_gup.size());
-  if (e == hipSuccess) e = up(h->st_glo32, st_glo32.data(), sizeof(float) * st_glo32.size());
-  if (e == hipSuccess) e = up(h->st_gup32, st_gup32.data(), sizeof(float) * st_gup32.size());
-  if (e == hipSuccess) e = up(h->en_ptr_d, en_ptr.data(), sizeof(int) * en_ptr.size());
-  if (e == hipSuccess) e = up(h->en_k_d, en_k.data(), sizeof(int) * en_k.size());
-  if (e == hipSuccess) e = up(h->en_lo_d, en_lo.data(), sizeof(int) * en_lo.size());
-  if (e == hipSuccess) e = up(h->en_up_d, en_up.data(), sizeof(int) * en_up.size());
-  if (e == hipSuccess) e = up(h->en_glo64, en_glo.data(), sizeof(double) * en_glo.size());
-  if (e == hipSuccess) e = up(h->en_gup64, en_gup.data(), sizeof(double) * en_gup.size());
-  if (e == hipSuccess) e = up(h->en_glo32, en_glo32.data(), sizeof(float) * en_glo32.size());
-  if (e == hipSuccess) e = up(h->en_gup32, en_gup32.data(), sizeof(float) * en_gup32.size());
   if (e == hipSuccess) e = up(h->pair_ptr_d, pair_ptr.data(), sizeof(int) * pair_ptr.size());
   if (e == hipSuccess) e = up(h->pair_a_d, pair_a.data(), sizeof(int) * pair_a.size());
   if (e == hipSuccess) e = up(h->pair_b_d, pair_b.data(), sizeof(int) * pair_b.size());
@@ -1773,12 +1538,6 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
   h->st_lo_h = st_lo;
   h->st_up_h = st_up;
   h->st_glo_h = st_glo;
-  h->mj_ptr_d = (int*)(w + pl.o_mj_ptr);
-  h->mj_rows_d = (int*)(w + pl.o_mj_rows);
-  h->mj_kind_d = (int*)(w + pl.o_mj_kind);
-  h->mj_lk_d = (int*)(w + pl.o_mj_lk);
-  h->mj_lcol_d = (int*)(w + pl.o_mj_lcol);
-  h->mj_lw_d = (double*)(w + pl.o_mj_lw);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess && h->nx <= sgk::kSineMaxNx) {
     h->sine = sgk::sine_sizes(h->nx);
@@ -1786,17 +1545,12 @@ int sg_setup(const sg_problem* pr, const sg_opts* op, void* workspace, size_t wo
     e = hipGetLastError();
     h->sine_ok = e == hipSuccess && h->sine.groups <= h->num_cu;
   }
-  if (e == hipSuccess && build_march_jobs(h, 0) != SG_OK) e = hipErrorUnknown;
   if (e == hipSuccess &&
       build_stage_tables(h, (sgk::StageTerm*)(w + pl.o_stg_terms), (sgk::StageSlot*)(w + pl.o_stg_slots),
                          (int*)(w + pl.o_stg_wslot)) != SG_OK)
     e = hipErrorUnknown;
   if (e == hipSuccess) {
-    // the full operator takes the row-staged kernel where it fits and its pieces
-    // of 10 node rows keep at least half of the compute units busy (one block per
-    // CU); the autotuner chooses among 4..16 rows or the other kernels
-    const long pieces10 = (long)((h->nx + sgk::kStageOut - 1) / sgk::kStageOut) * ((h->nx + 9) / 10);
-    int rows = 2 * pieces10 >= h->num_cu ? 10 : 0;
+    int rows = default_stage_rows(h);
     if (const char* env = std::getenv("SGPC_MV_STAGE")) rows = std::atoi(env);
     set_stage_rows(h, rows);
   }

@@ -138,68 +138,9 @@ struct SgOpArgs {
   const int* active;  // if not null: the launch does nothing while *active == 0
 };
 
-// Dense per-row neighbour tables [P][M] for the strip kernel: lo[a*M + k] is the
-// row index of a - e_{k+1} (or -1) with coefficient glo = sqrt(a_{k+1}); up the same
-// for a + e_{k+1} with gup = sqrt(a_{k+1} + 1).
+// Strip kernel; rows: node rows per wave (2, 4, 6 or 8; 0 = automatic).
 template <typename T>
-struct StripTables {
-  const int* lo;
-  const int* up;
-  const T* glo;
-  const T* gup;
-  int M;
-  int blocks_per_band;  // row chunks per grid band (0 = default)
-  // Compact per-row entry lists for the occupancy variant: entries of row a are
-  // ent_ptr[a] .. ent_ptr[a+1]-1, each (k, lo, up) with glo/gup (absent side: index a, weight 0).
-  const int* ent_ptr;
-  const int* ent_k;
-  const int* ent_lo;
-  const int* ent_up;
-  const T* ent_glo;
-  const T* ent_gup;
-  int variant;  // 0: coefficients in registers, 1: coefficients loaded per entry
-};
-
-// Row groups of one use of the SG operator (the full matvec, or one coupling
-// product) for the y-marching kernel. Group g owns rows grows[gptr[g] ..
-// gptr[g+1]-1]. A group of kind 0 holds at most kMarchRGU rows that have upper
-// neighbours (all KL terms used, neighbours from the dense [P][M] tables); a
-// group of kind 1 holds at most kMarchRGL rows with lower neighbours only,
-// whose KL terms are gathered into kMarchNS slots: lk[g][s] is the KL term
-// (0-based, -1 unused) of slot s and lcol/lw[g][j][s] the lower neighbour of
-// row j through that term (-1 none) and its weight. The grid rows 1..nx are cut
-// into nseg segments of seg_rows node rows; a block handles one (segment,
-// group) pair.
-constexpr int kMarchRGU = 2;
-constexpr int kMarchRGL = 6;
-constexpr int kMarchNS = 4;
-// Spatial pieces of the piece kernel: W interior node columns per piece (one
-// wavefront holds W + 2 columns with the halo), nstrips = ceil(nx / W) pieces
-// across, TY node rows per piece, nyseg = ceil(nx / TY) pieces up. W = 0: the
-// piece kernel is not used. max_waves_per_cu caps the resident waves (0: as
-// many as fit).
-struct PieceGeom {
-  int W;
-  int nstrips;
-  int TY;
-  int nyseg;
-  int max_waves_per_cu;
-};
-struct MarchJob {
-  const int* gptr;
-  const int* grows;
-  const int* gkind;
-  const int* lk;
-  const int* lcol;
-  const double* lw;
-  int ngroups;
-  int nseg;
-  int seg_rows;
-  PieceGeom piece;
-};
-
-template <typename T>
-void launch_sgop(const SgOpArgs<T>& args, const StripTables<T>& tab, const MarchJob* job, hipStream_t s);
+void launch_sgop(const SgOpArgs<T>& args, int rows, hipStream_t s);
 
 // Row-staged SG operator (the full FP64 operator Y = sum_k K_k U G_k^T): a block
 // of kStageWaves waves stages node rows of all P chaos columns, for a segment of
@@ -238,13 +179,6 @@ struct StageJob {
 // LDS bytes of the row-staged kernel, 0 if the problem does not fit it.
 size_t stage_lds_bytes(int P, int M, int nterms, int nslots);
 void launch_stage(const SgOpArgs<double>& args, const StageJob& job, hipStream_t s);
-
-// Largest number of KL terms served by the piece kernel (dense [P][M] tables).
-constexpr int kPieceMaxM = 12;
-
-// Resident blocks per CU of the y-marching kernel for this M and block size (0 if unsupported).
-int march_blocks_per_cu(int M, int block);
-bool march_supported(int n_e, int M);
 
 // Persistent batched PCG on K_0 = theta0 * K_Lap (one independent solve per column).
 struct PcgScratch {
@@ -541,22 +475,14 @@ struct sg_ctx {
   hipStream_t stream;
   int num_cu;
   int tile;
-  int mv_blocks_per_band;
-  int mv_variant;  // 0, 1: band kernels; 2: y-marching kernel
   int pcg_max_blocks;
-  bool march_ok;
-  int mv_seg_per_xcd = 0;  // grid segments per XCD of the y-marching kernel (0 = automatic)
-  int mv_piece_rows = 0;   // node rows per piece of the piece kernel (0 = default 16)
-  int mv_piece_waves = 0;  // cap on resident waves per CU of the piece kernel (0 = as many as fit)
+  int mv_rows = 0;         // node rows per wave of the strip kernel (0 = automatic)
   // row-staged kernel for the full operator (sg_matvec and the outer CG products)
   bool stage_ok = false;   // tables built and the sizes fit
   int mv_stage = 0;        // node rows per piece when the full operator uses it, 0 = off
   sgk::StageJob stage{};
-  std::vector<sgk::MarchJob> mjobs;
-  std::vector<int> st_lo_h, st_up_h;  // host copies of the dense neighbour tables (row groups)
+  std::vector<int> st_lo_h, st_up_h;  // dense neighbour tables [P][M] (-1: none) for the staged term lists
   std::vector<double> st_glo_h;
-  int *mj_ptr_d, *mj_rows_d, *mj_kind_d, *mj_lk_d, *mj_lcol_d;
-  double* mj_lw_d;
   const int* mask = nullptr;  // device flag of a batch member: SG operator launches skip while it is 0
   // host copies of the chaos lists (for counters)
   std::vector<int> lo_ptr, up_ptr;
@@ -569,12 +495,6 @@ struct sg_ctx {
   int *lo_ptr_d, *lo_ent_d, *up_ptr_d, *up_ent_d;
   double *lo_g64, *up_g64;
   float *lo_g32, *up_g32;
-  int *st_lo_d, *st_up_d;
-  int *en_ptr_d, *en_k_d, *en_lo_d, *en_up_d;
-  double *en_glo64, *en_gup64;
-  float *en_glo32, *en_gup32;
-  double *st_glo64, *st_gup64;
-  float *st_glo32, *st_gup32;
   int *pair_ptr_d, *pair_a_d, *pair_b_d;
   double* pair_g_d;
   double *r, *z, *pv, *q, *lam, *tmp, *rhs;  // FP64 n x P blocks
