@@ -55,31 +55,6 @@ constexpr long kSpinLimit = 1L << 26;      // bounded waits: a stuck column abor
 enum { PART_BB = 0, PART_PQ0 = 1, PART_PQ1 = 2, PART_RR0 = 3, PART_RR1 = 4, PART_RZ0 = 5, PART_RZ1 = 6, PART_N = 7 };
 static_assert(PART_N == kPcgPartials, "partial arrays of the inner solver");
 
-// DPP move of a double within rows of 16 lanes (every source lane exists).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
-// Sum over the 64 lanes of a wave, the same in every lane and in a fixed
-// order: butterflies within rows of 16 lanes (neighbour in the quad, the
-// other pair of the quad, the other quad of each 8, the other 8 of each 16;
-// both partners add the same two values), then the four row sums in order.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_f64<0xB1>(v);   // quad_perm [1,0,3,2]
-  v += dpp_f64<0x4E>(v);   // quad_perm [2,3,0,1]
-  v += dpp_f64<0x141>(v);  // row_half_mirror
-  v += dpp_f64<0x140>(v);  // row_mirror
-  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
-}
-
 // Split-phase barrier of one column: every block that owns tiles of the column
 // adds its tile count to a monotonic arrival counter after finishing its tiles;
 // phase k of the column is complete once the counter reaches k * ntiles. The

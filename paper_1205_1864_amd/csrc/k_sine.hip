@@ -23,7 +23,6 @@ namespace {
 
 constexpr long kSpinLimit = 1L << 26;  // bounded waits: a stuck group aborts the launch
 constexpr int kSumWidth = 4;           // sums exchanged at once by the blocks of a group
-constexpr unsigned long long kEmpty = 0x7ff8dead7ff8deadull;  // an exchange place without a value (a NaN)
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -379,39 +378,14 @@ __global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab,
 // Iteration
 // ---------------------------------------------------------------------------
 
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, false);
-  return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double lane_f64(double v, int lane) {
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-// Sum over the wave in a fixed order, the same in every lane.
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_f64<0xB1>(v);
-  v += dpp_f64<0x4E>(v);
-  v += dpp_f64<0x141>(v);
-  v += dpp_f64<0x140>(v);
-  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
-}
-
 // Sums over a column: the block's threads, then the blocks of its group (in
 // a fixed order), the same bits in every thread of the group. A group
 // of one block needs its own barrier only. Otherwise the blocks exchange their
-// sums through memory that every compute unit sees coherently (agent-scope
-// atomics): a published value is its own flag, since the place it goes to holds
-// kEmpty before and no sum is stored with those bits. Three exchange buffers
-// take turns. Passing the wait of one exchange means that every block has read
+// sums through places that are empty until a value is there. Three exchange
+// buffers take turns. Passing the wait of one exchange means that every block has read
 // the one before it, so a block clears its places of that one, waits until the
 // stores are done and only then publishes again: nobody finds an old value.
 // The wait is bounded and ends the launch with an error status.
-__device__ __forceinline__ void agent_store(unsigned long long* p, unsigned long long v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 struct ColumnSums {
   double (*red)[kSineThreads / 64][kSumWidth];  // two buffers, used in turn
   double (*all)[kSumWidth];                     // group sums, two buffers
@@ -450,10 +424,8 @@ struct ColumnSums {
       // lane i < 4 publishes sum i; then lanes read the group's places, 64 at a time
       t += __shfl_xor(t, 16);
       if (lane < kSumWidth) {
-        unsigned long long bits = (unsigned long long)__double_as_longlong(t);
-        if (bits == kEmpty) bits = 0x7ff8000000000000ull;
         __builtin_amdgcn_s_waitcnt(0);  // this lane's clearing store of the last exchange is done
-        agent_store(slot(epoch, g) + lane, bits);
+        agent_store(slot(epoch, g) + lane, publishable(t));
       }
       double s = 0.0;
       int ok = dead ? 0 : 1;
@@ -463,7 +435,7 @@ struct ColumnSums {
         unsigned long long bits = 0;
         if (k < groups * kSumWidth) {
           long spins = 0;
-          while ((bits = __hip_atomic_load(src + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == kEmpty && ok) {
+          while ((bits = agent_load(src + k)) == kEmpty && ok) {
             __builtin_amdgcn_s_sleep(1);
             if (++spins > kSpinLimit) ok = 0;
           }

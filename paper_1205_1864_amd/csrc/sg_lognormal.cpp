@@ -18,6 +18,7 @@
 
 #include "sg_host.h"
 #include "sg_internal.h"
+#include "sg_logn.h"
 
 namespace sgk {
 void launch_logn_blocks(const long* ptr, const int* term, const double* g, const double* kc, int ne2, int nslots,
@@ -56,6 +57,12 @@ struct sg_logn_ctx {
   double *cr = nullptr, *cz = nullptr, *cp = nullptr, *cq = nullptr, *Dinv = nullptr, *part = nullptr;
   double* XF = nullptr;  // forward-sweep values of block Gauss-Seidel
   std::vector<double> host_part;
+  // one-launch block solves: stored blocks per row, iteration count, status
+  int* first = nullptr;
+  unsigned long long* its_d = nullptr;
+  unsigned long long* status_d = nullptr;
+  bool one_launch = true;  // off while a solve repeats without them
+  long spins = 1L << 20;   // polls before a wait expires, about a second
 };
 
 namespace {
@@ -113,7 +120,7 @@ double triple(int a, int b, int c) {
 struct Plan {
   int P = 0, T = 0, nslots = 0;
   size_t o_C = 0, o_kc = 0, o_ptr = 0, o_term = 0, o_g = 0, o_rptr = 0, o_rcol = 0, o_rslot = 0, total = 0;
-  size_t o_vec = 0, o_part = 0;
+  size_t o_vec = 0, o_part = 0, o_first = 0, o_count = 0;
   // host tables
   std::vector<std::vector<int>> alpha, coef;
   std::vector<long> ptr;
@@ -226,6 +233,8 @@ int plan(const sg_problem* pr, Plan& pl) {
   const size_t nP = (size_t)(pr->n_e - 1) * (pr->n_e - 1) * pl.P;
   pl.o_vec = take(tot, sizeof(double) * nP * 12);
   pl.o_part = take(tot, sizeof(double) * 2 * kLognDotBlocks);  // two partial sets
+  pl.o_first = take(tot, sizeof(int) * 2 * pl.P);
+  pl.o_count = take(tot, 2 * sizeof(unsigned long long));
   pl.total = tot;
   return SG_OK;
 }
@@ -248,11 +257,43 @@ int dotp(sg_logn_ctx* h, const double* x, const double* y, long len, double& out
 //           level block D_l of Section 6, where the level blocks couple, or one
 //           block A_aa);
 //   kind 1: I (x) K(k_0) over nr columns (the mean-based preconditioner).
-// B and X: n x nr device blocks.
+// B and X: n x nr device blocks. nsys systems of kind 1 lie side by side. Systems
+// that fit run in one launch without the host (their iterations are counted on the
+// device: 10 x 10, N = 4, degree 4, 2835 unknowns, 63 us per iteration with four
+// launches and two host round trips, 5 us in one launch); larger ones iterate here.
 int range_solve(sg_logn_ctx* h, int kind, int lo, int nr, const double* B, double* X, double rtol, int maxit,
-                long& its) {
+                long& its, int nsys = 1) {
   const long len = h->n * (long)nr;
   hipStream_t s = h->stream;
+  if (h->one_launch) {
+    sgk::LognSolveArgs a{};
+    a.rptr = h->rptr;
+    a.rcol = h->rcol;
+    a.C = h->C;
+    a.Dinv = h->Dinv;
+    a.n_e = h->n_e;
+    a.P = h->P;
+    a.lo = kind == 0 ? lo : 0;  // K(k_0) is block (0, 0)
+    a.nr = nr;
+    a.B = B;
+    a.X = X;
+    a.stride = h->n;
+    a.rtol = rtol;
+    a.maxit = maxit;
+    a.ex = reinterpret_cast<unsigned long long*>(h->cr);  // cr, cz and cp lie side by side
+    a.first = h->first;
+    a.last = h->first + h->P;
+    a.its = h->its_d;
+    a.status = h->status_d;
+    a.spins = h->spins;
+    bool done = false;
+    SG_HIP(sgk::launch_logn_solve(a, nsys, s, &done));
+    if (done) return SG_OK;
+  }
+  for (int k = 1; k < nsys; ++k) {
+    const int rck = range_solve(h, kind, lo, nr, B + k * h->n, X + k * h->n, rtol, maxit, its);
+    if (rck) return rck;
+  }
   const double* dinv = kind == 0 ? h->Dinv + (long)lo * h->n : h->Dinv;  // column 0: K(k_0)
   const long dn = kind == 0 ? len : h->n;
   double bb = 0.0, rz = 0.0, pq = 0.0, rr = 0.0, rzn = 0.0;
@@ -339,6 +380,87 @@ int hsc_apply(sg_logn_ctx* h, const double* R, double* Z, double rtol, int maxit
   return SG_OK;
 }
 
+// Flexible CG of sg_logn_solve; `expired`: a block solve's bounded wait ran out and
+// the results are not set.
+int solve_fcg(sg_logn_ctx* h, int precond, const double* F, double* U, double rtol, int maxit, double inner_rtol,
+              int inner_maxit, int32_t* outer_it, int64_t* inner_it, double* relres, double* kappa, bool& expired) {
+  expired = false;
+  const long nP = h->n * (long)h->P;
+  hipStream_t s = h->stream;
+  // flexible CG (Section 5) on A with Algorithm 1 as the preconditioner
+  sgk::launch_logn_axpby(nP, 0.0, F, 0.0, U, 0, nullptr, 0, s);  // U = 0
+  sgk::launch_logn_axpby(nP, 1.0, F, 0.0, h->R, 0, nullptr, 0, s);
+  const unsigned long long zero[2] = {0, 0};
+  SG_HIP(hipMemcpyAsync(h->its_d, zero, sizeof(zero), hipMemcpyHostToDevice, s));
+  double ff = 0.0, rr = 0.0;
+  int rc = dotp(h, F, F, nP, ff);  // waits for the stream
+  if (rc) return rc;
+  if (!std::isfinite(ff)) return fail(SG_EINVAL, "right-hand side is not finite");
+  std::vector<double> al, be;
+  long its_in = 0;
+  int it = 0, status = SG_NOT_CONVERGED;
+  double rel = ff > 0.0 ? 1.0 : 0.0, pq_prev = 0.0;
+  if (ff == 0.0 || rel <= rtol) status = SG_OK;
+  for (; status == SG_NOT_CONVERGED && it < maxit; ++it) {
+    if (precond == SG_PC_HSC)
+      rc = hsc_apply(h, h->R, h->Z, inner_rtol, inner_maxit, its_in);
+    else if (precond == SG_PC_BGS)
+      rc = bgs_apply(h, h->R, h->Z, inner_rtol, inner_maxit, its_in);
+    else  // each column its own K(k_0) solve, so every column meets the inner tolerance
+      rc = range_solve(h, 1, 0, 1, h->R, h->Z, inner_rtol, inner_maxit, its_in, h->P);
+    if (rc) return rc;
+    if (it == 0) {
+      sgk::launch_logn_axpby(nP, 1.0, h->Z, 0.0, h->Pv, 0, nullptr, 0, s);
+    } else {
+      double zq = 0.0;
+      if ((rc = dotp(h, h->Z, h->Q, nP, zq))) return rc;
+      const double beta = -zq / pq_prev;
+      be.push_back(beta);
+      sgk::launch_logn_axpby(nP, 1.0, h->Z, beta, h->Pv, 0, nullptr, 0, s);
+    }
+    sgk::launch_logn_matvec(h->rptr, h->rcol, h->rslot, h->C, h->Pv, h->n_e, h->n, h->P, h->Q, s);
+    double pq = 0.0, pr = 0.0;
+    if ((rc = dotp(h, h->Pv, h->Q, nP, pq))) return rc;
+    if (!(pq > 0.0) || !std::isfinite(pq)) {
+      status = SG_BREAKDOWN;
+      break;
+    }
+    if ((rc = dotp(h, h->Pv, h->R, nP, pr))) return rc;
+    const double alpha = pr / pq;
+    al.push_back(alpha);
+    sgk::launch_logn_axpby(nP, alpha, h->Pv, 1.0, U, 0, nullptr, 0, s);
+    sgk::launch_logn_axpby(nP, -alpha, h->Q, 1.0, h->R, 0, nullptr, 0, s);
+    pq_prev = pq;
+    if ((rc = dotp(h, h->R, h->R, nP, rr))) return rc;
+    rel = std::sqrt(rr / ff);
+    if (!std::isfinite(rel)) {
+      status = SG_BREAKDOWN;
+      ++it;
+      break;
+    }
+    if (rel <= rtol) {
+      status = SG_OK;
+      ++it;
+      break;
+    }
+  }
+  unsigned long long counts[2] = {0, 0};
+  SG_HIP(hipMemcpyAsync(counts, h->its_d, sizeof(counts), hipMemcpyDeviceToHost, s));
+  SG_HIP(hipStreamSynchronize(s));
+  if (counts[1] != 0) {
+    expired = true;
+    return SG_EDEVICE;
+  }
+  its_in += (long)counts[0];
+  if (outer_it) *outer_it = it;
+  if (inner_it) *inner_it = its_in;
+  if (relres) *relres = rel;
+  if (kappa) *kappa = al.empty() ? 1.0 : sgh::lanczos_kappa(al, be);
+  if (status == SG_NOT_CONVERGED) return fail(SG_NOT_CONVERGED, "outer iteration did not converge");
+  if (status == SG_BREAKDOWN) return fail(SG_BREAKDOWN, "breakdown: non-positive or non-finite curvature");
+  return SG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -413,6 +535,10 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
     for (int i = 0; i < 12; ++i) *vecs[i] = v + i * nP;
     h->part = (double*)(w + pl.o_part);
     h->host_part.assign(2 * kLognDotBlocks, 0.0);
+    h->first = (int*)(w + pl.o_first);
+    h->its_d = (unsigned long long*)(w + pl.o_count);
+    h->status_d = h->its_d + 1;
+    if (const char* v = std::getenv("SGPC_LOGN_SPINS")) h->spins = std::max(0L, std::atol(v));
     h->off.assign(1, 0);
     for (int d = 0; d <= pr->p; ++d) {
       int cnt = 0;
@@ -475,72 +601,15 @@ int sg_logn_solve(sg_logn_handle h, int32_t precond, const double* F, double* U,
   if (F == U) return fail(SG_EINVAL, "F and U must be distinct");
   if (!(rtol >= 0.0) || maxit < 0 || !(inner_rtol > 0.0 && inner_rtol < 1.0) || inner_maxit < 1)
     return fail(SG_EINVAL, "need rtol >= 0, maxit >= 0, 0 < inner_rtol < 1, inner_maxit >= 1");
-  const long nP = h->n * (long)h->P;
-  hipStream_t s = h->stream;
-  // flexible CG (Section 5) on A with Algorithm 1 as the preconditioner
-  sgk::launch_logn_axpby(nP, 0.0, F, 0.0, U, 0, nullptr, 0, s);  // U = 0
-  sgk::launch_logn_axpby(nP, 1.0, F, 0.0, h->R, 0, nullptr, 0, s);
-  double ff = 0.0, rr = 0.0;
-  int rc = dotp(h, F, F, nP, ff);
-  if (rc) return rc;
-  if (!std::isfinite(ff)) return fail(SG_EINVAL, "right-hand side is not finite");
-  std::vector<double> al, be;
-  long its_in = 0;
-  int it = 0, status = SG_NOT_CONVERGED;
-  double rel = ff > 0.0 ? 1.0 : 0.0, pq_prev = 0.0;
-  if (ff == 0.0 || rel <= rtol) status = SG_OK;
-  for (; status == SG_NOT_CONVERGED && it < maxit; ++it) {
-    if (precond == SG_PC_HSC)
-      rc = hsc_apply(h, h->R, h->Z, inner_rtol, inner_maxit, its_in);
-    else if (precond == SG_PC_BGS)
-      rc = bgs_apply(h, h->R, h->Z, inner_rtol, inner_maxit, its_in);
-    else  // each column its own K(k_0) solve, so every column meets the inner tolerance
-      for (int a = 0; a < h->P && !rc; ++a)
-        rc = range_solve(h, 1, 0, 1, h->R + a * h->n, h->Z + a * h->n, inner_rtol, inner_maxit, its_in);
-    if (rc) return rc;
-    if (it == 0) {
-      sgk::launch_logn_axpby(nP, 1.0, h->Z, 0.0, h->Pv, 0, nullptr, 0, s);
-    } else {
-      double zq = 0.0;
-      if ((rc = dotp(h, h->Z, h->Q, nP, zq))) return rc;
-      const double beta = -zq / pq_prev;
-      be.push_back(beta);
-      sgk::launch_logn_axpby(nP, 1.0, h->Z, beta, h->Pv, 0, nullptr, 0, s);
-    }
-    sgk::launch_logn_matvec(h->rptr, h->rcol, h->rslot, h->C, h->Pv, h->n_e, h->n, h->P, h->Q, s);
-    double pq = 0.0, pr = 0.0;
-    if ((rc = dotp(h, h->Pv, h->Q, nP, pq))) return rc;
-    if (!(pq > 0.0) || !std::isfinite(pq)) {
-      status = SG_BREAKDOWN;
-      break;
-    }
-    if ((rc = dotp(h, h->Pv, h->R, nP, pr))) return rc;
-    const double alpha = pr / pq;
-    al.push_back(alpha);
-    sgk::launch_logn_axpby(nP, alpha, h->Pv, 1.0, U, 0, nullptr, 0, s);
-    sgk::launch_logn_axpby(nP, -alpha, h->Q, 1.0, h->R, 0, nullptr, 0, s);
-    pq_prev = pq;
-    if ((rc = dotp(h, h->R, h->R, nP, rr))) return rc;
-    rel = std::sqrt(rr / ff);
-    if (!std::isfinite(rel)) {
-      status = SG_BREAKDOWN;
-      ++it;
-      break;
-    }
-    if (rel <= rtol) {
-      status = SG_OK;
-      ++it;
-      break;
-    }
+  // a device too busy to run a block solve's blocks together: once more without those
+  bool expired = false;
+  h->one_launch = true;
+  int rc = solve_fcg(h, precond, F, U, rtol, maxit, inner_rtol, inner_maxit, outer_it, inner_it, relres, kappa, expired);
+  if (expired) {
+    h->one_launch = false;
+    rc = solve_fcg(h, precond, F, U, rtol, maxit, inner_rtol, inner_maxit, outer_it, inner_it, relres, kappa, expired);
   }
-  SG_HIP(hipStreamSynchronize(s));
-  if (outer_it) *outer_it = it;
-  if (inner_it) *inner_it = its_in;
-  if (relres) *relres = rel;
-  if (kappa) *kappa = al.empty() ? 1.0 : sgh::lanczos_kappa(al, be);
-  if (status == SG_NOT_CONVERGED) return fail(SG_NOT_CONVERGED, "outer iteration did not converge");
-  if (status == SG_BREAKDOWN) return fail(SG_BREAKDOWN, "breakdown: non-positive or non-finite curvature");
-  return SG_OK;
+  return rc;
 }
 
 void sg_logn_destroy(sg_logn_handle h) { delete h; }
