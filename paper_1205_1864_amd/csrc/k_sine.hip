@@ -378,6 +378,22 @@ __global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab,
 // Iteration
 // ---------------------------------------------------------------------------
 
+// Half sums of two values at once: lanes 0..31 get a of lanes l and l + 32, lanes
+// 32..63 the same of b (fold32); or rows 0 and 2 of a, rows 1 and 3 of b (fold16).
+// Seven adds sum four values over a wave, against 24 for one after the other.
+__device__ __forceinline__ double fold32(double a, double b) {
+  const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+  const auto lo = __builtin_amdgcn_permlane32_swap(ua.x, ub.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(ua.y, ub.y, false, false);
+  return __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) + __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
+}
+__device__ __forceinline__ double fold16(double a, double b) {
+  const uint2 ua = __builtin_bit_cast(uint2, a), ub = __builtin_bit_cast(uint2, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap(ua.x, ub.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(ua.y, ub.y, false, false);
+  return __builtin_bit_cast(double, make_uint2(lo[0], hi[0])) + __builtin_bit_cast(double, make_uint2(lo[1], hi[1]));
+}
+
 // Sums over a column: the block's threads, then the blocks of its group (in
 // a fixed order), the same bits in every thread of the group. A group
 // of one block needs its own barrier only. Otherwise the blocks exchange their
@@ -399,62 +415,61 @@ struct ColumnSums {
   __device__ unsigned long long* slot(unsigned e, int k) const { return ex + ((long)(e % 3) * groups + k) * kSumWidth; }
 
   __device__ void sum(double (&v)[kSumWidth]) {
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = lane >> 4;
     double (*buf)[kSumWidth] = red[epoch & 1];
-#pragma unroll
-    for (int i = 0; i < kSumWidth; ++i) v[i] = wave_sum(v[i]);
-    // all four before the branch (sunk past it, they would keep every slot's terms alive)
-    asm volatile("" ::"v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
-    if (lane == 0)
-#pragma unroll
-      for (int i = 0; i < kSumWidth; ++i) buf[wv][i] = v[i];
-    __syncthreads();
-    // lane 4 w + i (and lane 32 + 4 w + i) holds sum i of wave w
-    double t = buf[(lane >> 2) & 7][lane & 3];
+    // row i of the lanes ends up with sum i of the wave
+    double t = fold16(fold32(v[0], v[2]), fold32(v[1], v[3]));
     t += dpp_f64<0x128>(t);  // row_ror:8
     t += dpp_f64<0x124>(t);  // row_ror:4
+    t += dpp_f64<0x122>(t);  // row_ror:2
+    t += dpp_f64<0x121>(t);  // row_ror:1
+    // before the branch (sunk past it, the adds would keep every slot's terms alive)
+    asm volatile("" ::"v"(t));
+    if ((lane & 15) == 0) buf[wv][row] = t;
+    __syncthreads();
+    // lane w (and w + 8) of row i holds sum i of wave w
+    t = buf[lane & 7][row];
+    t += dpp_f64<0x124>(t);
+    t += dpp_f64<0x122>(t);
+    t += dpp_f64<0x121>(t);
     if (groups == 1) {
 #pragma unroll
-      for (int i = 0; i < kSumWidth; ++i) v[i] = lane_f64(t, i) + lane_f64(t, 16 + i);
+      for (int i = 0; i < kSumWidth; ++i) v[i] = lane_f64(t, 16 * i);
       ++epoch;
       return;
     }
     double (*out)[kSumWidth] = all + (epoch & 1);
     if (wv == 0) {
-      // lane i < 4 publishes sum i; then lanes read the group's places, 64 at a time
-      t += __shfl_xor(t, 16);
-      if (lane < kSumWidth) {
+      // row i publishes sum i; then its lanes read the places of 16 blocks at a time
+      if ((lane & 15) == 0) {
         __builtin_amdgcn_s_waitcnt(0);  // this lane's clearing store of the last exchange is done
-        agent_store(slot(epoch, g) + lane, publishable(t));
+        agent_store(slot(epoch, g) + row, publishable(t));
       }
       double s = 0.0;
       int ok = dead ? 0 : 1;
-      const unsigned long long* src = slot(epoch, 0);
-      for (int k0 = 0; k0 < groups * kSumWidth; k0 += 64) {
-        const int k = k0 + lane;
+      for (int k0 = 0; k0 < groups; k0 += 16) {
+        const int k = k0 + (lane & 15);
         unsigned long long bits = 0;
-        if (k < groups * kSumWidth) {
+        if (k < groups) {
+          const unsigned long long* src = slot(epoch, k) + row;
           long spins = 0;
-          while ((bits = agent_load(src + k)) == kEmpty && ok) {
+          while ((bits = agent_load(src)) == kEmpty && ok) {
             __builtin_amdgcn_s_sleep(1);
             if (++spins > kSpinLimit) ok = 0;
           }
         }
-        // lane 4 k + i holds sum i of block k: add the four blocks of each row of lanes, then the rows
         double val = __longlong_as_double((long long)bits);
-        val += dpp_f64<0x128>(val);  // row_ror:8
-        val += dpp_f64<0x124>(val);  // row_ror:4
-        if (groups > 4) {
-          val += __shfl_xor(val, 16);
-          val += __shfl_xor(val, 32);
-        }
+        val += dpp_f64<0x128>(val);
+        val += dpp_f64<0x124>(val);
+        val += dpp_f64<0x122>(val);
+        val += dpp_f64<0x121>(val);
         s += val;
       }
       ok = __all(ok);
       if (!ok && lane == 0) atomicExch(status, 1);
-      if (lane < kSumWidth) {
-        (*out)[lane] = s;
-        if (epoch > 0) agent_store(slot(epoch + 2, g) + lane, kEmpty);  // the place of exchange epoch - 1
+      if ((lane & 15) == 0) {
+        (*out)[row] = s;
+        if (epoch > 0) agent_store(slot(epoch + 2, g) + row, kEmpty);  // the place of exchange epoch - 1
       }
       if (lane == 0) *sflag = ok;
     }
@@ -469,26 +484,32 @@ struct ColumnSums {
 // One column at a time per group of blocks. Every slot keeps, for its pair of
 // modes, rho = the residual polynomial and phi = the direction polynomial at
 // the pair's eigenvalue (r = rho r_0, p = pi phi r_0 with pi the factor of the
-// preconditioner), and xi = sum alpha phi, the solution polynomial. With the
-// weight w = the sum of the pair's r_0^2
+// preconditioner). With the weight w = the sum of the pair's r_0^2
 //   r.z = sum v rho^2,  r.r = sum v rho^2 / pi,  p.q = sum v t phi^2,
 // v = pi w and t the eigenvalue of M K_0: one multiple of r_0 per pair stands
 // for all vectors of the iteration. p.q of the next direction p' = z + beta p is
 // z.K z + 2 beta z.K p + beta^2 p.q, so a single pass over the slots makes an
 // iteration (its rounding error is that of the three terms, at most cond(M K_0)
 // times p'.q'). All of a block's slots stay in registers (1 / pi and, beyond 11
-// slots a thread, t in LDS). Slots without a mode have v = 0 and t = 0.
-// Bound by the chain of an iteration: about 0.6 us of arithmetic on 18 slots a
-// thread and 1.8 us for the sums across the group (255^2: four blocks a column,
-// 2.4 us an iteration; the 220 columns of a large launch go through 64 groups in
-// four turns, 10.6 us per iteration of all). With one block a column, whose 68
-// slots a thread stream v, t and 1 / pi, an iteration took 15.8 us for one column
-// (cache bandwidth of one compute unit) and 23.4 us for 220.
+// slots a thread, what of t fits in LDS). Slots without a mode have v = 0 and t = 0.
+// Bound by the chain of an iteration: the arithmetic (about 0.8 us on 23 slots a
+// thread), the sums over the block (0.3 us) and across the group (1.2 us), so a
+// launch of many columns is faster the fewer blocks a column takes: as many slots
+// as the registers hold, without a solution vector (x follows from rho). 255^2,
+// three blocks of 23 slots a thread: 2.4 us an iteration; the 220 columns of a large
+// launch go through 85 groups in three turns, 7.2 us per iteration of all (10.4 us
+// with xi = sum alpha phi in registers too, 18 slots and four blocks a column; 23.4
+// us with one block a column that streams v, t and 1 / pi). 511^2, 120 columns:
+// 13.7 us, ten blocks of 27 slots (22.9 us, fifteen of 18).
 // RAGGED: the listed columns of several problems; those whose tables have other
 // slot and block counts than this launch are left to the launches for theirs.
+constexpr int sine_t_regs(int nr) {
+  constexpr int arrays = 39;  // of a value per thread, 156 KB
+  return nr <= 11 ? nr : 2 * nr > arrays ? 2 * nr - arrays : 0;
+}
 template <typename T, int NR, bool RAGGED>
 __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A, SineRagged<T> C, int ngroups) {
-  constexpr bool TREG = NR <= 11;
+  constexpr int TR = sine_t_regs(NR);  // slots whose t is in registers
   extern __shared__ unsigned char smem[];
   __shared__ double red[2][kSineThreads / 64][kSumWidth], all[2][kSumWidth];
   __shared__ int sflag;
@@ -505,14 +526,11 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
     __syncthreads();
   }
   const int group = place_ / G, g = place_ - group * G;
-  const long sbase = (long)g * NR * kSineThreads;  // this block's first slot
-  const int lane = tid & 63, w0 = __builtin_amdgcn_readfirstlane(tid >> 6) * NR;
+  const int sbase = g * NR * kSineThreads;  // this block's first slot
+  const int lane_ = tid & 63, w0 = __builtin_amdgcn_readfirstlane(tid >> 6) * NR;
   int nx = A.tab.nx;
-  const int4* tiles = A.tab.tiles + sbase / 256;
-  const double* tt = A.tab.t + sbase + w0 * 64 + lane;  // element e at 64 e
-  const double* ip = A.tab.ipi + sbase + w0 * 64 + lane;
-  // row and column of element e (its 64 slots are a quarter of a tile)
-  auto place = [&](int e, int& a, int& b) { return slot_place(tiles[(w0 + e) >> 2], ((w0 + e) & 3) * 64 + lane, a, b); };
+  const int4* tiles;
+  const double *tt, *ip;
   double* lds = reinterpret_cast<double*>(smem) + tid;
   ColumnSums cs{red, all, reinterpret_cast<unsigned long long*>(A.sc.part) + (long)group * G * 3 * kSumWidth,
                 A.sc.status, &sflag, G, g, 0u, false};
@@ -520,17 +538,26 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
   for (int c = group; c < ncols; c += ngroups) {
     T* s = A.s + (long)c * A.n;
     const T* s0 = A.s0 + (long)c * A.n;
+    int sb = sbase, lane = lane_;
+    asm volatile("" : "+s"(sb), "+v"(lane));  // no address below is kept from one column to the next
+    tiles = A.tab.tiles + sb / 256;
+    tt = A.tab.t + sb + w0 * 64 + lane;  // element e at 64 e
+    ip = A.tab.ipi + sb + w0 * 64 + lane;
     if constexpr (RAGGED) {
       const int o = ld_uniform(C.cols.act, c);
       const SineTables<T>& tab = C.tabs[ld_uniform(C.cols.prob, o)];
       if (tab.ept != NR || tab.groups != G) continue;
       nx = tab.nx;
-      tiles = tab.tiles + sbase / 256;
-      tt = tab.t + sbase + w0 * 64 + lane;
-      ip = tab.ipi + sbase + w0 * 64 + lane;
+      tiles = tab.tiles + sb / 256;
+      tt = tab.t + sb + w0 * 64 + lane;
+      ip = tab.ipi + sb + w0 * 64 + lane;
       s = C.column(COL_S, o);
       s0 = C.column(COL_S0, o);
     }
+    // row and column of element e (its 64 slots are a quarter of a tile)
+    auto place = [&](int e, int& a, int& b) {
+      return slot_place(tiles[(w0 + e) >> 2], ((w0 + e) & 3) * 64 + lane, a, b);
+    };
     // ---- start: weights, b.b, r.r, r.z, z.K z (warm: r = b - K_0 x in place)
     double sums[kSumWidth] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 2
@@ -560,17 +587,16 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
       }
       lds[e * kSineThreads] = v;
     }
-    double rho[NR], phi[NR], xi[NR], rv[NR], rt[TREG ? NR : 1];
+    double rho[NR], phi[NR], rv[NR], rt[TR > 0 ? TR : 1];
 #pragma unroll
     for (int e = 0; e < NR; ++e) {
       if (e % 4 == 0) __builtin_amdgcn_sched_barrier(0);
       rv[e] = lds[e * kSineThreads];
       rho[e] = 1.0;  // v = t = 0 where there is no mode
       phi[e] = 0.0;
-      xi[e] = 0.0;
       lds[e * kSineThreads] = ip[64 * e];
-      if constexpr (TREG) rt[e] = tt[64 * e];
-      else lds[(NR + e) * kSineThreads] = tt[64 * e];
+      if (e < TR) rt[e < TR ? e : 0] = tt[64 * e];
+      else lds[(NR - TR + e) * kSineThreads] = tt[64 * e];
     }
     cs.sum(sums);
     const double bb = sums[0];
@@ -584,10 +610,9 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
       double q[kSumWidth] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int e = 0; e < NR; ++e) {
-        if (e % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // the LDS reads of four slots at a time
-        const double iv = lds[e * kSineThreads], tv = TREG ? rt[TREG ? e : 0] : lds[(NR + e) * kSineThreads];
+        if (e % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // the LDS reads of two slots at a time
+        const double iv = lds[e * kSineThreads], tv = e < TR ? rt[e < TR ? e : 0] : lds[(NR - TR + e) * kSineThreads];
         phi[e] = fma(beta, phi[e], rho[e]);
-        xi[e] = fma(alpha, phi[e], xi[e]);
         rho[e] = fma(-alpha * phi[e], tv, rho[e]);
         const double vr = rv[e] * rho[e], z = vr * rho[e];
         q[1] += z;
@@ -602,15 +627,16 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
       rz = q[1];
     }
     if (tid == 0 && g == 0) A.sc.iters[c] = it;
-    // ---- solution: x = x_0 + pi xi r_0 (a zero right-hand side gives 0 also from a warm start)
+    // ---- solution: x = x_0 + K_0^-1 (r_0 - r) = x_0 + (1 - rho) / (t / pi) r_0, to the rounding
+    // of x's exact value (a zero right-hand side gives 0 also from a warm start)
     const bool guess = A.warm && bb != 0.0;
 #pragma unroll
-    for (int e = 0; e < NR; ++e) lds[e * kSineThreads] = xi[e];
+    for (int e = 0; e < NR; ++e) lds[e * kSineThreads] = 1.0 - rho[e];
 #pragma unroll 2
     for (int e = 0; e < NR; ++e) {
       int a, b;
       if (!place(e, a, b)) continue;
-      const double m = lds[e * kSineThreads] / ip[64 * e];
+      const double m = lds[e * kSineThreads] / (tt[64 * e] * ip[64 * e]);
       const long i1 = (long)a * nx + b, i2 = (long)b * nx + a;
       double x1 = guess ? (double)s0[i1] : 0.0, x2 = guess ? (double)s0[i2] : 0.0;
       if (it > 0) {
@@ -678,7 +704,7 @@ hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from
 template <typename T, bool RAGGED>
 hipError_t pcg(const SineArgs<T>& A, const SineRagged<T>& C, int ngroups, hipStream_t s) {
   auto launch = [&](auto kfn, int nr) {
-    const size_t sm = sizeof(double) * kSineThreads * (nr <= 11 ? nr : 2 * nr);
+    const size_t sm = sizeof(double) * kSineThreads * (2 * nr - sine_t_regs(nr));
     const hipError_t e = allow_lds(kfn, sm);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kfn, dim3((unsigned)(ngroups * A.tab.groups)), dim3(kSineThreads), sm, s, A, C, ngroups);
@@ -691,6 +717,8 @@ hipError_t pcg(const SineArgs<T>& A, const SineRagged<T>& C, int ngroups, hipStr
     case 11: return launch(sine_pcg_kernel<T, 11, RAGGED>, 11);
     case 14: return launch(sine_pcg_kernel<T, 14, RAGGED>, 14);
     case 18: return launch(sine_pcg_kernel<T, 18, RAGGED>, 18);
+    case 23: return launch(sine_pcg_kernel<T, 23, RAGGED>, 23);
+    case 27: return launch(sine_pcg_kernel<T, 27, RAGGED>, 27);
   }
   return hipErrorInvalidValue;
 }

@@ -290,7 +290,7 @@ size_t pcg_scratch_bytes(int ncols, int ntiles);
 // tiles of the array with a <= b (row index a, column index b), 256 slots a tile.
 constexpr int kSineMaxNx = 1024;    // longest transform (rows of both parities in LDS)
 constexpr int kSineThreads = 512;   // threads per block of the iteration kernel
-constexpr int kSineSlots = 18;      // most slots per thread (their state stays in registers)
+constexpr int kSineSlots = 27;      // most slots per thread (their state stays in registers)
 // Factors per transform length: packs of the sine matrices in the order the
 // matrix instructions read them (pack[p][tile][step][lane], parity p, 16 x 4
 // entries per step), and per slot t = eigenvalue of M K_0 and 1 / (factor of M).
@@ -320,7 +320,7 @@ inline SineSizes sine_sizes(int nx) {
   const long per = (tiles * 256 + kSineThreads - 1) / kSineThreads;
   z.groups = (int)((per + kSineSlots - 1) / kSineSlots);
   z.ept = (int)((per + z.groups - 1) / z.groups);
-  for (int k : {2, 5, 8, 11, 14, kSineSlots})  // the counts of the compiled kernels (empty slots hold no mode)
+  for (int k : {2, 5, 8, 11, 14, 18, 23, kSineSlots})  // the counts of the compiled kernels (empty slots hold no mode)
     if (z.ept <= k) {
       z.ept = k;
       break;

@@ -17,10 +17,11 @@ def _solver(prob, **kw):
 
 
 # n_e and what changes there: the smallest grid; one and two 16-mode tiles per
-# parity (33 / 34); 3, 4 and 5 tiles (65, 97, 130), 5, 8, 14 and 18 slots per
-# thread; two blocks per column (130), four (256, 257: an even and an odd number
-# of modes per parity), five (258); transforms of more than 256 modes per parity (515)
-SIZES = [3, 4, 5, 32, 33, 34, 65, 66, 97, 130, 256, 257, 258, 515]
+# parity (33 / 34); 3, 4 and 5 tiles (65, 97, 130), 5, 8, 11 and 23 slots per
+# thread; two blocks per column (131, 200: 14 and 27 slots), three (256, 257: an even
+# and an odd number of modes per parity; 258), ten and twelve (512, 515: transforms
+# of up to and of more than 256 modes per parity)
+SIZES = [3, 4, 5, 32, 33, 34, 65, 66, 97, 130, 131, 200, 256, 257, 258, 512, 515]
 
 
 @pytest.mark.parametrize("prec,tol", [(64, 1e-11), (32, 2e-5)])
