@@ -3,15 +3,15 @@
 //
 // A solve is five launches: right-hand side -> [x pass] -> [y pass] -> spectral
 // right-hand side -> iteration -> spectral solution -> [y pass] -> [x pass].
-// A pass is a product with the sine matrix of each parity on folded data (FP64
-// or FP32 matrix instructions).
+// A pass is a product with sine matrices of a quarter (or half) of the length on
+// folded data (FP64 or FP32 matrix instructions).
 //
 // Why: on the grid an iteration of degree d sweeps a column d times with halos
 // and meets two column-wide synchronisations; here it is a dozen operations per
 // pair of modes on values that never leave the registers. Measured at 256^2,
 // degree 16, FP64: the 220 columns of the top level to 1e-4 (about 30
-// iterations) 13.5 ms on banded tiles, 0.95 ms here; the benchmark's whole solve
-// 230 -> 25 ms; 28 columns of 100^2 unknowns at degree 8 730 -> 149 us.
+// iterations) 13.5 ms on banded tiles, 0.63 ms here; the benchmark's whole solve
+// 230 -> 18.5 ms; 28 columns of 100^2 unknowns at degree 8 730 -> 118 us.
 #include <algorithm>
 
 #include "sg_internal.h"
@@ -48,36 +48,161 @@ struct Mac<float> {
   __device__ static __forceinline__ int row(int lane, int r) { return 4 * (lane >> 4) + r; }
 };
 
+// Lengths of the products of a transform over n_e = nx + 1 intervals, in their
+// order: two (odd and even wave numbers), or four (H = n_e / 2):
+//   0: odd k at odd places, k < ceil(H / 2)    1: odd k at even places
+//   2: k = 2, 6, 10, ..                         3: k = 4, 8, 12, ..
+struct Fold {
+  int N, H, h1, ho, he;
+  bool four;
+  __host__ __device__ Fold(int nx, int parts)
+      : N(nx + 1), H(N / 2), h1(H / 2), ho((nx + 1) / 2), he(nx / 2), four(parts == 4) {}
+  __host__ __device__ int len(int p) const {
+    if (!four) return p ? he : ho;
+    return p == 0 ? H - h1 : p == 3 ? H - h1 - 1 : h1;
+  }
+  // space index (from 1) and wave number behind entry (j, k) of part p
+  __device__ int place(int p, int j) const { return !four || p >= 2 ? j + 1 : 2 * j + 1 + p; }
+  __device__ int wave(int p, int k) const {
+    if (!four) return 2 * k + 1 + p;
+    return p < 2 ? 2 * k + 1 : 4 * k + 2 * (p - 1);
+  }
+  // wave number of spectral index a
+  __device__ int wave_number(int a) const {
+    if (a < ho) return 2 * a + 1;
+    if (!four) return 2 * (a - ho) + 2;
+    return a - H < h1 ? wave(2, a - H) : wave(3, a - H - h1);
+  }
+  // items of the input, up to four entries each
+  __host__ __device__ int items(bool inv) const { return !four ? (ho + 1) / 2 : inv ? H - h1 : h1; }
+  // entries (from 0) of item i; those that the item does not have repeat others
+  template <bool INV>
+  __device__ __forceinline__ void entries(int i, int (&e)[4]) const {
+    if (!four) {
+      const int m = min(i + (ho + 1) / 2, ho - 1);
+      e[0] = i;
+      e[1] = INV ? min(ho + i, N - 2) : N - 2 - i;
+      e[2] = m;
+      e[3] = INV ? min(ho + m, N - 2) : N - 2 - m;
+    } else if (INV) {
+      e[0] = i;
+      e[1] = H - 1 - i;
+      e[2] = H + i;
+      e[3] = min(H + h1 + i, N - 2);
+    } else {
+      e[0] = i;
+      e[1] = N - 2 - i;
+      e[2] = H - 2 - i;
+      e[3] = H + i;
+    }
+  }
+  // item i with its entries' values x into the parts; get(e) for the entry in the middle
+  template <bool INV, typename T, typename G, typename P>
+  __device__ __forceinline__ void fold(int i, const T (&x)[4], G get, P put) const {
+    if (!four) {
+      auto two = [&](int k, T u, T v) {
+        put(0, k, INV || k >= he ? u : u + v);
+        if (k < he) put(1, k, INV ? v : u - v);
+      };
+      two(i, x[0], x[1]);
+      if (i + (ho + 1) / 2 < ho) two(i + (ho + 1) / 2, x[2], x[3]);
+    } else if (INV) {
+      if (i < h1) {
+        put(0, i, x[0] + x[1]);
+        put(1, i, x[0] - x[1]);
+        put(2, i, x[2]);
+      } else {
+        put(0, i, x[0]);
+      }
+      if (i < H - h1 - 1) put(3, i, x[3]);
+    } else {
+      const int j = i + 1, m = H - j;  // places
+      const T v = x[0] - x[1];
+      put(1 - (j & 1), i >> 1, x[0] + x[1]);
+      if (m == j) {
+        put(2, i, v);
+      } else {
+        const T w = x[2] - x[3];
+        put(1 - (m & 1), (m - 1) >> 1, x[2] + x[3]);
+        put(2, i, v + w);
+        put(3, i, v - w);
+      }
+      if (j == h1) put(1 - (H & 1), (H - 1) >> 1, get(H - 1));
+    }
+  }
+  // the entries of the result that item i's places in the parts, get(p, k), make up
+  // (the items of the opposite direction's input)
+  template <bool INV, typename G, typename P>
+  __device__ __forceinline__ void unfold(int i, G get, P put) const {
+    if (!four) {
+      auto two = [&](int k) {
+        const auto u = get(0, k);
+        if (k >= he) {
+          put(k, u);
+        } else {
+          const auto v = get(1, k);
+          put(k, INV ? u + v : u);
+          put(INV ? N - 2 - k : ho + k, INV ? u - v : v);
+        }
+      };
+      two(i);
+      if (i + (ho + 1) / 2 < ho) two(i + (ho + 1) / 2);
+    } else if (!INV) {
+      const auto u = get(0, i);
+      if (i < h1) {
+        const auto v = get(1, i);
+        put(i, u + v);
+        put(H - 1 - i, u - v);
+        put(H + i, get(2, i));
+      } else {
+        put(i, u);
+      }
+      if (i < H - h1 - 1) put(H + h1 + i, get(3, i));
+    } else {
+      const int j = i + 1, m = H - j;  // places
+      const auto u = get(1 - (j & 1), i >> 1), p = get(2, i);
+      if (m == j) {
+        put(i, u + p);
+        put(N - 2 - i, u - p);
+      } else {
+        const auto q = get(3, i), t = get(1 - (m & 1), (m - 1) >> 1);
+        const auto v = p + q, w = p - q;
+        put(i, u + v);
+        put(N - 2 - i, u - v);
+        put(m - 1, t + w);
+        put(H + i, t - w);
+      }
+      if (j == h1) put(H - 1, get(1 - (H & 1), (H - 1) >> 1));
+    }
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Tables
 // ---------------------------------------------------------------------------
 
-// Wave number of spectral index a.
-__device__ __forceinline__ int wave_number(int a, int ho) { return a < ho ? 2 * a + 1 : 2 * (a - ho) + 2; }
-
 template <typename T>
 __global__ void sine_pack_kernel(SineSizes z, int n_e, T* pack) {
-  // pack order: fwd[0], fwd[1], inv[0], inv[1]
-  const long total = 4 * z.pack;
-  const int steps = 4 * z.nt;
+  // pack order: forward parts, inverse parts
+  const long total = 2 * z.parts * z.pack;
+  const int steps = 4 * z.nq;
   const double scale = sqrt(2.0 / n_e);
+  const Fold F(z.nx, z.parts);
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < total; i += (long)gridDim.x * blockDim.x) {
     const int which = (int)(i / z.pack);
     const long o = i % z.pack;
     const int lane = (int)(o % 64);
     const int step = (int)(o / 64 % steps), tile = (int)(o / 64 / steps);
-    const int p = which & 1;
-    int j = 4 * step + lane / 16, k = 16 * tile + lane % 16;  // space index, index within the parity
-    if (which >= 2) {
+    const int p = which % z.parts;
+    int j = 4 * step + lane / 16, k = 16 * tile + lane % 16;  // place and wave within the part
+    if (which >= z.parts) {
       const int u = j;
       j = k;
       k = u;
     }
-    const int len = p ? z.he : z.ho;
     double v = 0.0;
-    if (j < len && k < len) {
-      const long kw = p ? 2 * k + 2 : 2 * k + 1;
-      const long m = (long)(j + 1) * kw % (2L * n_e);
+    if (j < F.len(p) && k < F.len(p)) {
+      const long m = (long)F.place(p, j) * F.wave(p, k) % (2L * n_e);
       v = scale * sinpi((double)m / n_e);
     }
     pack[i] = (T)v;
@@ -113,13 +238,14 @@ __device__ __forceinline__ bool slot_place(const int4& d, int in_tile, int& a, i
 }
 
 __global__ void sine_slot_kernel(SineSizes z, SineConsts c, const int4* tiles, double* t, double* ipi) {
+  const Fold F(z.nx, z.parts);
   for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < z.slots; i += (long)gridDim.x * blockDim.x) {
     int a, b;
     double tv = 0.0, iv = 0.0;
     if (slot_place(tiles[i / 256], (int)(i % 256), a, b)) {
       // eigenvalue of D^-1 K_0, (8 - 2 c_i - 2 c_j - 4 c_i c_j) / 8 with
       // c = cos(k pi / n_e), written through 1 - c = 2 sin^2(k pi / 2 n_e)
-      const double si = sinpi(wave_number(a, z.ho) / (2.0 * c.n_e)), sj = sinpi(wave_number(b, z.ho) / (2.0 * c.n_e));
+      const double si = sinpi(F.wave_number(a) / (2.0 * c.n_e)), sj = sinpi(F.wave_number(b) / (2.0 * c.n_e));
       const double ui = 2.0 * si * si, uj = 2.0 * sj * sj;
       const double mu = (6.0 * (ui + uj) - 4.0 * ui * uj) / 8.0;
       double S = 1.0 / c.diag, W = S * c.inv_theta, Z = W;
@@ -140,7 +266,7 @@ __global__ void sine_slot_kernel(SineSizes z, SineConsts c, const int4* tiles, d
 // Transform passes
 // ---------------------------------------------------------------------------
 
-constexpr int kPassThreads = 512;
+constexpr int kPassThreads = 1024;
 
 // What the first pass of a solve clears for the iteration that follows on the
 // stream: the exchange places and tickets of its groups, and the status word.
@@ -170,19 +296,116 @@ struct SineRagged {
   }
 };
 
-// Bound by the matrix cores and the loads that feed them: 220 columns of 255^2
-// take 120 to 130 us a pass in FP64 (29 TFLOP/s of folded products, 1.8 TB/s), 60
-// to 80 us in FP32. Two blocks fit a compute unit up to 128 modes per parity, so
-// that one block's loads run under the other's products.
+// Strip of block b of n: neighbours in an array go to one XCD (blocks are dealt to
+// the eight in turn), whose L2 then holds the cache lines that they share.
+__device__ __forceinline__ int xcd_block(int b, int n) {
+  const int x = b & 7, q = n >> 3, r = n & 7;
+  return x * q + min(x, r) + (b >> 3);
+}
+
+constexpr int kPassBatch = 4;  // most items of a strip per thread
+
+// The products of a block: item = a tile of 16 outputs of a pair of parts, IT items
+// per wave of NB operand tiles each. The sine matrices come from L2, W steps at
+// a time while the last W are multiplied; the first are on their way while the
+// block folds its data.
+template <typename T, int NB, int IT>
+struct Products {
+  using V = typename Mac<T>::V;
+  int nq, pairs, items, wave, nw;
+  const T* pack;
+  static constexpr int W = 4;
+  T w0[W], w1[W];
+
+  __device__ __forceinline__ Products(int parts, int nq_, const T* pk)
+      : nq(nq_),
+        pairs(parts / 2),
+        items(nq_ * (parts / 2)),
+        wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)),
+        nw(blockDim.x >> 6),
+        pack(pk) {
+    load(wave < items ? wave : 0, 0, threadIdx.x & 63, w0, w1);
+  }
+  __device__ __forceinline__ void load(int item, int chunk, int lane, T (&a)[W], T (&b)[W]) const {
+    const T* f = pack + ((2 * (item % pairs) * nq + item / pairs) * nq * 4 + chunk * W) * 64;
+    const T* g = f + nq * nq * 256;
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+      a[k] = f[64 * k + lane];
+      b[k] = g[64 * k + lane];
+    }
+  }
+  // `tile` multiplies operand tile i of a part at step k, `result` takes the
+  // products once every wave has read its operands
+  template <typename L, typename S>
+  __device__ __forceinline__ void run(L tile, S result) {
+    const int lane = threadIdx.x & 63;
+    V acc[IT][2][NB];
+#pragma unroll
+    for (int t = 0; t < IT; ++t)
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        acc[t][0][i] = V{0, 0, 0, 0};
+        acc[t][1][i] = V{0, 0, 0, 0};
+      }
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+      const int item = wave + t * nw;
+      if (item >= items) continue;
+      const int chunks = 4 / W * nq;
+      const int p = 2 * (item % pairs);
+      for (int c = 0; c < chunks; ++c) {
+        T n0[W], n1[W];
+        const bool last = c + 1 == chunks;
+        load(last && IT > 1 && item + nw < items ? item + nw : item, last ? 0 : c + 1, lane, n0, n1);
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+#pragma unroll
+          for (int i = 0; i < NB; ++i) {
+            acc[t][0][i] = tile(w0[k], p, i, W * c + k, acc[t][0][i]);
+            acc[t][1][i] = tile(w1[k], p + 1, i, W * c + k, acc[t][1][i]);
+          }
+#pragma unroll
+        for (int k = 0; k < W; ++k) {
+          w0[k] = n0[k];
+          w1[k] = n1[k];
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < IT; ++t) {
+      const int item = wave + t * nw;
+      if (item >= items) continue;
+      const int p = 2 * (item % pairs), ct = item / pairs;
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          result(p, ct, i, r, acc[t][0][i][r]);
+          result(p + 1, ct, i, r, acc[t][1][i][r]);
+        }
+    }
+    __syncthreads();
+  }
+};
+
+// The passes are bound by memory and the matrix cores in turn (a block's loads,
+// products and stores follow each other; two blocks fit a compute unit up to n_e =
+// 256, one above). 220 columns of 255^2: 62 us a pass in FP64 (3.7 TB/s; 44 us for a
+// copy, 28 us for the products alone), 35 us in FP32; 120 columns of 511^2: 245 us
+// (97 us and 122 us). With two products per transform, unfolding from the registers
+// and 128-byte stores it was 120 to 130, 60 to 80 and 610 us. A block's index
+// arithmetic counts: with one element per step of the unfolding loop 255^2 took 75
+// to 95 us. Blocks that load their next strip during the products gained nothing
+// (75 to 95 us): the table's entries, asked for after it, return after it.
 //
-// Pass along x: `rows` rows of nx values. Forward: a block folds R = 16 RT rows
-// into the parity parts in LDS and multiplies them by the sine matrices from
-// the right; inverse: it multiplies the two halves of a spectral row and
-// unfolds the results. A wave takes one 16-column tile of both parities, so
-// that the unfolding stays within a lane.
+// Pass along x: a block folds 16 RT rows of nx values into the parts in LDS,
+// multiplies them by the sine matrices from the right and unfolds the products,
+// which take the operands' place.
 // RAGGED: the launch covers columns of several problems, `strips` blocks each
 // (as many as the largest grid needs; the blocks past a column's rows end).
-template <typename T, bool INV, int RT, bool RAGGED>
+template <typename T, bool INV, int RT, int IT, bool RAGGED>
 __global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab, const T* in, T* out, long rows,
                                                               SineReset reset, SineRagged<T> C, int from, int to,
                                                               int strips) {
@@ -194,184 +417,148 @@ __global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab,
     for (int i = threadIdx.x; i < reset.ntickets; i += blockDim.x) reset.tickets[i] = 0u;
     if (threadIdx.x == 0) *reset.status = 0;
   }
-  long strip = blockIdx.x;
+  long strip = RAGGED ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
   if constexpr (RAGGED) {
     const int i = blockIdx.x / strips;
     if (i >= ld_uniform(C.cols.nact, 0)) return;
     const int o = ld_uniform(C.cols.act, i);
-    strip = blockIdx.x - i * strips;
+    strip -= (long)i * strips;
     tab = C.tabs[ld_uniform(C.cols.prob, o)];
     if (strip * 16 * RT >= tab.nx) return;
     rows = tab.nx;
     in = C.column(from, o);
     out = C.column(to, o);
   }
-  const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt, ld = hp + 4;
-  constexpr int R = 16 * RT;
-  T* Q = reinterpret_cast<T*>(smem);  // [2][R][ld]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int nx = tab.nx, parts = tab.parts, nq = tab.nq, hq = 16 * nq;
+  constexpr int R = 16 * RT, PAD = 16 / sizeof(T);  // rows of an operand fall into different LDS banks
+  const int ld = hq + PAD;
+  T* Q = reinterpret_cast<T*>(smem);  // [parts][R][ld], each part half the banks further
+  auto base = [&](int p) { return p * (R * ld + 128 / (int)sizeof(T)); };
+  const Fold F(nx, parts);
+  const int t = threadIdx.x, lane = t & 63;
+  // this thread's u-th place in (rows x items): as many lanes to a row as it has items, in powers of two
+  auto mine = [&](int items, int u, int& r, int& i) {
+    const int llog = items <= 8 ? 3 : items <= 16 ? 4 : items <= 32 ? 5 : 6;
+    const int rstep = blockDim.x >> llog, rper = max(1, R / rstep), chunk = u / rper;
+    r = (t >> llog) + (u - chunk * rper) * rstep;
+    i = (t & ((1 << llog) - 1)) + (chunk << llog);
+    return r < R && i < items;
+  };
   const long r0 = strip * R;
-  for (int r = wave; r < R; r += nw) {
-    const bool on = r0 + r < rows;
-    const T* src = in + (r0 + r) * nx;
-    for (int j = lane; j < hp; j += 64) {
-      T u = T(0), v = T(0);
-      if (INV) {
-        if (on && j < ho) u = src[j];
-        if (on && j < he) v = src[ho + j];
-      } else if (on && j < ho) {
-        u = src[j];
-        if (j < he) {
-          const T m = src[nx - 1 - j];
-          v = u - m;
-          u = u + m;
-        }
-      }
-      Q[r * ld + j] = u;
-      Q[(R + r) * ld + j] = v;
+  Products<T, RT, IT> products(parts, nq, INV ? tab.inv : tab.fwd);
+  {
+    T x[kPassBatch][4];
+    const int items = F.items(INV);
+    auto source = [&](int r) { return in + min(r0 + r, rows - 1) * nx; };  // rows past the end are not stored
+#pragma unroll
+    for (int u = 0; u < kPassBatch; ++u) {
+      int r, i, e[4];
+      if (!mine(items, u, r, i)) continue;
+      F.template entries<INV>(i, e);
+      const T* src = source(r);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[u][k] = src[e[k]];
+    }
+    for (int r = t >> 4; r < R; r += blockDim.x >> 4)
+      for (int p = 0; p < parts; ++p)
+        for (int j = F.len(p) + (t & 15); j < hq; j += 16) Q[base(p) + r * ld + j] = T(0);
+#pragma unroll
+    for (int u = 0; u < kPassBatch; ++u) {
+      int r, i;
+      if (!mine(items, u, r, i)) continue;
+      F.template fold<INV>(
+          i, x[u], [&](int m) { return source(r)[m]; }, [&](int p, int j, T v) { Q[base(p) + r * ld + j] = v; });
     }
   }
   __syncthreads();
-  const int steps = 4 * nt;
-  const T* pk0 = INV ? tab.inv[0] : tab.fwd[0];
-  const T* pk1 = INV ? tab.inv[1] : tab.fwd[1];
-  for (int ct = wave; ct < nt; ct += nw) {
-    V acc[2][RT];
+  const T* q = Q + (lane & 15) * ld + (lane >> 4);
+  products.run([&](T w, int p, int i, int k, V a) { return M::mac(q[base(p) + 16 * i * ld + 4 * k], w, a); },
+               [&](int p, int ct, int i, int r, T v) {
+                 Q[base(p) + (16 * i + M::row(lane, r)) * ld + 16 * ct + (lane & 15)] = v;
+               });
+  const int outs = F.items(!INV);
 #pragma unroll
-    for (int i = 0; i < RT; ++i) {
-      acc[0][i] = V{0, 0, 0, 0};
-      acc[1][i] = V{0, 0, 0, 0};
-    }
-    const T* f0 = pk0 + (long)ct * steps * 64 + lane;
-    const T* f1 = pk1 + (long)ct * steps * 64 + lane;
-    const T* q = Q + (lane & 15) * ld + (lane >> 4);
-#pragma unroll 4
-    for (int k = 0; k < steps; ++k) {
-      const T b0 = f0[64 * k], b1 = f1[64 * k];
-#pragma unroll
-      for (int i = 0; i < RT; ++i) {
-        acc[0][i] = M::mac(q[16 * i * ld + 4 * k], b0, acc[0][i]);
-        acc[1][i] = M::mac(q[(R + 16 * i) * ld + 4 * k], b1, acc[1][i]);
-      }
-    }
-    const int c = 16 * ct + (lane & 15);
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const long row = r0 + 16 * i + M::row(lane, r);
-        if (row >= rows) continue;
-        T* dst = out + row * nx;
-        const T u = acc[0][i][r], v = acc[1][i][r];
-        if (INV) {
-          if (c < he) {
-            dst[c] = u + v;
-            dst[nx - 1 - c] = u - v;
-          } else if (c < ho) {
-            dst[c] = u;
-          }
-        } else {
-          if (c < ho) dst[c] = u;
-          if (c < he) dst[ho + c] = v;
-        }
-      }
+  for (int u = 0; u < kPassBatch; ++u) {
+    int r, i;
+    if (!mine(outs, u, r, i) || r0 + r >= rows) continue;
+    T* dst = out + (r0 + r) * nx;
+    const T* g = Q + r * ld;
+    F.template unfold<INV>(
+        i, [&](int p, int k) { return g[base(p) + k]; }, [&](int e, T v) { dst[e] = v; });
   }
 }
 
 // Pass along y of one column's nx x nx array: a block takes CW = 16 CT array
-// columns, folds (forward) or splits (inverse) their rows into the parity parts
-// in LDS and multiplies by the sine matrices from the left. With 32 columns
-// the two halves of every other row are exchanged, so that the four rows of a
-// matrix operand fall into different LDS banks.
-template <typename T, bool INV, int CT, bool RAGGED>
+// columns, folds their rows into the parts in LDS, multiplies by the sine
+// matrices from the left and unfolds the products. With 32 columns the two halves
+// of every other row (pair of rows in FP32) are exchanged, so that the four rows
+// of a matrix operand fall into different LDS banks.
+template <typename T, bool INV, int CT, int IT, bool RAGGED>
 __global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab, const T* in, T* out, long n,
                                                               SineRagged<T> C, int from, int to, int strips) {
   using M = Mac<T>;
   using V = typename M::V;
   extern __shared__ unsigned char smem[];
-  const int col = blockIdx.x / strips;
-  const T* src = in + (long)col * n;
-  T* dst = out + (long)col * n;
+  int strip = RAGGED ? blockIdx.x : xcd_block(blockIdx.x, gridDim.x);
+  const int col = strip / strips;
+  strip -= col * strips;
   if constexpr (RAGGED) {
     if (col >= ld_uniform(C.cols.nact, 0)) return;
     const int o = ld_uniform(C.cols.act, col);
     tab = C.tabs[ld_uniform(C.cols.prob, o)];
-    if ((blockIdx.x - col * strips) * 16 * CT >= tab.nx) return;
-    src = C.column(from, o);
-    dst = C.column(to, o);
+    if (strip * 16 * CT >= tab.nx) return;
+    in = C.column(from, o);
+    out = C.column(to, o);
+  } else {
+    in += (long)col * n;
+    out += (long)col * n;
   }
-  const int nx = tab.nx, ho = tab.ho, he = tab.he, nt = tab.nt, hp = 16 * nt;
+  const int nx = tab.nx, parts = tab.parts, nq = tab.nq, hq = 16 * nq;
   constexpr int CW = 16 * CT;
-  T* Q = reinterpret_cast<T*>(smem);  // [2][hp][CW]
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  const int c0 = (blockIdx.x - col * strips) * CW;
-  auto place = [&](int j, int c) { return j * CW + (CT == 2 ? c ^ ((j & 1) << 4) : c); };
+  T* Q = reinterpret_cast<T*>(smem);  // [parts][hq][CW]
+  const Fold F(nx, parts);
+  constexpr int SH = sizeof(T) == 4 ? 1 : 0;
+  auto place = [&](int p, int j, int c) { return (p * hq + j) * CW + (CT == 2 ? c ^ (((j >> SH) & 1) << 4) : c); };
+  const int c = threadIdx.x % CW, l0 = threadIdx.x / CW, lstep = blockDim.x / CW, at = strip * CW + c;
+  const int lane = threadIdx.x & 63;
+  Products<T, CT, IT> products(parts, nq, INV ? tab.inv : tab.fwd);
   {
-    const int c = threadIdx.x % CW;
-    const bool on = c0 + c < nx;
-    for (int j = threadIdx.x / CW; j < hp; j += blockDim.x / CW) {
-      T u = T(0), v = T(0);
-      if (INV) {
-        if (on && j < ho) u = src[(long)j * nx + c0 + c];
-        if (on && j < he) v = src[(long)(ho + j) * nx + c0 + c];
-      } else if (on && j < ho) {
-        u = src[(long)j * nx + c0 + c];
-        if (j < he) {
-          const T m = src[(long)(nx - 1 - j) * nx + c0 + c];
-          v = u - m;
-          u = u + m;
-        }
-      }
-      Q[place(j, c)] = u;
-      Q[hp * CW + place(j, c)] = v;
+    T x[kPassBatch][4];
+    const int items = F.items(INV);
+    const T* src = in + min(at, nx - 1);  // columns past the end are not stored
+#pragma unroll
+    for (int u = 0; u < kPassBatch; ++u) {
+      const int i = l0 + u * lstep;
+      int e[4];
+      if (i >= items) continue;
+      F.template entries<INV>(i, e);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[u][k] = src[e[k] * nx];
+    }
+    for (int p = 0; p < parts; ++p)
+      for (int j = F.len(p) + l0; j < hq; j += lstep) Q[place(p, j, c)] = T(0);
+#pragma unroll
+    for (int u = 0; u < kPassBatch; ++u) {
+      const int i = l0 + u * lstep;
+      if (i >= items) continue;
+      F.template fold<INV>(
+          i, x[u], [&](int m) { return src[m * nx]; }, [&](int p, int j, T v) { Q[place(p, j, c)] = v; });
     }
   }
   __syncthreads();
-  const int steps = 4 * nt;
-  const T* pk0 = INV ? tab.inv[0] : tab.fwd[0];
-  const T* pk1 = INV ? tab.inv[1] : tab.fwd[1];
-  for (int rt = wave; rt < nt; rt += nw) {
-    V acc[2][CT];
+  products.run(
+      [&](T w, int p, int i, int k, V a) {
+        return M::mac(w, Q[place(p, 4 * k + (lane >> 4), 16 * i + (lane & 15))], a);
+      },
+      [&](int p, int rt, int i, int r, T v) { Q[place(p, 16 * rt + M::row(lane, r), 16 * i + (lane & 15))] = v; });
+  const int outs = F.items(!INV);
+  if (at < nx)
 #pragma unroll
-    for (int i = 0; i < CT; ++i) {
-      acc[0][i] = V{0, 0, 0, 0};
-      acc[1][i] = V{0, 0, 0, 0};
-    }
-    const T* f0 = pk0 + (long)rt * steps * 64 + lane;
-    const T* f1 = pk1 + (long)rt * steps * 64 + lane;
-#pragma unroll 4
-    for (int k = 0; k < steps; ++k) {
-      const T a0 = f0[64 * k], a1 = f1[64 * k];
-      const int j = 4 * k + (lane >> 4);
-#pragma unroll
-      for (int i = 0; i < CT; ++i) {
-        const int o = place(j, 16 * i + (lane & 15));
-        acc[0][i] = M::mac(a0, Q[o], acc[0][i]);
-        acc[1][i] = M::mac(a1, Q[hp * CW + o], acc[1][i]);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < CT; ++i) {
-      const int c = c0 + 16 * i + (lane & 15);
-      if (c >= nx) continue;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int j = 16 * rt + M::row(lane, r);
-        const T u = acc[0][i][r], v = acc[1][i][r];
-        if (INV) {
-          if (j < he) {
-            dst[(long)j * nx + c] = u + v;
-            dst[(long)(nx - 1 - j) * nx + c] = u - v;
-          } else if (j < ho) {
-            dst[(long)j * nx + c] = u;
-          }
-        } else {
-          if (j < ho) dst[(long)j * nx + c] = u;
-          if (j < he) dst[(long)(ho + j) * nx + c] = v;
-        }
-      }
-    }
-  }
+    for (int u = 0; u < kPassBatch; ++u)
+      if (l0 + u * lstep < outs)
+        F.template unfold<INV>(
+            l0 + u * lstep, [&](int p, int k) { return Q[place(p, k, c)]; },
+            [&](int e, T v) { out[e * nx + at] = v; });
 }
 
 // ---------------------------------------------------------------------------
@@ -661,44 +848,77 @@ const T* column_base(const SineArgs<T>& A, int which) {
   return which == COL_B ? A.b : which == COL_X ? A.x : which == COL_S ? A.s : which == COL_S0 ? A.s0 : A.w;
 }
 
+// Shape of a pass: `parts` x `nq` tiles, for a ragged launch bounds of every grid up
+// to the longest (two products take ceil(nx / 32) tiles, four at most as many in
+// each of two pairs, rounded up).
+struct PassShape {
+  int nq, parts, items;
+  template <typename T>
+  PassShape(const SineTables<T>& t, bool ragged, int nx) : nq(t.nq), parts(t.parts) {
+    if (ragged) {
+      const int nt = ((nx + 1) / 2 + 15) / 16;
+      nq = (nt + 1) / 2;
+      parts = 4;
+    }
+    items = nq * parts / 2;
+  }
+  int threads() const { return items <= 4 ? 256 : items <= 8 ? 512 : 1024; }
+  // the padding of rows along x is the larger one
+  size_t lds(size_t elem, int width) const { return parts * (elem * width * (16 * nq + 16 / elem) + 128); }
+};
+
+// Strips of 32 rows or columns, or of 16 where 32 would leave the device half empty
+// (28 columns of 100^2: 5 to 6 us a pass against 7 to 8; from half a device of strips
+// of 32 on, 45 columns of 127^2, both take 7 to 8) or do not fit in LDS (more than 16
+// items, two a wave).
+template <typename F1, typename F2, typename F3>
+hipError_t pass_variant(const PassShape& sh, long lines, int num_cu, F1 wide, F2 narrow, F3 longest) {
+  if (sh.items > 16) return longest(16);
+  return (lines + 31) / 32 <= num_cu / 2 ? narrow(16) : wide(32);
+}
+
 // One pass over every column: `nx` the longest transform, C the columns of a ragged launch.
 template <typename T, bool INV, bool RAGGED>
 hipError_t x_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, const SineReset& reset,
-                  hipStream_t s) {
-  const int nt = ((nx + 1) / 2 + 15) / 16, hp = 16 * nt;
+                  int num_cu, hipStream_t s) {
+  const PassShape sh(A.tab, RAGGED, nx);
   const long rows = (long)A.ncols * nx;
-  const int threads = 64 * std::min(8, nt);
   const T* in = RAGGED ? nullptr : column_base(A, from);
   T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
   auto launch = [&](auto kfn, int R) {
-    const size_t sm = sizeof(T) * 2 * R * (hp + 4);
+    const size_t sm = sh.lds(sizeof(T), R);
     const hipError_t e = allow_lds(kfn, sm);
     if (e != hipSuccess) return e;
     const int strips = (nx + R - 1) / R;
-    const long blocks = RAGGED ? (long)A.ncols * strips : (rows + R - 1) / R;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)blocks), dim3(threads), sm, s, A.tab, in, out, rows, reset, C, from, to,
-                       strips);
+    const unsigned blocks = RAGGED ? (unsigned)A.ncols * strips : (unsigned)((rows + R - 1) / R);
+    hipLaunchKernelGGL(kfn, dim3(blocks), dim3(sh.threads()), sm, s, A.tab, in, out, rows, reset, C, from,
+                       to, strips);
     return hipGetLastError();
   };
-  return hp <= 256 ? launch(sine_x_kernel<T, INV, 2, RAGGED>, 32) : launch(sine_x_kernel<T, INV, 1, RAGGED>, 16);
+  return pass_variant(
+      sh, rows, num_cu, [&](int R) { return launch(sine_x_kernel<T, INV, 2, 1, RAGGED>, R); },
+      [&](int R) { return launch(sine_x_kernel<T, INV, 1, 1, RAGGED>, R); },
+      [&](int R) { return launch(sine_x_kernel<T, INV, 1, 2, RAGGED>, R); });
 }
 
 template <typename T, bool INV, bool RAGGED>
-hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, hipStream_t s) {
-  const int nt = ((nx + 1) / 2 + 15) / 16, hp = 16 * nt;
-  const int threads = 64 * std::min(8, nt);
+hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, int num_cu, hipStream_t s) {
+  const PassShape sh(A.tab, RAGGED, nx);
   const T* in = RAGGED ? nullptr : column_base(A, from);
   T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
   auto launch = [&](auto kfn, int W) {
-    const size_t sm = sizeof(T) * 2 * hp * W;
+    const size_t sm = sh.lds(sizeof(T), W);
     const hipError_t e = allow_lds(kfn, sm);
     if (e != hipSuccess) return e;
     const int strips = (nx + W - 1) / W;
-    hipLaunchKernelGGL(kfn, dim3((unsigned)strips * A.ncols), dim3(threads), sm, s, A.tab, in, out, A.n, C, from, to,
-                       strips);
+    hipLaunchKernelGGL(kfn, dim3((unsigned)strips * A.ncols), dim3(sh.threads()), sm, s, A.tab, in, out, A.n, C, from,
+                       to, strips);
     return hipGetLastError();
   };
-  return hp <= 256 ? launch(sine_y_kernel<T, INV, 2, RAGGED>, 32) : launch(sine_y_kernel<T, INV, 1, RAGGED>, 16);
+  return pass_variant(
+      sh, (long)A.ncols * nx, num_cu, [&](int W) { return launch(sine_y_kernel<T, INV, 2, 1, RAGGED>, W); },
+      [&](int W) { return launch(sine_y_kernel<T, INV, 1, 1, RAGGED>, W); },
+      [&](int W) { return launch(sine_y_kernel<T, INV, 1, 2, RAGGED>, W); });
 }
 
 template <typename T, bool RAGGED>
@@ -730,21 +950,22 @@ int group_count(int ncols, int groups, int num_cu) {
 }
 
 template <typename T, bool RAGGED>
-hipError_t transform_in(const SineArgs<T>& A, const SineRagged<T>& C, int nx, const SineReset& reset, hipStream_t s) {
+hipError_t transform_in(const SineArgs<T>& A, const SineRagged<T>& C, int nx, const SineReset& reset, int num_cu,
+                        hipStream_t s) {
   hipError_t e = hipSuccess;
   if (A.warm) {
-    e = x_pass<T, false, RAGGED>(A, C, nx, COL_X, COL_W, SineReset{}, s);
-    if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S0, s);
+    e = x_pass<T, false, RAGGED>(A, C, nx, COL_X, COL_W, SineReset{}, num_cu, s);
+    if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S0, num_cu, s);
   }
-  if (e == hipSuccess) e = x_pass<T, false, RAGGED>(A, C, nx, COL_B, COL_W, reset, s);
-  if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S, s);
+  if (e == hipSuccess) e = x_pass<T, false, RAGGED>(A, C, nx, COL_B, COL_W, reset, num_cu, s);
+  if (e == hipSuccess) e = y_pass<T, false, RAGGED>(A, C, nx, COL_W, COL_S, num_cu, s);
   return e;
 }
 
 template <typename T, bool RAGGED>
-hipError_t transform_out(const SineArgs<T>& A, const SineRagged<T>& C, int nx, hipStream_t s) {
-  hipError_t e = y_pass<T, true, RAGGED>(A, C, nx, COL_S, COL_W, s);
-  if (e == hipSuccess) e = x_pass<T, true, RAGGED>(A, C, nx, COL_W, COL_X, SineReset{}, s);
+hipError_t transform_out(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int num_cu, hipStream_t s) {
+  hipError_t e = y_pass<T, true, RAGGED>(A, C, nx, COL_S, COL_W, num_cu, s);
+  if (e == hipSuccess) e = x_pass<T, true, RAGGED>(A, C, nx, COL_W, COL_X, SineReset{}, num_cu, s);
   return e;
 }
 
@@ -755,7 +976,7 @@ void launch_sine_tables(const SineSizes& z, const SineConsts& k, T* pack, int4* 
                         bool packs, hipStream_t s) {
   auto grid = [](long n) { return dim3((unsigned)std::min<long>((n + 255) / 256, 4096)); };
   if (packs) {
-    hipLaunchKernelGGL(sine_pack_kernel<T>, grid(4 * z.pack), dim3(256), 0, s, z, k.n_e, pack);
+    hipLaunchKernelGGL(sine_pack_kernel<T>, grid(2 * z.parts * z.pack), dim3(256), 0, s, z, k.n_e, pack);
     hipLaunchKernelGGL(sine_tile_kernel, grid(z.ntiles), dim3(256), 0, s, z, tiles);
   }
   hipLaunchKernelGGL(sine_slot_kernel, grid(z.slots), dim3(256), 0, s, z, k, tiles, t, ipi);
@@ -768,15 +989,15 @@ hipError_t launch_sine(const SineArgs<T>& A, int num_cu, hipStream_t s) {
   const SineSizes z = sine_sizes(t.nx);
   const int ngroups = group_count(A.ncols, t.groups, num_cu);
   if (t.nx < 1 || t.nx > kSineMaxNx || A.n != (long)t.nx * t.nx || t.ept != z.ept || t.groups != z.groups ||
-      t.nt != z.nt || ngroups < 1)
+      t.parts != z.parts || t.nq != z.nq || ngroups < 1)
     return hipErrorInvalidValue;
   const SineReset reset{reinterpret_cast<unsigned long long*>(A.sc.part),
                         t.groups == 1 ? 0 : ngroups * t.groups * 3 * kSumWidth, A.sc.arrivals, t.groups == 1 ? 0 : 1,
                         A.sc.status};
   const SineRagged<T> none{};
-  hipError_t e = transform_in<T, false>(A, none, t.nx, reset, s);
+  hipError_t e = transform_in<T, false>(A, none, t.nx, reset, num_cu, s);
   if (e == hipSuccess) e = pcg<T, false>(A, none, ngroups, s);
-  if (e == hipSuccess) e = transform_out<T, false>(A, none, t.nx, s);
+  if (e == hipSuccess) e = transform_out<T, false>(A, none, t.nx, num_cu, s);
   return e;
 }
 
@@ -792,7 +1013,7 @@ hipError_t launch_sine_ragged(const SineArgs<T>& args, const PcgCols<T>& cols, c
   constexpr int share = kSineMaxBlocks * 3 * kSumWidth;
   const SineReset reset{reinterpret_cast<unsigned long long*>(args.sc.part), nclasses * share, args.sc.arrivals,
                         nclasses, args.sc.status};
-  hipError_t e = transform_in<T, true>(args, C, max_nx, reset, s);
+  hipError_t e = transform_in<T, true>(args, C, max_nx, reset, num_cu, s);
   for (int k = 0; k < nclasses && e == hipSuccess; ++k) {
     SineArgs<T> a = args;
     a.tab.ept = classes[k].ept;
@@ -803,7 +1024,7 @@ hipError_t launch_sine_ragged(const SineArgs<T>& args, const PcgCols<T>& cols, c
     if (ngroups < 1) return hipErrorInvalidValue;
     e = pcg<T, true>(a, C, ngroups, s);
   }
-  if (e == hipSuccess) e = transform_out<T, true>(args, C, max_nx, s);
+  if (e == hipSuccess) e = transform_out<T, true>(args, C, max_nx, num_cu, s);
   return e;
 }
 

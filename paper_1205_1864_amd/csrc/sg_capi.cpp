@@ -166,7 +166,7 @@ void make_plan(const sg_problem* pr, const sg_opts* op, Plan& pl) {
   for (int i = 0; i < 6; ++i) pl.o_pcg[i] = L.take(isz * pl.n * (long)pl.maxcols);
   const sgk::SineSizes sz = sgk::sine_sizes(std::min(pl.nx, sgk::kSineMaxNx));
   const bool sine = pl.nx <= sgk::kSineMaxNx;
-  pl.o_sine_pack = L.take(sine ? isz * 4 * sz.pack : 0);
+  pl.o_sine_pack = L.take(sine ? isz * 2 * sz.parts * sz.pack : 0);
   pl.o_sine_tiles = L.take(sine ? sizeof(int4) * sz.ntiles : 0);
   pl.o_sine_t = L.take(sine ? sizeof(double) * sz.slots : 0);
   pl.o_sine_ipi = L.take(sine ? sizeof(double) * sz.slots : 0);
@@ -394,7 +394,7 @@ template <typename T>
 sgk::SineTables<T> sine_tables(const sg_ctx* h) {
   const sgk::SineSizes& z = h->sine;
   const T* pk = (const T*)h->sine_pack;
-  return {z.nx, z.ho, z.he, z.nt, z.ept, z.groups, {pk, pk + z.pack}, {pk + 2 * z.pack, pk + 3 * z.pack},
+  return {z.nx, z.ho, z.he, z.parts, z.nq, z.ept, z.groups, pk, pk + z.parts * z.pack,
           h->sine_tiles, h->sine_t, h->sine_ipi};
 }
 template sgk::SineTables<double> sine_tables<double>(const sg_ctx*);

@@ -284,30 +284,34 @@ size_t pcg_scratch_bytes(int ncols, int ntiles);
 // [ky'][kx'] whose index k' lists the odd wave numbers 1, 3, .. (ho of them)
 // before the even ones 2, 4, .. (he): a sine of odd k is even about the middle
 // of the interval and one of even k odd, so a transform of length nx splits
-// into two products of half the length on the folded data.
+// into two products of half the length on the folded data. With n_e = 2 H each of
+// the two splits once more about H / 2 (a sine of odd k at odd and at even places,
+// a sine of even k = 2 k' by the parity of k'), into four products of a quarter of
+// the length; the even wave numbers are then listed as 2, 6, 10, .. before 4, 8, ..
 // Modes (ky, kx) and (kx, ky) have the same eigenvalue and therefore the same
 // residual polynomial, so the iteration runs on slots, one per pair: 16 x 16
 // tiles of the array with a <= b (row index a, column index b), 256 slots a tile.
-constexpr int kSineMaxNx = 1024;    // longest transform (rows of both parities in LDS)
+constexpr int kSineMaxNx = 1024;    // longest transform (16 rows in LDS)
 constexpr int kSineThreads = 512;   // threads per block of the iteration kernel
 constexpr int kSineSlots = 27;      // most slots per thread (their state stays in registers)
 // Factors per transform length: packs of the sine matrices in the order the
-// matrix instructions read them (pack[p][tile][step][lane], parity p, 16 x 4
-// entries per step), and per slot t = eigenvalue of M K_0 and 1 / (factor of M).
+// matrix instructions read them (pack[part][tile][step][lane], 16 x 4 entries per
+// step), and per slot t = eigenvalue of M K_0 and 1 / (factor of M).
 template <typename T>
 struct SineTables {
-  int nx, ho, he, nt;  // nt: tiles of 16 per parity (of ho)
+  int nx, ho, he;
+  int parts, nq;       // 2 or 4 products, tiles of 16 in the longest of them
   int ept, groups;     // slots per thread, blocks that share a column
-  const T* fwd[2];     // S_p[4 s + l / 16][16 c + l % 16]
-  const T* inv[2];     // S_p[16 c + l % 16][4 s + l / 16]
+  const T* fwd;        // [part] S_p[4 s + l / 16][16 c + l % 16]
+  const T* inv;        // [part] S_p[16 c + l % 16][4 s + l / 16]
   const int4* tiles;   // [2 ept groups]: first row and column, row and column end
   const double* t;     // [512 ept groups]
   const double* ipi;   // 0 in slots that hold no mode
 };
 // Sizes of those tables.
 struct SineSizes {
-  int nx, ho, he, nt, ept, groups;
-  long pack, slots, ntiles;  // entries of one pack, slots, tiles
+  int nx, ho, he, nt, parts, nq, ept, groups;  // nt: slot tiles per parity (of ho)
+  long pack, slots, ntiles;  // entries of one part's pack, slots, tiles
 };
 inline SineSizes sine_sizes(int nx) {
   SineSizes z{};
@@ -327,7 +331,13 @@ inline SineSizes sine_sizes(int nx) {
     }
   z.slots = (long)z.ept * z.groups * kSineThreads;
   z.ntiles = z.slots / 256;
-  z.pack = 256L * z.nt * z.nt;
+  // four products where n_e is even and they save tiles (up to 16 modes per
+  // parity a quarter still fills a tile)
+  const int nq = (nx / 2 + 1 + 31) / 32;  // tiles of ceil(n_e / 4) modes
+  const bool four = nx % 2 == 1 && nq < z.nt;
+  z.parts = four ? 4 : 2;
+  z.nq = four ? nq : z.nt;
+  z.pack = 256L * z.nq * z.nq;
   return z;
 }
 // The problem's constants behind the slot tables.

@@ -19,9 +19,10 @@ def _solver(prob, **kw):
 # n_e and what changes there: the smallest grid; one and two 16-mode tiles per
 # parity (33 / 34); 3, 4 and 5 tiles (65, 97, 130), 5, 8, 11 and 23 slots per
 # thread; two blocks per column (131, 200: 14 and 27 slots), three (256, 257: an even
-# and an odd number of modes per parity; 258), ten and twelve (512, 515: transforms
-# of up to and of more than 256 modes per parity)
-SIZES = [3, 4, 5, 32, 33, 34, 65, 66, 97, 130, 131, 200, 256, 257, 258, 512, 515]
+# and an odd number of modes per parity; 258), ten to twelve (512, 514, 515). Transforms
+# in four products from 34 on where n_e is even (n_e / 2 odd: 34, 66, 130, 258, 514;
+# even: 36, 200, 256, 512), in two elsewhere; more than sixteen tiles from 514 on
+SIZES = [3, 4, 5, 32, 33, 34, 36, 65, 66, 97, 130, 131, 200, 256, 257, 258, 512, 514, 515]
 
 
 @pytest.mark.parametrize("prec,tol", [(64, 1e-11), (32, 2e-5)])
@@ -50,7 +51,7 @@ def test_fixed_iterations_match_oracle(n_e, prec, tol):
 
 
 @pytest.mark.parametrize("prec,tol", [(64, 1e-11), (32, 1e-4)])
-@pytest.mark.parametrize("n_e,ncols", [(12, 120), (47, 35), (101, 20), (256, 90), (300, 35)])
+@pytest.mark.parametrize("n_e,ncols", [(12, 120), (47, 35), (101, 20), (201, 90), (256, 90), (300, 35)])
 def test_solves_match_tiled_solver(n_e, ncols, prec, tol):
     """Solves to a tolerance, more columns than groups of blocks among them, cold
     and (through a warm-started action) warm: the tiled solver's counts and results.
