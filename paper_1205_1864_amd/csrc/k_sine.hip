@@ -1,7 +1,7 @@
 // Inner PCG in the sine basis: transforms to and from the basis and the
 // iteration on the transformed columns.
 //
-// A solve is five launches: right-hand side -> [x pass] -> [y pass] -> spectral
+// A solve is five launches (one for columns of up to 64 rows): right-hand side -> [x pass] -> [y pass] -> spectral
 // right-hand side -> iteration -> spectral solution -> [y pass] -> [x pass].
 // A pass is a product with sine matrices of a quarter (or half) of the length on
 // folded data (FP64 or FP32 matrix instructions).
@@ -285,7 +285,7 @@ template <typename T>
 struct SineRagged {
   PcgCols<T> cols;
   const SineTables<T>* tabs;
-  __device__ T* column(int which, int o) const {
+  __device__ __forceinline__ T* column(int which, int o) const {
     switch (which) {
       case COL_B: return const_cast<T*>(ld_uniform(cols.b, o));
       case COL_X: return ld_uniform(cols.x, o);
@@ -562,6 +562,197 @@ __global__ __launch_bounds__(kPassThreads) void sine_y_kernel(SineTables<T> tab,
 }
 
 // ---------------------------------------------------------------------------
+// Transforms inside a block
+// ---------------------------------------------------------------------------
+
+// Where entry q of part p lies in a vector of nx places that is folded in place:
+// first + q step.
+__device__ __forceinline__ void in_place(const Fold& F, bool inv, int p, int& first, int& step) {
+  step = 1;
+  if (!F.four) {
+    first = p == 0 ? 0 : inv ? F.ho : F.N - 2;
+    if (p == 1 && !inv) step = -1;
+  } else if (inv) {
+    first = p == 0 ? 0 : p == 1 ? F.H - 1 : p == 2 ? F.H : F.H + F.h1;
+    if (p == 1) step = -1;
+  } else {
+    first = p < 2 ? p : p == 2 ? F.N - 2 : F.H;
+    step = p < 2 ? 2 : p == 2 ? -1 : 1;
+  }
+}
+
+constexpr int kFusedSlots = 2;  // pairs of products a wave holds: two products of two tiles or four of one
+
+// One direction of a transform of the nx x nx array D in LDS, in place: this
+// wave's 16 lines (rows along x, ALONG_X; columns along y), which no other wave
+// touches meanwhile. at(line, place) is an element of a line; lines past the end
+// hold whatever LDS holds and reach no other line.
+template <typename T, bool INV, bool ALONG_X, typename At>
+__device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* pack, At at) {
+  using M = Mac<T>;
+  using V = typename M::V;
+  // not known to be the same in every call: addresses are computed again instead of being kept
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int line = lane & 15, sub = lane >> 4, nx = F.N - 1;
+  // fold
+  if (!INV) {
+    for (int i = sub; i < F.items(false); i += 4) {
+      int e[4];
+      F.template entries<false>(i, e);
+      T x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) x[k] = *at(line, e[k]);
+      if (F.four) {
+        const T v = x[0] - x[1], w = x[2] - x[3];
+        const bool mid = e[2] == e[0];
+        *at(line, e[0]) = x[0] + x[1];
+        *at(line, e[1]) = mid ? v : v + w;
+        if (!mid) {
+          *at(line, e[2]) = x[2] + x[3];
+          *at(line, e[3]) = v - w;
+        }
+      } else {
+        if (e[0] < F.he) {
+          *at(line, e[0]) = x[0] + x[1];
+          *at(line, e[1]) = x[0] - x[1];
+        }
+        if (i + (F.ho + 1) / 2 < F.he) {
+          *at(line, e[2]) = x[2] + x[3];
+          *at(line, e[3]) = x[2] - x[3];
+        }
+      }
+    }
+  } else if (F.four) {
+    for (int i = sub; i < F.h1; i += 4) {
+      const T u = *at(line, i), m = *at(line, F.H - 1 - i);
+      *at(line, i) = u + m;
+      *at(line, F.H - 1 - i) = u - m;
+    }
+  }
+  // products: slot t takes tile t of the pair (two products) or the tile of pair t
+  const int pairs = F.four ? 2 : 1, steps = 4 * nq, part = nq * steps * 64;
+  V acc[kFusedSlots][2];
+  const T* f[kFusedSlots];
+  bool on[kFusedSlots];
+#pragma unroll
+  for (int t = 0; t < kFusedSlots; ++t) {
+    const int pr = F.four ? t : 0, ct = F.four ? 0 : t;
+    on[t] = ct < nq;
+    f[t] = pack + (2 * pr * nq + ct) * steps * 64;
+    acc[t][0] = V{0, 0, 0, 0};
+    acc[t][1] = V{0, 0, 0, 0};
+  }
+  int first[4], step[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) in_place(F, INV, p < 2 * pairs ? p : 0, first[p], step[p]);
+  T n0[kFusedSlots], n1[kFusedSlots];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int t = 0; t < kFusedSlots; ++t)
+      if (on[t]) {
+        n0[t] = f[t][64 * k + lane];
+        n1[t] = f[t][part + 64 * k + lane];
+      }
+  };
+  load(0);
+  for (int k = 0; k < steps; ++k) {
+    T w0[kFusedSlots], w1[kFusedSlots], x[4];
+#pragma unroll
+    for (int t = 0; t < kFusedSlots; ++t) {
+      w0[t] = n0[t];
+      w1[t] = n1[t];
+    }
+    if (k + 1 < steps) load(k + 1);
+    // entries past a part's length meet zeros of the matrix: any place of the line will do
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      if (p < 2 * pairs) x[p] = *at(line, min(max(first[p] + (4 * k + sub) * step[p], 0), nx - 1));
+#pragma unroll
+    for (int t = 0; t < kFusedSlots; ++t)
+      if (on[t]) {
+        const T x0 = t == 1 && F.four ? x[2] : x[0], x1 = t == 1 && F.four ? x[3] : x[1];
+        acc[t][0] = ALONG_X ? M::mac(x0, w0[t], acc[t][0]) : M::mac(w0[t], x0, acc[t][0]);
+        acc[t][1] = ALONG_X ? M::mac(x1, w1[t], acc[t][1]) : M::mac(w1[t], x1, acc[t][1]);
+      }
+  }
+  // unfold: the products of a pair meet in a lane
+#pragma unroll
+  for (int t = 0; t < kFusedSlots; ++t) {
+    if (!on[t]) continue;
+    const int pr = F.four ? t : 0, ct = F.four ? 0 : t;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int ln = ALONG_X ? M::row(lane, r) : line;
+      const int k = 16 * ct + (ALONG_X ? line : M::row(lane, r));
+      const T u = acc[t][0][r], v = acc[t][1][r];
+      auto put = [&](int e, T y) { *at(ln, e) = y; };
+      if (!F.four) {
+        if (k < F.ho) put(k, u);
+        if (k < F.he) put(INV ? F.N - 2 - k : F.ho + k, v);
+      } else if (!INV && pr == 0) {
+        if (k < F.h1) {
+          put(k, u + v);
+          put(F.H - 1 - k, u - v);
+        } else if (k < F.H - F.h1) {
+          put(k, u);
+        }
+      } else if (!INV) {
+        if (k < F.h1) put(F.H + k, u);
+        if (k < F.H - F.h1 - 1) put(F.H + F.h1 + k, v);
+      } else if (pr == 0) {
+        if (k < F.H - F.h1) put(2 * k, u);
+        if (k < F.h1) put(2 * k + 1, v);
+      } else if (k < F.H - F.h1 - 1) {
+        put(F.N - 2 - k, u + v);
+        put(F.H + k, u - v);
+      } else if (k < F.h1) {
+        put(F.N - 2 - k, u);
+      }
+    }
+  }
+  if (INV)
+    for (int i = sub; i < F.he; i += 4) {
+      const T u = *at(line, i), v = *at(line, F.N - 2 - i);
+      *at(line, i) = u + v;
+      *at(line, F.N - 2 - i) = u - v;
+    }
+}
+
+// Both directions on one column of at most 64 rows, src to dst through LDS. A wave
+// takes 16 rows, then 16 columns, so the block meets only in between.
+template <typename T, bool INV>
+__device__ __forceinline__ void column_transform(int nx, int parts, int nq, const T* pack, const T* src, T* dst,
+                                                 T* D) {
+  nx = __builtin_amdgcn_readfirstlane(nx);
+  asm volatile("" : "+s"(nx));
+  const Fold F(nx, parts);
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nr = (nx + 15) / 16, ld = 16 * nr + 16 / (int)sizeof(T);
+  if (wave < nr) {
+    const int r1 = min(16, nx - 16 * wave);
+    T* d = D + 16 * wave * ld;
+    const T* s = src + 16 * wave * nx;
+    for (int c = lane; c < nx; c += 64)
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (r < r1) d[r * ld + c] = s[r * nx + c];
+    line_transform<T, INV, true>(F, nq, pack, [&](int r, int c) { return d + r * ld + c; });
+  }
+  __syncthreads();
+  if (wave < nr) {
+    T* d = D + 16 * wave;
+    line_transform<T, INV, false>(F, nq, pack, [&](int c, int r) { return d + r * ld + c; });
+  }
+  __syncthreads();
+  for (int r = wave; r < nx; r += blockDim.x >> 6)
+    for (int c = lane; c < nx; c += 64) dst[r * nx + c] = D[r * ld + c];
+  __syncthreads();
+}
+
+// ---------------------------------------------------------------------------
 // Iteration
 // ---------------------------------------------------------------------------
 
@@ -601,7 +792,7 @@ struct ColumnSums {
 
   __device__ unsigned long long* slot(unsigned e, int k) const { return ex + ((long)(e % 3) * groups + k) * kSumWidth; }
 
-  __device__ void sum(double (&v)[kSumWidth]) {
+  __device__ __forceinline__ void sum(double (&v)[kSumWidth]) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, row = lane >> 4;
     double (*buf)[kSumWidth] = red[epoch & 1];
     // row i of the lanes ends up with sum i of the wave
@@ -688,20 +879,21 @@ struct ColumnSums {
 // with xi = sum alpha phi in registers too, 18 slots and four blocks a column; 23.4
 // us with one block a column that streams v, t and 1 / pi). 511^2, 120 columns:
 // 13.7 us, ten blocks of 27 slots (22.9 us, fifteen of 18).
+// FUSED: columns of at most kSineFusedNx rows, transformed here too.
 // RAGGED: the listed columns of several problems; those whose tables have other
 // slot and block counts than this launch are left to the launches for theirs.
 constexpr int sine_t_regs(int nr) {
   constexpr int arrays = 39;  // of a value per thread, 156 KB
   return nr <= 11 ? nr : 2 * nr > arrays ? 2 * nr - arrays : 0;
 }
-template <typename T, int NR, bool RAGGED>
-__global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A, SineRagged<T> C, int ngroups) {
+template <typename T, int NR, bool RAGGED, bool FUSED>
+__global__ __launch_bounds__(kSineThreads, FUSED ? 4 : 1) void sine_pcg_kernel(SineArgs<T> A, SineRagged<T> C, int ngroups) {
   constexpr int TR = sine_t_regs(NR);  // slots whose t is in registers
   extern __shared__ unsigned char smem[];
   __shared__ double red[2][kSineThreads / 64][kSumWidth], all[2][kSumWidth];
   __shared__ int sflag;
   const int tid = threadIdx.x;
-  const int G = A.tab.groups;
+  const int G = FUSED ? 1 : A.tab.groups;
   // The blocks of a group wait for each other, so groups form in the order in
   // which blocks start: whatever else holds compute units, at most one group of
   // a launch is incomplete, and the complete ones run to their end.
@@ -722,24 +914,31 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
   ColumnSums cs{red, all, reinterpret_cast<unsigned long long*>(A.sc.part) + (long)group * G * 3 * kSumWidth,
                 A.sc.status, &sflag, G, g, 0u, false};
   const int ncols = RAGGED ? ld_uniform(C.cols.nact, 0) : A.ncols;
+  if (FUSED && blockIdx.x == 0 && tid == 0) *A.sc.status = 0;
   for (int c = group; c < ncols; c += ngroups) {
     T* s = A.s + (long)c * A.n;
     const T* s0 = A.s0 + (long)c * A.n;
-    int sb = sbase, lane = lane_;
-    asm volatile("" : "+s"(sb), "+v"(lane));  // no address below is kept from one column to the next
-    tiles = A.tab.tiles + sb / 256;
-    tt = A.tab.t + sb + w0 * 64 + lane;  // element e at 64 e
-    ip = A.tab.ipi + sb + w0 * 64 + lane;
+    int lane = lane_;
+    asm volatile("" : "+v"(lane));  // no address below is kept from one column to the next
+    tiles = A.tab.tiles + sbase / 256;
+    tt = A.tab.t + sbase + w0 * 64 + lane;  // element e at 64 e
+    ip = A.tab.ipi + sbase + w0 * 64 + lane;
     if constexpr (RAGGED) {
       const int o = ld_uniform(C.cols.act, c);
       const SineTables<T>& tab = C.tabs[ld_uniform(C.cols.prob, o)];
       if (tab.ept != NR || tab.groups != G) continue;
       nx = tab.nx;
-      tiles = tab.tiles + sb / 256;
-      tt = tab.t + sb + w0 * 64 + lane;
-      ip = tab.ipi + sb + w0 * 64 + lane;
+      tiles = tab.tiles + sbase / 256;
+      tt = tab.t + sbase + w0 * 64 + lane;
+      ip = tab.ipi + sbase + w0 * 64 + lane;
       s = C.column(COL_S, o);
       s0 = C.column(COL_S0, o);
+    }
+    if constexpr (FUSED) {
+      T* D = reinterpret_cast<T*>(smem);
+      column_transform<T, false>(nx, A.tab.parts, A.tab.nq, A.tab.fwd, A.b + (long)c * A.n, s, D);
+      if (A.warm)
+        column_transform<T, false>(nx, A.tab.parts, A.tab.nq, A.tab.fwd, A.x + (long)c * A.n, const_cast<T*>(s0), D);
     }
     // row and column of element e (its 64 slots are a quarter of a tile)
     auto place = [&](int e, int& a, int& b) {
@@ -833,6 +1032,11 @@ __global__ __launch_bounds__(kSineThreads, 1) void sine_pcg_kernel(SineArgs<T> A
       s[i1] = (T)x1;
       if (a != b) s[i2] = (T)x2;
     }
+    if constexpr (FUSED) {
+      __syncthreads();
+      column_transform<T, true>(nx, A.tab.parts, A.tab.nq, A.tab.inv, s, A.x + (long)c * A.n,
+                                reinterpret_cast<T*>(smem));
+    }
   }
 }
 
@@ -921,25 +1125,31 @@ hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from
       [&](int W) { return launch(sine_y_kernel<T, INV, 1, 2, RAGGED>, W); });
 }
 
-template <typename T, bool RAGGED>
+template <typename T, bool RAGGED, bool FUSED>
 hipError_t pcg(const SineArgs<T>& A, const SineRagged<T>& C, int ngroups, hipStream_t s) {
   auto launch = [&](auto kfn, int nr) {
-    const size_t sm = sizeof(double) * kSineThreads * (2 * nr - sine_t_regs(nr));
+    size_t sm = sizeof(double) * kSineThreads * (2 * nr - sine_t_regs(nr));
+    if (FUSED) {  // the longest column of that many slots, in tiles
+      const int rows = nr == 2 ? 32 : 64;
+      sm = std::max(sm, sizeof(T) * rows * (rows + 16 / sizeof(T)));
+    }
     const hipError_t e = allow_lds(kfn, sm);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kfn, dim3((unsigned)(ngroups * A.tab.groups)), dim3(kSineThreads), sm, s, A, C, ngroups);
     return hipGetLastError();
   };
   switch (A.tab.ept) {
-    case 2: return launch(sine_pcg_kernel<T, 2, RAGGED>, 2);
-    case 5: return launch(sine_pcg_kernel<T, 5, RAGGED>, 5);
-    case 8: return launch(sine_pcg_kernel<T, 8, RAGGED>, 8);
-    case 11: return launch(sine_pcg_kernel<T, 11, RAGGED>, 11);
-    case 14: return launch(sine_pcg_kernel<T, 14, RAGGED>, 14);
-    case 18: return launch(sine_pcg_kernel<T, 18, RAGGED>, 18);
-    case 23: return launch(sine_pcg_kernel<T, 23, RAGGED>, 23);
-    case 27: return launch(sine_pcg_kernel<T, 27, RAGGED>, 27);
+    case 2: return launch(sine_pcg_kernel<T, 2, RAGGED, FUSED>, 2);
+    case 5: return launch(sine_pcg_kernel<T, 5, RAGGED, FUSED>, 5);
   }
+  if constexpr (!FUSED) switch (A.tab.ept) {
+      case 8: return launch(sine_pcg_kernel<T, 8, RAGGED, false>, 8);
+      case 11: return launch(sine_pcg_kernel<T, 11, RAGGED, false>, 11);
+      case 14: return launch(sine_pcg_kernel<T, 14, RAGGED, false>, 14);
+      case 18: return launch(sine_pcg_kernel<T, 18, RAGGED, false>, 18);
+      case 23: return launch(sine_pcg_kernel<T, 23, RAGGED, false>, 23);
+      case 27: return launch(sine_pcg_kernel<T, 27, RAGGED, false>, 27);
+    }
   return hipErrorInvalidValue;
 }
 
@@ -995,8 +1205,9 @@ hipError_t launch_sine(const SineArgs<T>& A, int num_cu, hipStream_t s) {
                         t.groups == 1 ? 0 : ngroups * t.groups * 3 * kSumWidth, A.sc.arrivals, t.groups == 1 ? 0 : 1,
                         A.sc.status};
   const SineRagged<T> none{};
+  if (t.nx <= kSineFusedNx) return pcg<T, false, true>(A, none, ngroups, s);
   hipError_t e = transform_in<T, false>(A, none, t.nx, reset, num_cu, s);
-  if (e == hipSuccess) e = pcg<T, false>(A, none, ngroups, s);
+  if (e == hipSuccess) e = pcg<T, false, false>(A, none, ngroups, s);
   if (e == hipSuccess) e = transform_out<T, false>(A, none, t.nx, num_cu, s);
   return e;
 }
@@ -1022,7 +1233,7 @@ hipError_t launch_sine_ragged(const SineArgs<T>& args, const PcgCols<T>& cols, c
     a.sc.arrivals = args.sc.arrivals + k;
     const int ngroups = group_count(args.ncols, classes[k].groups, num_cu);
     if (ngroups < 1) return hipErrorInvalidValue;
-    e = pcg<T, true>(a, C, ngroups, s);
+    e = pcg<T, true, false>(a, C, ngroups, s);
   }
   if (e == hipSuccess) e = transform_out<T, true>(args, C, max_nx, num_cu, s);
   return e;

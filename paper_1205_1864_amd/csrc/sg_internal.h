@@ -294,6 +294,15 @@ size_t pcg_scratch_bytes(int ncols, int ntiles);
 constexpr int kSineMaxNx = 1024;    // longest transform (16 rows in LDS)
 constexpr int kSineThreads = 512;   // threads per block of the iteration kernel
 constexpr int kSineSlots = 27;      // most slots per thread (their state stays in registers)
+// Columns of up to 64 rows are transformed within the iteration's launch, one launch
+// in place of five (20 iterations at once, 10 / 280 columns: 15^2 50 / 67 us against
+// 66 / 81, 64^2 67 / 97 against 70 / 121). Longer ones by passes of the whole device:
+// one compute unit's products and its waits cost more than the launches (74^2 with
+// four tiles a wave 101 / 197 us against 80 / 160). Nor in ragged launches, whose
+// passes take the short columns along with the long ones (16 problems of up to 255^2
+// 69.3 ms against 68.1). Up to 64 rows a transform is two products of at most two
+// tiles or four of one.
+constexpr int kSineFusedNx = 64;
 // Factors per transform length: packs of the sine matrices in the order the
 // matrix instructions read them (pack[part][tile][step][lane], 16 x 4 entries per
 // step), and per slot t = eigenvalue of M K_0 and 1 / (factor of M).

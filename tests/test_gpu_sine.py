@@ -17,7 +17,7 @@ def _solver(prob, **kw):
 
 
 # n_e and what changes there: the smallest grid; one and two 16-mode tiles per
-# parity (33 / 34); 3, 4 and 5 tiles (65, 97, 130), 5, 8, 11 and 23 slots per
+# parity (33 / 34); one and five launches a solve (65 / 66); 3, 4 and 5 tiles (65, 97, 130), 5, 8, 11 and 23 slots per
 # thread; two blocks per column (131, 200: 14 and 27 slots), three (256, 257: an even
 # and an odd number of modes per parity; 258), ten to twelve (512, 514, 515). Transforms
 # in four products from 34 on where n_e is even (n_e / 2 odd: 34, 66, 130, 258, 514;
