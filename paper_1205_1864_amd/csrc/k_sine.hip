@@ -844,7 +844,7 @@ struct ColumnSums {
         s += val;
       }
       ok = __all(ok);
-      if (!ok && lane == 0) atomicExch(status, 1);
+      if (!ok && lane == 0) __hip_atomic_store(status, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       if ((lane & 15) == 0) {
         (*out)[row] = s;
         if (epoch > 0) agent_store(slot(epoch + 2, g) + row, kEmpty);  // the place of exchange epoch - 1

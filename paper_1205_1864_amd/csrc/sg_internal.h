@@ -528,8 +528,6 @@ struct sg_ctx {
   int pcg_maxcols;
   sgk::PcgScratch pcgsc;
   double* red_part;  // reduction partials
-  double* red_out;   // reduction results (device)
-  std::vector<double> host_out;  // host mirror of red_out
   long inner_it_acc;
   double inner_ms_acc;
   double inner_bytes_acc;
@@ -551,6 +549,7 @@ struct sg_ctx {
   int nev = 0;             // events created in evpool
   int* iters_host = nullptr;   // pinned, iters_cap ints
   int* status_host = nullptr;  // pinned, kMaxPending ints
+  double* host_out = nullptr;  // pinned, written by the last kernel of a reduction
   long iters_cap = 0, iters_used = 0;
   // one preconditioner action captured into a HIP graph (opts.use_graph)
   bool capturing = false;   // inner launches are ordinary launches and never settle the read-back
