@@ -39,11 +39,10 @@ HBM_PEAK_GBS = 8000.0
 CHEB_DEGREE = 16  # updates of the Chebyshev preconditioner of the inner PCG (fastest measured; 8 as an extra)
 # HBM bytes per launch measured with separate FETCH_SIZE and WRITE_SIZE counter
 # runs of this benchmark, scaled by the same counters of a 512 MiB elementwise
-# kernel (profiles/hbm_traffic_solve_256sq_M10_p3.txt). Emptied when the
+# kernel (profiles/hbm_traffic_* and sine_kernels_solve_256sq_M10_p3.txt). Emptied when the
 # kernel changes.
-# pcg_kernel<double, BandTile<double, 128 | 64, 15, 16>, 1>, average over a solve's launches, by the
-# inner schedule's block cap (-1: whole columns per block where they fill the device; 0: automatic grid)
-PCG_TRAFFIC_BYTES = {-1: 14.30e9}
+# inner solves (transforms and iteration in the sine basis), average over a timed solve's inner launches
+PCG_TRAFFIC_BYTES = 487.4e6
 # one SG matvec, by schedule (mv_variant, mv_param): the row-staged kernel with 10-row pieces
 MATVEC_TRAFFIC_BYTES = {(4, 10): 354.2e6}
 
@@ -476,12 +475,13 @@ def main():
             extra["extras_error"] = repr(exc)
     achieved = bytes_inner / (ms_inner * 1e-3) / 1e9 if ms_inner > 0 else 0.0
     # the counter traffic belongs to the schedules it was measured with
-    pcg_traffic = PCG_TRAFFIC_BYTES.get(schedule["pcg_max_blocks"]) if schedule["pcg_tile"] == 32 else None
+    pcg_traffic = PCG_TRAFFIC_BYTES if schedule["pcg_tile"] == 32 else None
     mv_traffic = MATVEC_TRAFFIC_BYTES.get((schedule["mv_variant"], schedule["mv_param"]))
     mv_kernel = {4: "sgop_stage_kernel", 3: "sgop_strip_kernel<double>"}.get(
         schedule["mv_variant"], f"SG operator variant {schedule['mv_variant']}")
     roofline = {
-        "kernel": "pcg_kernel (persistent batched inner PCG, all launches of the timed solves)",
+        "kernel": "sine_x_kernel, sine_y_kernel, sine_pcg_kernel (batched inner PCG in the sine basis, all inner "
+                  "solves of the timed solves)",
         "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": achieved / HBM_PEAK_GBS, "traffic": pcg_traffic, "traffic_unit": "bytes per launch",
         "avg_launch_ms": ms_inner / max(1, launches), "launches": launches,
