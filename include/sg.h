@@ -104,7 +104,7 @@ typedef struct sg_problem {
  *                     n_e = 1025 the same iteration in the sine basis, in
  *                     which K_0 and the preconditioner are diagonal (equal
  *                     iterates and counts up to rounding); on larger grids,
- *                     or with inner_maxit below n_e / 96, banded tiles, with
+ *                     or with inner_maxit below n_e / 176, banded tiles, with
  *                     64-row bands for launches of fewer tiles than compute
  *                     units.
  *   warm_start        0: every inner solve starts from zero. 1: the inner

@@ -382,11 +382,13 @@ int choose_tile(const sg_ctx* h, int degree) {
 
 // The sine basis costs four transform passes (n_e^3 operations a column) and next
 // to nothing per iteration, the tiles a full sweep of the column per iteration.
-// Measured where the two meet (FP64, degree 1, the worst for the transforms): 2
-// iterations at 256^2 (35 columns: 0.19 ms both), 5 at 512^2 (1.0 ms), 10 at
-// 1024^2 (20 columns: 4.3 ms), so an iteration cap below nx / 96 goes to the tiles.
+// Measured where the two meet (FP64, degree 1, the worst for the transforms; 35, 35
+// and 20 columns; ms of the sine basis / tiles): n_e = 256 0.14 / 0.19 at 2
+// iterations (0.13 on tiles at 1), 257 0.18 / 0.19 at 2, 512 0.50 / 0.50 at 2, 513
+// 0.69 / 0.69 at 3, 1024 1.5 / 1.5 at 3, 1023 2.2 / 2.3 at 5, so an iteration cap
+// below nx / 176 goes to the tiles.
 bool use_sine(const sg_ctx* h) {
-  return h->sine_ok && h->opts.tile == 0 && h->opts.inner_maxit * 96L >= h->nx;
+  return h->sine_ok && h->opts.tile == 0 && h->opts.inner_maxit * 176L >= h->nx;
 }
 
 template <typename T>
