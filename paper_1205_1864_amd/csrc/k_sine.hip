@@ -583,6 +583,15 @@ __device__ __forceinline__ void in_place(const Fold& F, bool inv, int p, int& fi
 
 constexpr int kFusedSlots = 2;  // pairs of products a wave holds: two products of two tiles or four of one
 
+// Between the lanes of a wave that exchange data through LDS: what they wrote before
+// is there for each other after it, and nothing they still read is written before it.
+// The hardware takes a wave's LDS accesses in their order, so this costs no instruction;
+// it holds the compiler, which sees one lane's places only, to that order.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // One direction of a transform of the nx x nx array D in LDS, in place: this
 // wave's 16 lines (rows along x, ALONG_X; columns along y), which no other wave
 // touches meanwhile. at(line, place) is an element of a line; lines past the end
@@ -595,6 +604,7 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
   const int line = lane & 15, sub = lane >> 4, nx = F.N - 1;
+  wave_fence();
   // fold
   if (!INV) {
     for (int i = sub; i < F.items(false); i += 4) {
@@ -630,6 +640,7 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
       *at(line, F.H - 1 - i) = u - m;
     }
   }
+  wave_fence();
   // products: slot t takes tile t of the pair (two products) or the tile of pair t
   const int pairs = F.four ? 2 : 1, steps = 4 * nq, part = nq * steps * 64;
   V acc[kFusedSlots][2];
@@ -676,6 +687,7 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
         acc[t][1] = ALONG_X ? M::mac(x1, w1[t], acc[t][1]) : M::mac(w1[t], x1, acc[t][1]);
       }
   }
+  wave_fence();
   // unfold: the products of a pair meet in a lane
 #pragma unroll
   for (int t = 0; t < kFusedSlots; ++t) {
@@ -711,12 +723,14 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
       }
     }
   }
-  if (INV)
+  if (INV) {
+    wave_fence();
     for (int i = sub; i < F.he; i += 4) {
       const T u = *at(line, i), v = *at(line, F.N - 2 - i);
       *at(line, i) = u + v;
       *at(line, F.N - 2 - i) = u - v;
     }
+  }
 }
 
 // Both directions on one column of at most 64 rows, src to dst through LDS. A wave
