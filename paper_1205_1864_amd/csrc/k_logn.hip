@@ -299,7 +299,8 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double (*red)[2
 // and two host round trips, 5.2 us here with 24 to 64 blocks (26 us with one block,
 // 8.4 with 8); 16 x 16: 10.2 us with 32 blocks, 67 with one.
 // A wait that expires (blocks of this launch held back by other work on the device)
-// sets the status, and every later launch returns at once.
+// sets the status. A block that waits looks at it now and then and gives up too, here
+// and in every later launch; whether a block leaves is settled between two barriers.
 template <int NT, int VPT, int TREG>
 __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
   constexpr bool REG = TREG > 0;
@@ -308,7 +309,6 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
   __shared__ double red[2][NT / 64][2];
   __shared__ int dead;
   const int tid = threadIdx.x;
-  if (agent_load(A.status) != 0) return;  // an earlier launch gave up: its caller starts again without
   const int sys = blockIdx.x / A.G, g = blockIdx.x - sys * A.G;
   const int nx = A.n_e - 1, n = nx * nx, len = n * A.nr;
   const int RS = nx + 1, CS = RS * RS;  // row and column strides of the padded p
@@ -463,8 +463,8 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
 #pragma unroll
           for (int k = 0; k < VPT; ++k) miss |= empty(k);
           if (!__any(miss)) break;
-          if (spins >= A.spins) {
-            dead = 1;
+          if (spins >= A.spins || ((spins & 63) == 63 && agent_load(A.status) != 0)) {
+            dead = 1;  // the block leaves as a whole after its next barrier
             break;
           }
           // the missing ones again, all on their way together

@@ -1,4 +1,5 @@
-"""Order of the LDS exchanges within a wave, from the compiled device code (CPU).
+"""What waves and blocks agree on, from the compiled device code (CPU): the order of
+the LDS exchanges within a wave, and one decision per block on a shared status.
 
 The transforms inside a block (columns of at most 64 rows) pass data between the
 lanes of one wave through LDS without a block barrier: staged rows to the fold,
@@ -6,7 +7,12 @@ the fold to the products, the products' reads to the unfolded results that take
 their places, and, towards the grid, the results to the last sums. The hardware
 keeps a wave's LDS accesses in order, but the compiler may swap a lane's write
 and its read of another place unless a fence stands between them. Every such
-transform has to state those fences, three one way and four the other."""
+transform has to state those fences, three one way and four the other.
+
+The one-launch block solves of the lognormal path give up where another block has.
+That status may be set at any time, so a block has to settle it between two barriers:
+were every wave to read it at the start and leave, some would go and the rest would
+run on without their rows."""
 
 import os
 import re
@@ -16,23 +22,38 @@ import subprocess
 import pytest
 
 
-def test_transforms_inside_a_block_are_fenced():
+def _kernels(src, pattern):
+    """(name, device code) of the kernels of a source whose names match."""
     if shutil.which("hipcc") is None and not os.path.exists("/opt/rocm/bin/hipcc"):
         pytest.skip("hipcc not found")
     from paper_1205_1864_amd import build as bld
     cmd = [bld.hipcc(), *bld.COMMON, "-x", "hip", "--cuda-device-only", "-S", "-emit-llvm", "-o", "-",
-           os.path.join(bld.CSRC, "k_sine.hip")]
+           os.path.join(bld.CSRC, src)]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-3000:]
-    fused = 0
+    out = []
     for body in re.split(r"^define ", res.stdout, flags=re.M)[1:]:
-        m = re.search(r"@(\S*sine_pcg_kernelI[df]Li\d+ELb0ELb1E\w*)\(", body.split("\n", 1)[0])
-        if not m:
-            continue
-        fused += 1
-        body = body.split("\n}", 1)[0]
+        m = re.search(r"@(\S*" + pattern + r"\w*)\(", body.split("\n", 1)[0])
+        if m:
+            out.append((m.group(1), body.split("\n}", 1)[0]))
+    return out
+
+
+def test_transforms_inside_a_block_are_fenced():
+    kernels = _kernels("k_sine.hip", r"sine_pcg_kernelI[df]Li\d+ELb0ELb1E")
+    assert len(kernels) == 4, "one-launch kernels of two sizes in two precisions"
+    for name, body in kernels:
         fences = len(re.findall(r'fence syncscope\("wavefront"\) acq_rel', body))
         barriers = len(re.findall(r"call void @llvm\.amdgcn\.wave\.barrier", body))
         # two directions of the right-hand side, the warm guess and the solution, rows and columns each
-        assert fences >= 2 * 3 + 2 * 3 + 2 * 4 and barriers >= fences, (m.group(1), fences, barriers)
-    assert fused == 4, "one-launch kernels of two sizes in two precisions"
+        assert fences >= 2 * 3 + 2 * 3 + 2 * 4 and barriers >= fences, (name, fences, barriers)
+
+
+def test_block_solves_decide_once_per_block():
+    kernels = _kernels("k_logn.hip", "logn_solve_kernelI")
+    assert len(kernels) == 9
+    for name, body in kernels:
+        entry = body.split("{", 1)[1].split("\n\n", 1)[0]  # up to the first branch, which every lane runs
+        assert re.search(r"^\s+br i1 ", entry, flags=re.M), name
+        assert "load atomic" not in entry, f"{name}: every wave reads the status for itself"
+        assert "load atomic" in body, name
