@@ -399,6 +399,12 @@ void sg_batch_destroy(sg_batch b);
  *                            condition estimate of the preconditioned operator.
  *                            Synchronises the stream. Returns SG_OK,
  *                            SG_NOT_CONVERGED or SG_BREAKDOWN as sg_solve.
+ *   sg_logn_repeats          solves of this handle that were repeated because the
+ *                            device was too busy to run the blocks of a block solve
+ *                            together, and the outer iteration in which the last of
+ *                            them was given up (0: none yet); host outputs, each may
+ *                            be NULL. A repeated solve runs its block solves as
+ *                            single launches per step, to the same tolerances.
  */
 typedef struct sg_logn_ctx* sg_logn_handle;
 int sg_logn_workspace_bytes(const sg_problem* prob, size_t* bytes);
@@ -409,6 +415,7 @@ int sg_logn_matvec(sg_logn_handle h, const double* U, double* Y);
 int sg_logn_solve(sg_logn_handle h, int32_t precond, const double* F, double* U, double rtol, int32_t maxit,
                   double inner_rtol, int32_t inner_maxit, int32_t* outer_it, int64_t* inner_it, double* relres,
                   double* kappa);
+int sg_logn_repeats(sg_logn_handle h, int64_t* solves, int32_t* outer_it);
 void sg_logn_destroy(sg_logn_handle h);
 
 /* Thread-local description of the last failure (never NULL). */

@@ -95,6 +95,7 @@ def _load():
         "sg_logn_setup": [P(SgProblem), VP, ctypes.c_size_t, VP, P(VP)],
         "sg_logn_sizes": [VP, P(I64), P(I32), P(I32)],
         "sg_logn_matvec": [VP, VP, VP],
+        "sg_logn_repeats": [VP, P(I64), P(I32)],
         "sg_logn_solve": [VP, I32, VP, VP, D, I32, D, I32, P(I32), P(I64), P(D), P(D)],
     }
     for name, args in sig.items():
@@ -464,6 +465,13 @@ class LognormalOperator:
                                       ctypes.byref(kap)), allow_positive=True)
         return U, {"rc": rc, "outer_it": int(it.value), "inner_it": int(iin.value), "relres": float(rel.value),
                    "kappa_est": float(kap.value)}
+
+    def repeats(self):
+        """(solves repeated on a device too busy for the one-launch block solves, the
+        outer iteration in which the last of them was given up)."""
+        n, it = ctypes.c_int64(), ctypes.c_int32()
+        _check(lib.sg_logn_repeats(self.handle, ctypes.byref(n), ctypes.byref(it)))
+        return int(n.value), int(it.value)
 
     def close(self):
         if getattr(self, "handle", None):

@@ -479,7 +479,7 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
       block_sum2<NT>(pq, unused, red[1]);
       if (A.G > 1) {
         if (dead) {
-          if (tid == 0) agent_store(A.status, 1ull);
+          if (tid == 0) __hip_atomic_store(A.status, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
           break;
         }
         if (it > 0 && sub == 0)

@@ -57,10 +57,13 @@ struct sg_logn_ctx {
   double *cr = nullptr, *cz = nullptr, *cp = nullptr, *cq = nullptr, *Dinv = nullptr, *part = nullptr;
   double* XF = nullptr;  // forward-sweep values of block Gauss-Seidel
   std::vector<double> host_part;
-  // one-launch block solves: stored blocks per row, iteration count, status
+  // one-launch block solves: stored blocks per row, iteration count, and the status in
+  // pinned memory (the host looks at it wherever it waits for the stream anyway)
   int* first = nullptr;
   unsigned long long* its_d = nullptr;
-  unsigned long long* status_d = nullptr;
+  unsigned long long* status = nullptr;
+  long repeats = 0;   // solves repeated with their iterations on the host
+  int repeat_it = 0;  // outer iteration in which the last of them was given up
   bool one_launch = true;  // off while a solve repeats without them
   long spins = 1L << 20;   // polls before a wait expires, about a second
 };
@@ -234,7 +237,7 @@ int plan(const sg_problem* pr, Plan& pl) {
   pl.o_vec = take(tot, sizeof(double) * nP * 12);
   pl.o_part = take(tot, sizeof(double) * 2 * kLognDotBlocks);  // two partial sets
   pl.o_first = take(tot, sizeof(int) * 2 * pl.P);
-  pl.o_count = take(tot, 2 * sizeof(unsigned long long));
+  pl.o_count = take(tot, sizeof(unsigned long long));
   pl.total = tot;
   return SG_OK;
 }
@@ -284,7 +287,7 @@ int range_solve(sg_logn_ctx* h, int kind, int lo, int nr, const double* B, doubl
     a.first = h->first;
     a.last = h->first + h->P;
     a.its = h->its_d;
-    a.status = h->status_d;
+    a.status = h->status;
     a.spins = h->spins;
     bool done = false;
     SG_HIP(sgk::launch_logn_solve(a, nsys, s, &done));
@@ -390,8 +393,9 @@ int solve_fcg(sg_logn_ctx* h, int precond, const double* F, double* U, double rt
   // flexible CG (Section 5) on A with Algorithm 1 as the preconditioner
   sgk::launch_logn_axpby(nP, 0.0, F, 0.0, U, 0, nullptr, 0, s);  // U = 0
   sgk::launch_logn_axpby(nP, 1.0, F, 0.0, h->R, 0, nullptr, 0, s);
-  const unsigned long long zero[2] = {0, 0};
-  SG_HIP(hipMemcpyAsync(h->its_d, zero, sizeof(zero), hipMemcpyHostToDevice, s));
+  *h->status = 0;  // the last solve waited for its launches
+  const unsigned long long zero = 0;
+  SG_HIP(hipMemcpyAsync(h->its_d, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
   double ff = 0.0, rr = 0.0;
   int rc = dotp(h, F, F, nP, ff);  // waits for the stream
   if (rc) return rc;
@@ -421,6 +425,11 @@ int solve_fcg(sg_logn_ctx* h, int precond, const double* F, double* U, double rt
     sgk::launch_logn_matvec(h->rptr, h->rcol, h->rslot, h->C, h->Pv, h->n_e, h->n, h->P, h->Q, s);
     double pq = 0.0, pr = 0.0;
     if ((rc = dotp(h, h->Pv, h->Q, nP, pq))) return rc;
+    if (*h->status != 0) {  // the action did not finish
+      h->repeat_it = it + 1;
+      expired = true;
+      return SG_EDEVICE;
+    }
     if (!(pq > 0.0) || !std::isfinite(pq)) {
       status = SG_BREAKDOWN;
       break;
@@ -444,14 +453,10 @@ int solve_fcg(sg_logn_ctx* h, int precond, const double* F, double* U, double rt
       break;
     }
   }
-  unsigned long long counts[2] = {0, 0};
-  SG_HIP(hipMemcpyAsync(counts, h->its_d, sizeof(counts), hipMemcpyDeviceToHost, s));
+  unsigned long long count = 0;
+  SG_HIP(hipMemcpyAsync(&count, h->its_d, sizeof(count), hipMemcpyDeviceToHost, s));
   SG_HIP(hipStreamSynchronize(s));
-  if (counts[1] != 0) {
-    expired = true;
-    return SG_EDEVICE;
-  }
-  its_in += (long)counts[0];
+  its_in += (long)count;
   if (outer_it) *outer_it = it;
   if (inner_it) *inner_it = its_in;
   if (relres) *relres = rel;
@@ -537,7 +542,6 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
     h->host_part.assign(2 * kLognDotBlocks, 0.0);
     h->first = (int*)(w + pl.o_first);
     h->its_d = (unsigned long long*)(w + pl.o_count);
-    h->status_d = h->its_d + 1;
     if (const char* v = std::getenv("SGPC_LOGN_SPINS")) h->spins = std::max(0L, std::atol(v));
     h->off.assign(1, 0);
     for (int d = 0; d <= pr->p; ++d) {
@@ -549,6 +553,10 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
       }
       h->off.push_back(h->off.back() + cnt);
     }
+  }
+  if (hipHostMalloc((void**)&h->status, sizeof(*h->status), hipHostMallocDefault) != hipSuccess) {
+    delete h;
+    return fail(SG_ENOMEM, "pinned allocation failed");
   }
   auto up = [&](size_t off, const void* src, size_t bytes) {
     return bytes ? hipMemcpyAsync(w + off, src, bytes, hipMemcpyHostToDevice, h->stream) : hipSuccess;
@@ -569,7 +577,7 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
   // the host tables are freed on return: wait for the copies
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) {
-    delete h;
+    sg_logn_destroy(h);
     return fail(SG_EDEVICE, std::string("lognormal setup: ") + hipGetErrorString(e));
   }
   *out = h;
@@ -606,12 +614,24 @@ int sg_logn_solve(sg_logn_handle h, int32_t precond, const double* F, double* U,
   h->one_launch = true;
   int rc = solve_fcg(h, precond, F, U, rtol, maxit, inner_rtol, inner_maxit, outer_it, inner_it, relres, kappa, expired);
   if (expired) {
+    ++h->repeats;
     h->one_launch = false;
     rc = solve_fcg(h, precond, F, U, rtol, maxit, inner_rtol, inner_maxit, outer_it, inner_it, relres, kappa, expired);
   }
   return rc;
 }
 
-void sg_logn_destroy(sg_logn_handle h) { delete h; }
+int sg_logn_repeats(sg_logn_handle h, int64_t* solves, int32_t* outer_it) {
+  if (!h) return fail(SG_EINVAL, "null handle");
+  if (solves) *solves = h->repeats;
+  if (outer_it) *outer_it = h->repeat_it;
+  return SG_OK;
+}
+
+void sg_logn_destroy(sg_logn_handle h) {
+  if (!h) return;
+  (void)hipHostFree(h->status);
+  delete h;
+}
 
 }  // extern "C"
