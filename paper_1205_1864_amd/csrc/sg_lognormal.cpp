@@ -554,10 +554,6 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
       h->off.push_back(h->off.back() + cnt);
     }
   }
-  if (hipHostMalloc((void**)&h->status, sizeof(*h->status), hipHostMallocDefault) != hipSuccess) {
-    delete h;
-    return fail(SG_ENOMEM, "pinned allocation failed");
-  }
   auto up = [&](size_t off, const void* src, size_t bytes) {
     return bytes ? hipMemcpyAsync(w + off, src, bytes, hipMemcpyHostToDevice, h->stream) : hipSuccess;
   };
@@ -576,6 +572,7 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
   }
   // the host tables are freed on return: wait for the copies
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+  if (e == hipSuccess) e = hipHostMalloc((void**)&h->status, sizeof(*h->status), hipHostMallocDefault);
   if (e != hipSuccess) {
     sg_logn_destroy(h);
     return fail(SG_EDEVICE, std::string("lognormal setup: ") + hipGetErrorString(e));
@@ -630,7 +627,7 @@ int sg_logn_repeats(sg_logn_handle h, int64_t* solves, int32_t* outer_it) {
 
 void sg_logn_destroy(sg_logn_handle h) {
   if (!h) return;
-  (void)hipHostFree(h->status);
+  if (h->status) (void)hipHostFree(h->status);
   delete h;
 }
 
