@@ -246,7 +246,8 @@ def main():
     # not timed: picks the launch schedules for this problem (only the SG operator's when the
     # inner schedule is fixed)
     schedule = solver.sg_autotune(1 if args.pcg_blocks is not None else 3)
-    log(f"autotune: {schedule}")
+    inner_kind = solver.inner_kind()
+    log(f"autotune: {schedule}, inner solver {inner_kind}")
     U = solver.empty()
 
     # ---- timed steps: the HSC-FCG solve
@@ -474,14 +475,15 @@ def main():
             traceback.print_exc()
             extra["extras_error"] = repr(exc)
     achieved = bytes_inner / (ms_inner * 1e-3) / 1e9 if ms_inner > 0 else 0.0
-    # the counter traffic belongs to the schedules it was measured with
-    pcg_traffic = PCG_TRAFFIC_BYTES if schedule["pcg_tile"] == 32 else None
+    # the counter traffic belongs to the solver and the schedules it was measured with
+    pcg_traffic = PCG_TRAFFIC_BYTES if inner_kind == 0 else None
+    pcg_kernel = "sine_x_kernel, sine_y_kernel, sine_pcg_kernel (batched inner PCG in the sine basis" if inner_kind == 0 \
+        else f"pcg_kernel (batched inner PCG on {'banded' if inner_kind == 32 else 'square'} tiles"
     mv_traffic = MATVEC_TRAFFIC_BYTES.get((schedule["mv_variant"], schedule["mv_param"]))
     mv_kernel = {4: "sgop_stage_kernel", 3: "sgop_strip_kernel<double>"}.get(
         schedule["mv_variant"], f"SG operator variant {schedule['mv_variant']}")
     roofline = {
-        "kernel": "sine_x_kernel, sine_y_kernel, sine_pcg_kernel (batched inner PCG in the sine basis, all inner "
-                  "solves of the timed solves)",
+        "kernel": f"{pcg_kernel}, all inner solves of the timed solves)",
         "bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": achieved / HBM_PEAK_GBS, "traffic": pcg_traffic, "traffic_unit": "bytes per launch",
         "avg_launch_ms": ms_inner / max(1, launches), "launches": launches,

@@ -286,7 +286,8 @@ typedef struct sg_tune_report {
                               row); 4: row-staged kernel (node rows of all chaos columns in LDS) */
   int32_t mv_param;        /* 100 * node rows per wave (3; 0 = automatic); node rows per piece (4) */
   int32_t pcg_tile;        /* inner tile kind (32 banded, or the sine basis where tile = 0 was the
-                              fastest; 16 square) */
+                              fastest; 16 square); sg_inner_kind and sg_batch_inner_kind tell the
+                              sine basis from the banded tiles */
   int32_t pcg_max_blocks;  /* cap on the blocks of an inner launch (0 = as many as fit; -1 = whole
                               columns per block for launches whose columns fill at least 3/4 of the
                               resident blocks, no cap for smaller ones) */
@@ -298,6 +299,10 @@ typedef struct sg_tune_report {
 } sg_tune_report;
 
 int sg_autotune(sg_handle h, int32_t flags, sg_tune_report* report);
+
+/* Solver of the inner launches with the handle's present options and schedule:
+ * *kind (host) = 0 the sine basis, 32 banded tiles, 16 square tiles. */
+int sg_inner_kind(sg_handle h, int32_t* kind);
 
 /* Release the handle (the workspace stays with the caller). */
 void sg_destroy(sg_handle h);
@@ -354,6 +359,8 @@ int sg_batch_solve(sg_batch b, const double* const* F, double* const* U, double 
  * the SG-operator schedule of the largest member with mv_ms summed over the
  * members. */
 int sg_batch_autotune(sg_batch b, int32_t flags, sg_tune_report* report);
+/* sg_inner_kind of the batch's ragged inner launches. */
+int sg_batch_inner_kind(sg_batch b, int32_t* kind);
 
 void sg_batch_destroy(sg_batch b);
 

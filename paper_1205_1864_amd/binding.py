@@ -86,6 +86,8 @@ def _load():
         "sg_qoi": [VP, VP, VP, VP, P(D)],
         "sg_adjoint_grad": [VP, VP, VP, VP, D, I32, P(D), P(D), VP, P(SgStats)],
         "sg_autotune": [VP, I32, P(SgTuneReport)],
+        "sg_inner_kind": [VP, P(I32)],
+        "sg_batch_inner_kind": [VP, P(I32)],
         "sg_batch_workspace_bytes": [I32, P(SgProblem), P(SgOpts), P(ctypes.c_size_t)],
         "sg_batch_setup": [I32, P(SgProblem), P(SgOpts), VP, ctypes.c_size_t, VP, P(VP)],
         "sg_batch_sizes": [VP, I32, P(I64), P(I32)],
@@ -335,6 +337,12 @@ class SGSolver:
         _check(lib.sg_autotune(self.handle, int(flags), ctypes.byref(rep)))
         return rep.as_dict()
 
+    def inner_kind(self) -> int:
+        """Solver of the inner launches: 0 the sine basis, 32 banded, 16 square tiles."""
+        kind = ctypes.c_int32()
+        _check(lib.sg_inner_kind(self.handle, ctypes.byref(kind)))
+        return int(kind.value)
+
     def close(self):
         if getattr(self, "handle", None):
             lib.sg_destroy(self.handle)
@@ -409,6 +417,12 @@ class SGBatch:
         rep = SgTuneReport()
         _check(lib.sg_batch_autotune(self.handle, int(flags), ctypes.byref(rep)))
         return rep.as_dict()
+
+    def inner_kind(self) -> int:
+        """Solver of the ragged inner launches, as SGSolver.inner_kind."""
+        kind = ctypes.c_int32()
+        _check(lib.sg_batch_inner_kind(self.handle, ctypes.byref(kind)))
+        return int(kind.value)
 
     def close(self):
         if getattr(self, "handle", None):

@@ -795,6 +795,12 @@ int sg_batch_autotune(sg_batch B, int32_t flags, sg_tune_report* report) {
   return SG_OK;
 }
 
+int sg_batch_inner_kind(sg_batch B, int32_t* kind) {
+  if (!B || !kind) return fail(SG_EINVAL, "null argument");
+  *kind = B->sine ? 0 : B->tile;
+  return SG_OK;
+}
+
 void sg_batch_destroy(sg_batch B) {
   if (!B) return;
   drop_graph(B);

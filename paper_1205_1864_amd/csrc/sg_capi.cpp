@@ -1765,6 +1765,12 @@ int sg_autotune(sg_handle h, int32_t flags, sg_tune_report* report) {
   return autotune(h, flags, report);
 }
 
+int sg_inner_kind(sg_handle h, int32_t* kind) {
+  if (!h || !kind) return fail(SG_EINVAL, "null argument");
+  *kind = use_sine(h) ? 0 : choose_tile(h, effective_degree(h));
+  return SG_OK;
+}
+
 void sg_destroy(sg_handle h) {
   if (!h) return;
   (void)hipStreamSynchronize(h->stream);
