@@ -272,9 +272,9 @@ int sg_adjoint_grad(sg_handle h, const double* U, const double* w_mean, const do
  *                wave, which the coupling products keep, and for the full
  *                operator the row-staged kernel where it fits);
  *   flags bit 1: the inner PCG (with tile = 0 the sine basis where it serves
- *                the grid; tile kind 16 or 32 where the Chebyshev halo
- *                allows 32; block count automatic, half the CUs, or whole
- *                columns per block), timed on
+ *                the grid; square tiles and banded ones, for tile = 0 and 16
+ *                with the automatic band heights; block count automatic, half
+ *                the CUs, or whole columns per block), timed on
  *                the columns of the largest chaos level with a constant
  *                right-hand side.
  * Runs on the handle's stream inside its workspace (the FCG vectors and the

@@ -388,7 +388,7 @@ int choose_tile(const sg_ctx* h, int degree) {
 // 0.69 / 0.69 at 3, 1024 1.5 / 1.5 at 3, 1023 2.2 / 2.3 at 5, so an iteration cap
 // below nx / 176 goes to the tiles.
 bool use_sine(const sg_ctx* h) {
-  return h->sine_ok && h->opts.tile == 0 && h->opts.inner_maxit * 176L >= h->nx;
+  return h->sine_ok && !h->tiles_only && h->opts.tile == 0 && h->opts.inner_maxit * 176L >= h->nx;
 }
 
 template <typename T>
@@ -1288,20 +1288,27 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
     sgk::launch_fill(h->pv, 1.0, N, s);
     if (h->opts.inner_precision == 32) sgk::launch_copy_d2f((float*)h->rw, h->pv, N, s);
     else sgk::launch_copy_d2d((double*)h->rw, h->pv, N, s);
-    // banded candidate: the automatic choice (0, which also shortens the bands of
-    // small launches) unless banded tiles were asked for explicitly
-    const int band = h->opts.tile == 32 ? 32 : 0;
-    std::vector<int> tiles = degree <= sgk::kBandMaxDegree ? std::vector<int>{band, 16}
-                                                                                       : std::vector<int>{16};
-    // with the sine-basis solver the automatic choice is that solver, and banded tiles a candidate beside it
-    if (use_sine(h)) tiles = {0, 32, 16};
+    // banded candidate: the automatic tiles (0, which also shortens the bands of
+    // small launches) unless banded tiles were asked for explicitly; the sine basis
+    // beside them only where it serves the options as they are, not for a caller of
+    // square tiles
+    struct Cand {
+      int tile;
+      bool tiles_only;
+    };
+    std::vector<Cand> tiles;
+    if (use_sine(h)) tiles.push_back({0, false});
+    if (degree <= sgk::kBandMaxDegree) tiles.push_back(h->opts.tile == 32 ? Cand{32, false} : Cand{0, true});
+    tiles.push_back({16, false});
     // automatic grid, half the compute units, whole columns per block (large launches)
     std::vector<int> blocks = {0, std::max(1, h->num_cu / 2), -1};
     double best = 1e300;
-    int bt = choose_tile(h, degree), bb = h->pcg_max_blocks;
-    for (int t : tiles)
+    Cand bt = tiles[0];
+    int bb = h->pcg_max_blocks;
+    for (const Cand& t : tiles)
       for (int mb : blocks) {
-        h->opts.tile = t;
+        h->opts.tile = t.tile;
+        h->tiles_only = t.tiles_only;
         h->pcg_max_blocks = mb;
         if (use_sine(h) && mb != 0) continue;  // its launches take no block cap
         int rc = h->opts.inner_precision == 32 ? run_pcg<float>(h, (const float*)h->rw, (float*)h->zw, ncols, -1)
@@ -1318,7 +1325,8 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
           bb = mb;
         }
       }
-    h->opts.tile = bt;
+    h->opts.tile = bt.tile;
+    h->tiles_only = bt.tiles_only;
     h->pcg_max_blocks = bb;
     R.pcg_ms = best;
     h->inner_it_acc = 0;
@@ -1616,6 +1624,7 @@ int sg_set_opts(sg_handle h, const sg_opts* opts) {
     return fail(SG_EINVAL, "inner precision is fixed at setup");
   const bool degree_changed = opts->cheb_degree != h->opts.cheb_degree;
   h->opts = *opts;
+  h->tiles_only = false;
   if (degree_changed && h->sine_ok) {
     build_sine_tables(h, false);
     SG_HIP(hipGetLastError());

@@ -520,6 +520,7 @@ struct sg_ctx {
   void* rw;  // inner-precision working residual, n x P
   void* zw;  // inner-precision output, n x P (FP32 only)
   void *pR0, *pR1, *pP0, *pP1, *pQ, *pZ;  // inner PCG state, n x maxcols
+  bool tiles_only = false;  // the tuner keeps automatic tiles (opts.tile = 0) from the sine basis
   bool sine_ok = false;   // tables of the sine-basis solver built (k_sine.hip)
   sgk::SineSizes sine{};
   void* sine_pack = nullptr;  // inner precision

@@ -26,6 +26,27 @@ def test_inner_kind_follows_the_options(n_e, maxit, tile, kind):
     solver.close()
 
 
+@pytest.mark.parametrize("prec", [64, 32])
+@pytest.mark.parametrize("tile,kinds,candidates", [(0, (0,), 7), (32, (16, 32), 6), (16, (16, 32), 6)])
+def test_autotune_stays_within_the_tiles_asked_for(tile, kinds, candidates, prec):
+    """A caller of square or banded tiles is moved between those two, three block
+    counts each; the sine basis is one candidate more with automatic tiles (on this
+    grid more than ten times faster than either, so it is the pick)."""
+    from paper_1205_1864_amd import binding as b
+    prob = make_problem("kind", 100, 3, 2, 0.2, 0.5)
+    print(f"autotune tile={tile} FP{prec}", flush=True)
+    solver = b.SGSolver(prob, b.Options(inner_precision=prec, cheb_degree=8, tile=tile))
+    rep = solver.sg_autotune(2)
+    assert rep["candidates"] == candidates and rep["pcg_tile"] in (16, 32)
+    assert solver.inner_kind() in kinds
+    F = b.to_device_block(prob.load_block())
+    U, st = solver.sg_solve(F, rtol=1e-8, maxit=100)
+    assert st["rc"] == 0 and st["true_relres"] <= 1.05e-8
+    solver.set_opts(b.Options(inner_precision=prec, cheb_degree=8))
+    assert solver.inner_kind() == 0
+    solver.close()
+
+
 @pytest.mark.parametrize("tile,n_e,kind", [(0, 20, 0), (32, 20, 32), (16, 20, 16), (0, 1026, 32)])
 def test_batch_inner_kind(tile, n_e, kind):
     from paper_1205_1864_amd import binding as b
