@@ -154,8 +154,9 @@ typedef struct sg_stats {
   double ms_matvec;           /* time in SG matvecs */
   double ms_inner;            /* device time of the inner PCG launches (HIP events on the stream; with
                                  use_graph, of the replayed preconditioner actions as a whole) */
-  double inner_bytes;         /* algorithmic bytes of those launches, per column: 10 n w in the sine
-                                 basis (15 n w from a warm start), whatever the iterations;
+  double inner_bytes;         /* algorithmic bytes of those launches, per column: in the sine basis,
+                                 whatever the iterations, 6 n w up to n_e = 65 (9 n w from a warm
+                                 start) and 10 n w (15 n w) above;
                                  (9 its + 6) n w with banded tiles, (10 its + 6) n w with 16 x 16
                                  tiles (3 n w when it stops at once; n w more from a warm start) */
   int64_t inner_launches;     /* number of inner PCG launches */

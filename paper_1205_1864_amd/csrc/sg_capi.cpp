@@ -545,8 +545,10 @@ int flush_inner(sg_ctx* h) {
       h->inner_it_acc += v;
       if (L.tile == 0) {
         // sine basis: four passes and the iteration each read and write a vector (warm: two more
-        // passes, and the iteration reads the guess)
-        h->inner_bytes_acc += (10.0 + (L.warm ? 5.0 : 0.0)) * (double)h->n * L.wsize;
+        // passes, and the iteration reads the guess); in one launch both directions of a
+        // transform are one pass
+        const bool one = h->nx <= sgk::kSineFusedNx;
+        h->inner_bytes_acc += (one ? (L.warm ? 9.0 : 6.0) : (L.warm ? 15.0 : 10.0)) * (double)h->n * L.wsize;
         mx = std::max(mx, v);
         continue;
       }
