@@ -74,7 +74,7 @@ struct Fold {
     return a - H < h1 ? wave(2, a - H) : wave(3, a - H - h1);
   }
   // items of the input, up to four entries each
-  __host__ __device__ int items(bool inv) const { return !four ? (ho + 1) / 2 : inv ? H - h1 : h1; }
+  __device__ int items(bool inv) const { return sine_items(N - 1, four ? 4 : 2, inv); }
   // entries (from 0) of item i; those that the item does not have repeat others
   template <bool INV>
   __device__ __forceinline__ void entries(int i, int (&e)[4]) const {
@@ -303,8 +303,6 @@ __device__ __forceinline__ int xcd_block(int b, int n) {
   return x * q + min(x, r) + (b >> 3);
 }
 
-constexpr int kPassBatch = 4;  // most items of a strip per thread
-
 // The products of a block: item = a tile of 16 outputs of a pair of parts, IT items
 // per wave of NB operand tiles each. The sine matrices come from L2, W steps at
 // a time while the last W are multiplied; the first are on their way while the
@@ -438,7 +436,7 @@ __global__ __launch_bounds__(kPassThreads) void sine_x_kernel(SineTables<T> tab,
   const int t = threadIdx.x, lane = t & 63;
   // this thread's u-th place in (rows x items): as many lanes to a row as it has items, in powers of two
   auto mine = [&](int items, int u, int& r, int& i) {
-    const int llog = items <= 8 ? 3 : items <= 16 ? 4 : items <= 32 ? 5 : 6;
+    const int llog = sine_lane_log(items);
     const int rstep = blockDim.x >> llog, rper = max(1, R / rstep), chunk = u / rper;
     r = (t >> llog) + (u - chunk * rper) * rstep;
     i = (t & ((1 << llog) - 1)) + (chunk << llog);
@@ -1066,40 +1064,20 @@ const T* column_base(const SineArgs<T>& A, int which) {
   return which == COL_B ? A.b : which == COL_X ? A.x : which == COL_S ? A.s : which == COL_S0 ? A.s0 : A.w;
 }
 
-// Shape of a pass: `parts` x `nq` tiles, for a ragged launch bounds of every grid up
-// to the longest (two products take ceil(nx / 32) tiles, four at most as many in
-// each of two pairs, rounded up).
-struct PassShape {
-  int nq, parts, items;
-  template <typename T>
-  PassShape(const SineTables<T>& t, bool ragged, int nx) : nq(t.nq), parts(t.parts) {
-    if (ragged) {
-      const int nt = ((nx + 1) / 2 + 15) / 16;
-      nq = (nt + 1) / 2;
-      parts = 4;
-    }
-    items = nq * parts / 2;
-  }
-  int threads() const { return items <= 4 ? 256 : items <= 8 ? 512 : 1024; }
-  // the padding of rows along x is the larger one
-  size_t lds(size_t elem, int width) const { return parts * (elem * width * (16 * nq + 16 / elem) + 128); }
-};
-
-// Strips of 32 rows or columns, or of 16 where 32 would leave the device half empty
-// (28 columns of 100^2: 5 to 6 us a pass against 7 to 8; from half a device of strips
-// of 32 on, 45 columns of 127^2, both take 7 to 8) or do not fit in LDS (more than 16
-// items, two a wave).
-template <typename F1, typename F2, typename F3>
-hipError_t pass_variant(const PassShape& sh, long lines, int num_cu, F1 wide, F2 narrow, F3 longest) {
-  if (sh.items > 16) return longest(16);
-  return (lines + 31) / 32 <= num_cu / 2 ? narrow(16) : wide(32);
+// The variant for strips of 32 or 16 lines and one or two product items a wave; refuses
+// a shape that the kernels do not provide for.
+template <typename T, typename F1, typename F2, typename F3>
+hipError_t pass_variant(const SinePass& sh, int nx, int parts, long all, int num_cu, F1 wide, F2 narrow, F3 longest) {
+  const int lines = sh.lines(all, num_cu);
+  if (!sh.served(nx, parts, lines, sizeof(T))) return hipErrorInvalidValue;
+  return sh.per_wave() == 2 ? longest(lines) : lines == 32 ? wide(lines) : narrow(lines);
 }
 
 // One pass over every column: `nx` the longest transform, C the columns of a ragged launch.
 template <typename T, bool INV, bool RAGGED>
 hipError_t x_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, const SineReset& reset,
                   int num_cu, hipStream_t s) {
-  const PassShape sh(A.tab, RAGGED, nx);
+  const SinePass sh(nx, RAGGED);
   const long rows = (long)A.ncols * nx;
   const T* in = RAGGED ? nullptr : column_base(A, from);
   T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
@@ -1113,15 +1091,15 @@ hipError_t x_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from
                        to, strips);
     return hipGetLastError();
   };
-  return pass_variant(
-      sh, rows, num_cu, [&](int R) { return launch(sine_x_kernel<T, INV, 2, 1, RAGGED>, R); },
+  return pass_variant<T>(
+      sh, nx, sine_sizes(nx).parts, rows, num_cu, [&](int R) { return launch(sine_x_kernel<T, INV, 2, 1, RAGGED>, R); },
       [&](int R) { return launch(sine_x_kernel<T, INV, 1, 1, RAGGED>, R); },
       [&](int R) { return launch(sine_x_kernel<T, INV, 1, 2, RAGGED>, R); });
 }
 
 template <typename T, bool INV, bool RAGGED>
 hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from, int to, int num_cu, hipStream_t s) {
-  const PassShape sh(A.tab, RAGGED, nx);
+  const SinePass sh(nx, RAGGED);
   const T* in = RAGGED ? nullptr : column_base(A, from);
   T* out = RAGGED ? nullptr : const_cast<T*>(column_base(A, to));
   auto launch = [&](auto kfn, int W) {
@@ -1133,8 +1111,8 @@ hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from
                        to, strips);
     return hipGetLastError();
   };
-  return pass_variant(
-      sh, (long)A.ncols * nx, num_cu, [&](int W) { return launch(sine_y_kernel<T, INV, 2, 1, RAGGED>, W); },
+  return pass_variant<T>(
+      sh, nx, sine_sizes(nx).parts, (long)A.ncols * nx, num_cu, [&](int W) { return launch(sine_y_kernel<T, INV, 2, 1, RAGGED>, W); },
       [&](int W) { return launch(sine_y_kernel<T, INV, 1, 1, RAGGED>, W); },
       [&](int W) { return launch(sine_y_kernel<T, INV, 1, 2, RAGGED>, W); });
 }

@@ -349,6 +349,60 @@ inline SineSizes sine_sizes(int nx) {
   z.pack = 256L * z.nq * z.nq;
   return z;
 }
+// Work items of a transform's input (inv: of the inverse one), up to four entries each.
+__host__ __device__ inline int sine_items(int nx, int parts, bool inv) {
+  const int H = (nx + 1) / 2, h1 = H / 2;
+  return parts == 2 ? (H + 1) / 2 : inv ? H - h1 : h1;
+}
+// Lanes of a pass along x that share a row, a power of two: its logarithm.
+__host__ __device__ inline int sine_lane_log(int items) { return items <= 8 ? 3 : items <= 16 ? 4 : items <= 32 ? 5 : 6; }
+
+constexpr int kPassBatch = 4;  // most items of a strip per thread
+// Shape of a pass: `parts` x `nq` tiles, for a ragged launch bounds of every grid up
+// to the longest (two products take ceil(nx / 32) tiles, four at most as many in
+// each of two pairs, rounded up).
+struct SinePass {
+  int nq, parts, items;  // items: pairs of product tiles
+  SinePass(int nx, bool ragged) {
+    const SineSizes z = sine_sizes(nx);
+    nq = z.nq;
+    parts = z.parts;
+    if (ragged) {
+      nq = (z.nt + 1) / 2;
+      parts = 4;
+    }
+    items = nq * parts / 2;
+  }
+  int threads() const { return items <= 4 ? 256 : items <= 8 ? 512 : 1024; }
+  // Strips of 32 rows or columns, or of 16 where 32 would leave the device half empty
+  // (28 columns of 100^2: 5 to 6 us a pass against 7 to 8; from half a device of strips
+  // of 32 on, 45 columns of 127^2, both take 7 to 8) or do not fit in LDS (more than 16
+  // items, two a wave).
+  int lines(long all, int num_cu) const { return items > 16 || (all + 31) / 32 <= num_cu / 2 ? 16 : 32; }
+  int per_wave() const { return items > 16 ? 2 : 1; }  // product items
+  // the padding of rows along x is the larger one
+  size_t lds(size_t elem, int lines) const { return parts * (elem * lines * (16 * nq + 16 / elem) + 128); }
+  // Most work items a thread meets on a grid of member_nx, whose transforms take
+  // member_parts products, in a launch of this shape: along x (rows dealt to powers of
+  // two of lanes) and along y (one column a thread).
+  int steps(int member_nx, int member_parts, int lines) const {
+    int most = 0;
+    for (int inv = 0; inv < 2; ++inv) {
+      const int n = sine_items(member_nx, member_parts, inv != 0);
+      const int log = sine_lane_log(n), rstep = threads() >> log, rper = lines / rstep > 1 ? lines / rstep : 1;
+      const int along_x = rper * ((n + (1 << log) - 1) >> log), lstep = threads() / lines;
+      const int along_y = (n + lstep - 1) / lstep;
+      most = most > along_x ? most : along_x;
+      most = most > along_y ? most : along_y;
+    }
+    return most;
+  }
+  // What the kernels provide for.
+  bool served(int member_nx, int member_parts, int lines, size_t elem) const {
+    return items <= per_wave() * threads() / 64 && steps(member_nx, member_parts, lines) <= kPassBatch &&
+           lds(elem, lines) <= 160 * 1024;
+  }
+};
 // The problem's constants behind the slot tables.
 struct SineConsts {
   int n_e;
