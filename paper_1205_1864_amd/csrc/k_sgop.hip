@@ -33,6 +33,11 @@ namespace {
 // 187 -> 77 / 100 us; before, one wave marched 16 rows, a chain of loads per row.
 // The same kernel without lane shifts (three loads per row) took 104 / 113 us
 // there, and 8 rows a wave 78 / 107 us.
+// That march read a large level once and a bit, so towards the lower level of many
+// terms it was ahead by a little on large grids: M = 8, p = 3, level 3 to 2 / 2 to 3,
+// 384^2 88 / 189 us against 96 / 119 now, 512^2 177 / 319 against 186 / 246 (both
+// directions are needed in an action). Stacking a block's waves in y instead of in x
+// gained nothing there (98 / 119 and 190 / 264 us).
 constexpr int kStripThreads = 256;
 
 // out0 and out1 receive the parts of the lower and the upper node row of an
@@ -347,12 +352,17 @@ void launch_stage(const SgOpArgs<double>& args, const StageJob& job, hipStream_t
 // Rows per wave (rows = 0): 4, which read 1.5 node rows and 1.25 element rows per
 // row, or 2 where a launch would have fewer than eight waves per compute unit
 // (the full operator at 32^2, M = 8, p = 3: 1320 waves of 4 rows 10 us, of 2 rows 8;
-// at 64^2, 5280 waves of 4 rows 15 us, of 2 rows 17).
+// at 64^2, 5280 waves of 4 rows 15 us, of 2 rows 17). Products with upper neighbours
+// only, which read the larger level, take 6 from some 6000 waves of 6 on (FP64, us with
+// 4 / 6 rows, level 3 to 2: 512^2, M = 8, 27 900 waves 182 / 174; 384^2, 16 100 96 / 93;
+// 256^2, M = 10, 11 800 89 / 88; level 2 to 1 there, 2150 waves 34 / 36). The other
+// direction does not gain (512^2, M = 8, level 2 to 3: 243 / 249).
 template <typename T>
 void launch_sgop(const SgOpArgs<T>& args, int rows, hipStream_t s) {
   if (args.nrows <= 0) return;
   const int strips = (args.nx + 61) / 62, width = (args.nx + strips - 1) / strips;
-  if (rows == 0) rows = (long)strips * ((args.nx + 3) / 4) * args.nrows < 2048 ? 2 : 4;
+  auto waves = [&](int r) { return (long)strips * ((args.nx + r - 1) / r) * args.nrows; };
+  if (rows == 0) rows = waves(4) < 2048 ? 2 : args.use_upper && !args.use_lower && waves(6) >= 6000 ? 6 : 4;
   if (rows <= 2) launch_strip<T, 2>(args, strips, width, s);
   else if (rows <= 4) launch_strip<T, 4>(args, strips, width, s);
   else if (rows <= 6) launch_strip<T, 6>(args, strips, width, s);
