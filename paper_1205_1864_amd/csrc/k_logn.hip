@@ -288,16 +288,21 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double (*red)[2
 // exchange after the next is complete (then every block has read them).
 // lpr lanes share an operator row; with TREG > 0 a lane keeps the element
 // coefficients of its (at most TREG) tasks in registers for the whole solve, so
-// the loop reads no memory but the exchange; its tasks are the blocks of one row or,
-// where a row has one block, several rows. Thread t holds the vector elements i = NT k + t;
-// x_i is kept by the block that k falls to (k % G, at most one k per block when
-// G >= VPT), or, if a block has several, in memory.
+// the loop reads no memory but the exchange (and the inverse diagonal beside more than
+// 8 unknowns a thread); its tasks are the blocks of one row or, where a row has one
+// block, several rows. As many are held as leave the registers unspilled: six beside 8
+// unknowns a thread, two beside 20 (with ten, 189 spilled registers made an iteration
+// of 16 x 16, N = 4, degree 4 11.5 us against 10.3, of two columns of 69^2 16.0 against
+// 10.3), none beside 38, where r and q alone spill (290 registers; 81 x 81, N = 2,
+// degree 2 25.8 us an iteration). Thread t holds the vector elements i = NT k + t; x_i
+// is kept by the block that k falls to (k % G, at most one k per block when G >= VPT),
+// or, if a block has several, in memory.
 // The stored blocks are numbered in the order of the rows' lists.
 // An iteration is a chain of latencies, not a stream: the exchange (one store and
 // its way to the others, about 2 us), two block sums and the tasks. 10 x 10, N = 4,
 // degree 4 (2835 unknowns of the top level): 63 us per iteration as four kernels
 // and two host round trips, 5.2 us here with 24 to 64 blocks (26 us with one block,
-// 8.4 with 8); 16 x 16: 10.2 us with 32 blocks, 67 with one.
+// 8.4 with 8); 16 x 16: 10.3 us with 32 blocks, 67 with one.
 // A wait that expires (blocks of this launch held back by other work on the device)
 // sets the status. A block that waits looks at it now and then and gives up too, here
 // and in every later launch; whether a block leaves is settled between two barriers.
@@ -561,7 +566,7 @@ bool logn_solve_shape(int n_e, int nr, int nsys, LognSolveArgs& A, int& nt, int&
   if (len > 38L * 512 || psize * 8 > lds_max) return false;
   nt = len <= 256 ? 64 : 512;
   vpt = nt == 64 ? 4 : len <= 2 * 512 ? 2 : len <= 8 * 512 ? 8 : len <= 20 * 512 ? 20 : 38;
-  const int held = vpt <= 8 ? 6 : vpt == 20 ? 10 : 0;  // tasks whose coefficients the kernel can hold
+  const int held = vpt <= 8 ? 6 : vpt == 20 ? 2 : 0;  // tasks whose coefficients the kernel can hold
   double best = 1e300;
   for (int G : {1, 2, 4, 8, 16, 24, 32, 48, 64}) {
     if (G > 1 && (G > len || nsys > 1 || nt == 64)) break;  // several systems take one block each
@@ -608,7 +613,7 @@ hipError_t launch_logn_solve(const LognSolveArgs& args, int nsys, hipStream_t s,
   };
   if (nt == 64) return treg ? launch(logn_solve_kernel<64, 4, 6>) : launch(logn_solve_kernel<64, 4, 0>);
   if (treg == 6) return vpt == 2 ? launch(logn_solve_kernel<512, 2, 6>) : launch(logn_solve_kernel<512, 8, 6>);
-  if (treg == 10) return launch(logn_solve_kernel<512, 20, 10>);
+  if (treg == 2) return launch(logn_solve_kernel<512, 20, 2>);
   return vpt == 2    ? launch(logn_solve_kernel<512, 2, 0>)
          : vpt == 8  ? launch(logn_solve_kernel<512, 8, 0>)
          : vpt == 20 ? launch(logn_solve_kernel<512, 20, 0>)

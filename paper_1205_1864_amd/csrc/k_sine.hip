@@ -881,7 +881,7 @@ struct ColumnSums {
 // z.K z + 2 beta z.K p + beta^2 p.q, so a single pass over the slots makes an
 // iteration (its rounding error is that of the three terms, at most cond(M K_0)
 // times p'.q'). All of a block's slots stay in registers (1 / pi and, beyond 11
-// slots a thread, what of t fits in LDS). Slots without a mode have v = 0 and t = 0.
+// slots a thread, what of t fits in LDS; of 27 slots 5 or 6 registers spill). Slots without a mode have v = 0 and t = 0.
 // Bound by the chain of an iteration: the arithmetic (about 0.8 us on 23 slots a
 // thread), the sums over the block (0.3 us) and across the group (1.2 us), so a
 // launch of many columns is faster the fewer blocks a column takes: as many slots
