@@ -304,8 +304,9 @@ __device__ __forceinline__ void block_sum2(double& a, double& b, double (*red)[2
 // and two host round trips, 5.2 us here with 24 to 64 blocks (26 us with one block,
 // 8.4 with 8); 16 x 16: 10.3 us with 32 blocks, 67 with one.
 // A wait that expires (blocks of this launch held back by other work on the device)
-// sets the status. A block that waits looks at it now and then and gives up too, here
-// and in every later launch; whether a block leaves is settled between two barriers.
+// sets the status, and in later launches the waves that find it set give up at their
+// first wait. Another block may set it while a block starts, so its waves may differ in
+// what they find: whether a block leaves is settled for all of it between two barriers.
 template <int NT, int VPT, int TREG>
 __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
   constexpr bool REG = TREG > 0;
@@ -314,6 +315,7 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
   __shared__ double red[2][NT / 64][2];
   __shared__ int dead;
   const int tid = threadIdx.x;
+  const long limit = __builtin_amdgcn_readfirstlane((int)agent_load(A.status)) != 0 ? 0 : A.spins;
   const int sys = blockIdx.x / A.G, g = blockIdx.x - sys * A.G;
   const int nx = A.n_e - 1, n = nx * nx, len = n * A.nr;
   const int RS = nx + 1, CS = RS * RS;  // row and column strides of the padded p
@@ -468,7 +470,7 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
 #pragma unroll
           for (int k = 0; k < VPT; ++k) miss |= empty(k);
           if (!__any(miss)) break;
-          if (spins >= A.spins || ((spins & 63) == 63 && agent_load(A.status) != 0)) {
+          if (spins >= limit) {
             dead = 1;  // the block leaves as a whole after its next barrier
             break;
           }
@@ -484,7 +486,10 @@ __global__ void __launch_bounds__(NT, 1) logn_solve_kernel(LognSolveArgs A) {
       block_sum2<NT>(pq, unused, red[1]);
       if (A.G > 1) {
         if (dead) {
-          if (tid == 0) __hip_atomic_store(A.status, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          if (tid == 0) {
+            agent_store(A.status, 1ull);
+            __hip_atomic_store(A.told, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+          }
           break;
         }
         if (it > 0 && sub == 0)

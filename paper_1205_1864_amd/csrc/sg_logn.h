@@ -21,7 +21,8 @@ struct LognSolveArgs {
   unsigned long long* ex;   // exchange, 3 n nr places (systems of several blocks)
   int *first, *last;        // [P] stored blocks of the sub-block per chaos row
   unsigned long long* its;  // CG iterations, added to
-  unsigned long long* status;  // host memory, set if a bounded wait expired
+  unsigned long long* status;  // set if a bounded wait expired
+  unsigned long long* told;    // the same in host memory
   long spins;               // polls of an exchange before a wait expires
 };
 

@@ -57,10 +57,11 @@ struct sg_logn_ctx {
   double *cr = nullptr, *cz = nullptr, *cp = nullptr, *cq = nullptr, *Dinv = nullptr, *part = nullptr;
   double* XF = nullptr;  // forward-sweep values of block Gauss-Seidel
   std::vector<double> host_part;
-  // one-launch block solves: stored blocks per row, iteration count, and the status in
-  // pinned memory (the host looks at it wherever it waits for the stream anyway)
+  // one-launch block solves: stored blocks per row, iteration count and status, the latter
+  // also in pinned memory (the host looks at it wherever it waits for the stream anyway)
   int* first = nullptr;
   unsigned long long* its_d = nullptr;
+  unsigned long long* status_d = nullptr;
   unsigned long long* status = nullptr;
   long repeats = 0;   // solves repeated with their iterations on the host
   int repeat_it = 0;  // outer iteration in which the last of them was given up
@@ -237,7 +238,7 @@ int plan(const sg_problem* pr, Plan& pl) {
   pl.o_vec = take(tot, sizeof(double) * nP * 12);
   pl.o_part = take(tot, sizeof(double) * 2 * kLognDotBlocks);  // two partial sets
   pl.o_first = take(tot, sizeof(int) * 2 * pl.P);
-  pl.o_count = take(tot, sizeof(unsigned long long));
+  pl.o_count = take(tot, 2 * sizeof(unsigned long long));
   pl.total = tot;
   return SG_OK;
 }
@@ -287,7 +288,8 @@ int range_solve(sg_logn_ctx* h, int kind, int lo, int nr, const double* B, doubl
     a.first = h->first;
     a.last = h->first + h->P;
     a.its = h->its_d;
-    a.status = h->status;
+    a.status = h->status_d;
+    a.told = h->status;
     a.spins = h->spins;
     bool done = false;
     SG_HIP(sgk::launch_logn_solve(a, nsys, s, &done));
@@ -394,8 +396,8 @@ int solve_fcg(sg_logn_ctx* h, int precond, const double* F, double* U, double rt
   sgk::launch_logn_axpby(nP, 0.0, F, 0.0, U, 0, nullptr, 0, s);  // U = 0
   sgk::launch_logn_axpby(nP, 1.0, F, 0.0, h->R, 0, nullptr, 0, s);
   *h->status = 0;  // the last solve waited for its launches
-  const unsigned long long zero = 0;
-  SG_HIP(hipMemcpyAsync(h->its_d, &zero, sizeof(zero), hipMemcpyHostToDevice, s));
+  const unsigned long long zero[2] = {0, 0};
+  SG_HIP(hipMemcpyAsync(h->its_d, zero, sizeof(zero), hipMemcpyHostToDevice, s));
   double ff = 0.0, rr = 0.0;
   int rc = dotp(h, F, F, nP, ff);  // waits for the stream
   if (rc) return rc;
@@ -542,6 +544,7 @@ int sg_logn_setup(const sg_problem* pr, void* workspace, size_t workspace_bytes,
     h->host_part.assign(2 * kLognDotBlocks, 0.0);
     h->first = (int*)(w + pl.o_first);
     h->its_d = (unsigned long long*)(w + pl.o_count);
+    h->status_d = h->its_d + 1;
     if (const char* v = std::getenv("SGPC_LOGN_SPINS")) h->spins = std::max(0L, std::atol(v));
     h->off.assign(1, 0);
     for (int d = 0; d <= pr->p; ++d) {
