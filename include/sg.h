@@ -104,7 +104,8 @@ typedef struct sg_problem {
  *                     n_e = 1025 the same iteration in the sine basis, in
  *                     which K_0 and the preconditioner are diagonal (equal
  *                     iterates and counts up to rounding); on larger grids,
- *                     or with inner_maxit below n_e / 176, banded tiles, with
+ *                     or with inner_maxit below n_e / 176 (launches of one or
+ *                     two columns: up to n_e / 110), banded tiles, with
  *                     64-row bands for launches of fewer tiles than compute
  *                     units.
  *   warm_start        0: every inner solve starts from zero. 1: the inner
@@ -301,8 +302,10 @@ typedef struct sg_tune_report {
 
 int sg_autotune(sg_handle h, int32_t flags, sg_tune_report* report);
 
-/* Solver of the inner launches with the handle's present options and schedule:
- * *kind (host) = 0 the sine basis, 32 banded tiles, 16 square tiles. */
+/* Solver of an inner launch of all P columns with the handle's present options and
+ * schedule: *kind (host) = 0 the sine basis, 32 banded tiles, 16 square tiles. (At a
+ * very low inner_maxit launches of one or two columns may take banded tiles where
+ * longer ones take the sine basis.) */
 int sg_inner_kind(sg_handle h, int32_t* kind);
 
 /* Release the handle (the workspace stays with the caller). */

@@ -562,7 +562,7 @@ int sg_batch_setup(int32_t count, const sg_problem* probs, const sg_opts* opts, 
   // sine-basis tables per problem, where every member has them
   B->sine_classes = sine_classes(count, probs);
   B->sine_tabs = w + bp.o_sine_tabs;
-  B->sine_ok = std::all_of(B->h.begin(), B->h.end(), [](const sg_ctx* h) { return sgh::use_sine(h); }) &&
+  B->sine_ok = std::all_of(B->h.begin(), B->h.end(), [](const sg_ctx* h) { return sgh::use_sine(h, 3); }) &&
                B->h[0]->num_cu <= sgk::kSineMaxBlocks;
   B->sine = B->sine_ok;
   std::vector<char> tabs(sizeof(sgk::SineTables<double>) * count);

@@ -387,8 +387,23 @@ int choose_tile(const sg_ctx* h, int degree) {
 // iterations (0.13 on tiles at 1), 257 0.18 / 0.19 at 2, 512 0.50 / 0.50 at 2, 513
 // 0.69 / 0.69 at 3, 1024 1.5 / 1.5 at 3, 1023 2.2 / 2.3 at 5, so an iteration cap
 // below nx / 176 goes to the tiles.
-bool use_sine(const sg_ctx* h) {
-  return h->sine_ok && !h->tiles_only && h->opts.tile == 0 && h->opts.inner_maxit * 176L >= h->nx;
+// One or two columns leave most of the device idle in either solver, and an iteration on
+// tiles is a short launch's work (us of the sine basis / tiles, one column, FP64, degree
+// 1): 300^2 103 / 101 at 3 iterations, 400^2 122 / 110 at 3, 512^2 129 / 117 at 3 and about
+// even at 4, 1024^2 257 / 277 at 6; in two products a transform (n_e odd) 301^2 119 / 101
+// at 3, 513^2 168 / 158 at 5, 801^2 292 / 254 at 6, 1025^2 388 / 277 at 6, 388 / 347 at 8
+// and 397 / 417 at 10. Two columns at 1025^2: 406 / 385 at 6. Degree 4 and FP32 meet an
+// iteration or two earlier. Up to 128 rows the sine basis is ahead from the first on.
+// The tolerance is not looked at: it does not tell the count. To 0.5 at degree 1, 35 white
+// noise columns of 1025^2 stop after one iteration (3.5 ms / 1.0 on tiles), 35 smooth ones
+// after 497 (14.8 / 349 ms), and whole solves with inner_rtol 0.3 to 0.5 take 4 to 11 times
+// as long on tiles (256^2 to 1025^2).
+bool use_sine(const sg_ctx* h, int ncols) {
+  if (!h->sine_ok || h->tiles_only || h->opts.tile != 0) return false;
+  const long cap = h->opts.inner_maxit;
+  const bool few = ncols <= 2 && h->nx > 128;
+  if (few && ncols == 1 && h->sine.parts == 2 && cap * 110 < h->nx) return false;
+  return cap * 176 >= h->nx + (few ? 100 : 0);
 }
 
 template <typename T>
@@ -445,7 +460,7 @@ int run_pcg(sg_ctx* h, const T* B, T* X, int ncols, int level_for_stats, std::ve
   if (ncols > buf.maxcols) return fail(SG_EINVAL, "too many columns for the inner solver");
   sgk::PcgArgs<T> a{};
   const int degree = effective_degree(h);
-  const bool sine = use_sine(h);
+  const bool sine = use_sine(h, ncols);
   const int tile = sine ? 0 : choose_tile(h, degree);
   a.nx = h->nx;
   a.n = h->n;
@@ -1299,7 +1314,7 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
       bool tiles_only;
     };
     std::vector<Cand> tiles;
-    if (use_sine(h)) tiles.push_back({0, false});
+    if (use_sine(h, ncols)) tiles.push_back({0, false});
     if (degree <= sgk::kBandMaxDegree) tiles.push_back(h->opts.tile == 32 ? Cand{32, false} : Cand{0, true});
     tiles.push_back({16, false});
     // automatic grid, half the compute units, whole columns per block (large launches)
@@ -1312,7 +1327,7 @@ int autotune(sg_ctx* h, int flags, sg_tune_report* out) {
         h->opts.tile = t.tile;
         h->tiles_only = t.tiles_only;
         h->pcg_max_blocks = mb;
-        if (use_sine(h) && mb != 0) continue;  // its launches take no block cap
+        if (use_sine(h, ncols) && mb != 0) continue;  // its launches take no block cap
         int rc = h->opts.inner_precision == 32 ? run_pcg<float>(h, (const float*)h->rw, (float*)h->zw, ncols, -1)
                                                : run_pcg<double>(h, (const double*)h->rw, h->z, ncols, -1);
         if (rc) return rc;
@@ -1778,7 +1793,7 @@ int sg_autotune(sg_handle h, int32_t flags, sg_tune_report* report) {
 
 int sg_inner_kind(sg_handle h, int32_t* kind) {
   if (!h || !kind) return fail(SG_EINVAL, "null argument");
-  *kind = use_sine(h) ? 0 : choose_tile(h, effective_degree(h));
+  *kind = use_sine(h, h->P) ? 0 : choose_tile(h, effective_degree(h));
   return SG_OK;
 }
 

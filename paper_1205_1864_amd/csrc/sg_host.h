@@ -32,9 +32,9 @@ template <typename T>
 void fill_pcg_consts(const sg_ctx* h, sgk::PcgArgs<T>& a);
 // Chebyshev degree actually used, and the inner tile edge for that degree.
 int effective_degree(const sg_ctx* h);
-// Whether the inner solves run in the sine basis (automatic tiles, on grids
-// whose tables were built, unless the iteration cap is very low).
-bool use_sine(const sg_ctx* h);
+// Whether an inner launch of `ncols` columns runs in the sine basis (automatic tiles, on
+// grids whose tables were built, unless the iteration cap is very low).
+bool use_sine(const sg_ctx* h, int ncols);
 // Tables of the sine-basis solver on the handle's grid.
 template <typename T>
 sgk::SineTables<T> sine_tables(const sg_ctx* h);

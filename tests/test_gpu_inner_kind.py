@@ -1,21 +1,26 @@
 """The library tells which solver its inner launches take: the sine basis (0),
 banded (32) or square (16) tiles, by the options, the grid and the tuners."""
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
-from sg_inputs import make_problem  # noqa: E402
+from oracle import hsc, sg  # noqa: E402
+from sg_inputs import make_problem, random_block  # noqa: E402
 
 
-@pytest.mark.parametrize("n_e,maxit,tile,kind", [
-    (20, 1000, 0, 0), (20, 1000, 32, 32), (20, 1000, 16, 16),
-    # the cap below which few iterations go to the tiles: nx / 176
-    (300, 2, 0, 0), (300, 1, 0, 32), (1025, 6, 0, 0), (1025, 5, 0, 32), (1026, 1000, 0, 32),
+@pytest.mark.parametrize("n_e,M,maxit,tile,kind", [
+    (20, 2, 1000, 0, 0), (20, 2, 1000, 32, 32), (20, 2, 1000, 16, 16),
+    # the cap below which few iterations go to the tiles: nx / 176 for three columns
+    (300, 2, 2, 0, 0), (300, 2, 1, 0, 32), (1025, 2, 6, 0, 0), (1025, 2, 5, 0, 32), (1026, 2, 1000, 0, 32),
+    # (nx + 100) / 176 for two, and for one nx / 110 in two products a transform, (nx + 100) / 176 in four
+    (1025, 1, 7, 0, 0), (1025, 1, 6, 0, 32), (1025, 0, 10, 0, 0), (1025, 0, 9, 0, 32), (1024, 0, 7, 0, 0),
+    (1024, 0, 6, 0, 32), (129, 0, 1, 0, 0), (130, 0, 2, 0, 0), (130, 0, 1, 0, 32),
 ])
-def test_inner_kind_follows_the_options(n_e, maxit, tile, kind):
+def test_inner_kind_follows_the_options(n_e, M, maxit, tile, kind):
     from paper_1205_1864_amd import binding as b
-    prob = make_problem("kind", n_e, 0, 0, 0.2, 0.5)
+    prob = make_problem("kind", n_e, M, 1 if M else 0, 0.2, 0.5)
     opts = dict(inner_maxit=maxit, tile=tile)
     solver = b.SGSolver(prob, b.Options(**opts))
     assert solver.inner_kind() == kind
@@ -24,6 +29,28 @@ def test_inner_kind_follows_the_options(n_e, maxit, tile, kind):
     solver.set_opts(b.Options(**opts))
     assert solver.inner_kind() == kind
     solver.close()
+
+
+@pytest.mark.parametrize("prec,tol", [(64, 1e-11), (32, 1e-4)])
+@pytest.mark.parametrize("warm", [False, True])
+def test_an_action_on_both_solvers(warm, prec, tol):
+    """Two iterations a solve at 300^2: the mean's one column on tiles, the three of level
+    one in the sine basis (10 n w of bytes a column, (9 its + 6) n w on tiles, warm more);
+    the oracle's Algorithm 1 with the same inner PCG, to the fixed-iteration tolerances."""
+    from paper_1205_1864_amd import binding as b
+    prob = make_problem("both", 300, 3, 1, 0.3, 0.5)
+    s = sg.build_system(prob)
+    print(f"both solvers warm={warm} FP{prec}", flush=True)
+    solver = b.SGSolver(prob, b.Options(inner_precision=prec, cheb_degree=4, inner_maxit=2, inner_rtol=0.0,
+                                        warm_start=warm))
+    R = random_block(prob.P, prob.n, seed=12)
+    Z = solver.sg_apply_hsc(b.to_device_block(R)).cpu().numpy()
+    Zo = hsc.hsc_apply(s, R.T, hsc.PCGMeanSolver(s, 0.0, 2, 4), warm=warm).T
+    assert np.linalg.norm(Z - Zo) <= tol * np.linalg.norm(Zo)
+    _, st = solver.sg_solve(b.to_device_block(prob.load_block()), rtol=1e-14, maxit=1)
+    solver.close()
+    assert st["inner_launches"] == 3
+    assert st["inner_bytes"] == (3 * 10 + 3 * (15 if warm else 10) + 9 * 2 + 6) * prob.n * (prec // 8)
 
 
 @pytest.mark.parametrize("prec", [64, 32])
