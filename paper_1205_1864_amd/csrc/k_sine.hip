@@ -602,6 +602,32 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
   int lane = threadIdx.x & 63;
   asm volatile("" : "+v"(lane));
   const int line = lane & 15, sub = lane >> 4, nx = F.N - 1;
+  // slot t takes tile t of the pair (two products) or the tile of pair t
+  const int pairs = F.four ? 2 : 1, steps = 4 * nq, part = nq * steps * 64;
+  V acc[kFusedSlots][2];
+  const T* f[kFusedSlots];
+  bool on[kFusedSlots];
+#pragma unroll
+  for (int t = 0; t < kFusedSlots; ++t) {
+    const int pr = F.four ? t : 0, ct = F.four ? 0 : t;
+    on[t] = ct < nq;
+    f[t] = pack + (2 * pr * nq + ct) * steps * 64;
+    acc[t][0] = V{0, 0, 0, 0};
+    acc[t][1] = V{0, 0, 0, 0};
+  }
+  int first[4], step[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) in_place(F, INV, p < 2 * pairs ? p : 0, first[p], step[p]);
+  T n0[kFusedSlots], n1[kFusedSlots];
+  auto load = [&](int k) {
+#pragma unroll
+    for (int t = 0; t < kFusedSlots; ++t)
+      if (on[t]) {
+        n0[t] = f[t][64 * k + lane];
+        n1[t] = f[t][part + 64 * k + lane];
+      }
+  };
+  load(0);  // on its way while the lines are folded
   wave_fence();
   // fold
   if (!INV) {
@@ -639,32 +665,7 @@ __device__ __forceinline__ void line_transform(const Fold& F, int nq, const T* p
     }
   }
   wave_fence();
-  // products: slot t takes tile t of the pair (two products) or the tile of pair t
-  const int pairs = F.four ? 2 : 1, steps = 4 * nq, part = nq * steps * 64;
-  V acc[kFusedSlots][2];
-  const T* f[kFusedSlots];
-  bool on[kFusedSlots];
-#pragma unroll
-  for (int t = 0; t < kFusedSlots; ++t) {
-    const int pr = F.four ? t : 0, ct = F.four ? 0 : t;
-    on[t] = ct < nq;
-    f[t] = pack + (2 * pr * nq + ct) * steps * 64;
-    acc[t][0] = V{0, 0, 0, 0};
-    acc[t][1] = V{0, 0, 0, 0};
-  }
-  int first[4], step[4];
-#pragma unroll
-  for (int p = 0; p < 4; ++p) in_place(F, INV, p < 2 * pairs ? p : 0, first[p], step[p]);
-  T n0[kFusedSlots], n1[kFusedSlots];
-  auto load = [&](int k) {
-#pragma unroll
-    for (int t = 0; t < kFusedSlots; ++t)
-      if (on[t]) {
-        n0[t] = f[t][64 * k + lane];
-        n1[t] = f[t][part + 64 * k + lane];
-      }
-  };
-  load(0);
+  // products
   for (int k = 0; k < steps; ++k) {
     T w0[kFusedSlots], w1[kFusedSlots], x[4];
 #pragma unroll
