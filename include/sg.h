@@ -270,9 +270,10 @@ int sg_adjoint_grad(sg_handle h, const double* U, const double* w_mean, const do
 
 /* Schedule autotuner. Times candidate launch schedules on this handle's own
  * grid and chaos sizes and keeps the fastest for all later calls:
- *   flags bit 0: the SG operator (strip kernel with 2, 4, 6 or 8 node rows per
- *                wave, which the coupling products keep, and for the full
- *                operator the row-staged kernel where it fits);
+ *   flags bit 0: the SG operator (strip kernel with automatic, 2, 4, 6 or 8 node
+ *                rows per wave, timed on the full operator and on the coupling
+ *                products of an action, and for the full operator the
+ *                row-staged kernel where it fits);
  *   flags bit 1: the inner PCG (with tile = 0 the sine basis where it serves
  *                the grid; square tiles and banded ones, for tile = 0 and 16
  *                with the automatic band heights; block count automatic, half

@@ -74,6 +74,34 @@ def test_autotune_stays_within_the_tiles_asked_for(tile, kinds, candidates, prec
     solver.close()
 
 
+@pytest.mark.parametrize("prec,pc", [(64, "hsc"), (32, "bgs"), (64, "mean")])
+@pytest.mark.parametrize("n_e,M,p", [(40, 5, 3), (130, 4, 2), (20, 2, 0)])
+def test_tuned_operator_and_couplings(n_e, M, p, prec, pc):
+    """The operator's tuner reports a kernel that exists and a schedule with which the
+    operator and the coupling products are the oracle's (chaos without a coupling too)."""
+    from paper_1205_1864_amd import binding as b
+    prob = make_problem("tune", n_e, M, p, 0.2, 0.5)
+    s = sg.build_system(prob)
+    print(f"operator tuner n_e={n_e} FP{prec} {pc}", flush=True)
+    solver = b.SGSolver(prob, b.Options(inner_precision=prec, precond=pc))
+    rep = solver.sg_autotune(1)
+    assert rep["mv_variant"] in (3, 4) and rep["mv_ms"] > 0 and rep["candidates"] >= 5
+    assert rep["mv_param"] in (0, 200, 400, 600, 800) if rep["mv_variant"] == 3 else rep["mv_param"] > 0
+    U = random_block(prob.P, prob.n, seed=4)
+    Ud = b.to_device_block(U)
+    Yo = sg.matvec(s, U.T.copy()).T
+    assert np.linalg.norm(solver.sg_matvec(Ud).cpu().numpy() - Yo) <= 1e-12 * np.linalg.norm(Yo)
+    for level in range(1, p + 1):
+        lo, hi = s.off[level], s.off[level + 1]
+        below = s.off[level - 1]
+        R = random_block(prob.P, prob.n, seed=level)
+        Ro = R.T.copy()
+        Ro[:, below:lo] -= sg.level_block(s, slice(below, lo), slice(lo, hi))(U.T[:, lo:hi])
+        Rg = solver.sg_coupling(level, 0, b.to_device_block(R), Ud).cpu().numpy()
+        assert np.linalg.norm(Rg - Ro.T) <= 1e-13 * np.linalg.norm(Ro)
+    solver.close()
+
+
 @pytest.mark.parametrize("tile,n_e,kind", [(0, 20, 0), (32, 20, 32), (16, 20, 16), (0, 1026, 32)])
 def test_batch_inner_kind(tile, n_e, kind):
     from paper_1205_1864_amd import binding as b
