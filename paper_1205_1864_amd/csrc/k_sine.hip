@@ -9,9 +9,9 @@
 // Why: on the grid an iteration of degree d sweeps a column d times with halos
 // and meets two column-wide synchronisations; here it is a dozen operations per
 // pair of modes on values that never leave the registers. Measured at 256^2,
-// degree 16, FP64: the 220 columns of the top level to 1e-4 (about 30
-// iterations) 13.5 ms on banded tiles, 0.63 ms here; the benchmark's whole solve
-// 230 -> 18.5 ms; 28 columns of 100^2 unknowns at degree 8 730 -> 118 us.
+// degree 16, FP64: 220 white-noise columns to 1e-4 (34 iterations) 15.7 ms on banded
+// tiles, 0.66 ms here; the benchmark's whole solve 230 -> 18 ms; 28 columns of 100^2
+// unknowns at degree 8 730 -> 102 us.
 #include <algorithm>
 
 #include "sg_internal.h"
@@ -882,7 +882,8 @@ struct ColumnSums {
 // z.K z + 2 beta z.K p + beta^2 p.q, so a single pass over the slots makes an
 // iteration (its rounding error is that of the three terms, at most cond(M K_0)
 // times p'.q'). All of a block's slots stay in registers (1 / pi and, beyond 11
-// slots a thread, what of t fits in LDS; of 27 slots 5 or 6 registers spill). Slots without a mode have v = 0 and t = 0.
+// slots a thread, what of t fits in LDS; of 27 slots 5 or 6 registers spill). Slots
+// without a mode have v = 0 and t = 0.
 // Bound by the chain of an iteration: the arithmetic (about 0.8 us on 23 slots a
 // thread), the sums over the block (0.3 us) and across the group (1.2 us), so a
 // launch of many columns is faster the fewer blocks a column takes: as many slots
@@ -1113,7 +1114,8 @@ hipError_t y_pass(const SineArgs<T>& A, const SineRagged<T>& C, int nx, int from
     return hipGetLastError();
   };
   return pass_variant<T>(
-      sh, nx, sine_sizes(nx).parts, (long)A.ncols * nx, num_cu, [&](int W) { return launch(sine_y_kernel<T, INV, 2, 1, RAGGED>, W); },
+      sh, nx, sine_sizes(nx).parts, (long)A.ncols * nx, num_cu,
+      [&](int W) { return launch(sine_y_kernel<T, INV, 2, 1, RAGGED>, W); },
       [&](int W) { return launch(sine_y_kernel<T, INV, 1, 1, RAGGED>, W); },
       [&](int W) { return launch(sine_y_kernel<T, INV, 1, 2, RAGGED>, W); });
 }
